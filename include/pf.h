@@ -96,12 +96,11 @@ typedef struct {
                                 1, 2, or 0 = automatic (2 when halving the
                                 corner-force space in LDS lets more workgroups
                                 share a CU).  The result does not depend on it. */
-    int32_t damage_chunks;   /* element chunks of the damage CG passes per
-                                workgroup: 1, 2, or 0 = automatic (2 when halving
-                                the corner-value space in LDS lets all of a
-                                pass's workgroups be resident at once and one
-                                chunk does not).  The result does not depend
-                                on it. */
+    int32_t damage_chunks;   /* how the damage solve's set-up pass holds its
+                                tile's element values in LDS: 1 together, 2 one
+                                kind after the other in half the space, or 0 =
+                                automatic (2 when that lets more workgroups
+                                share a CU).  The result does not depend on it. */
 } pf_tile_opts_t;
 
 /* Material and model of one instance (Sec. 2.1-2.2).  Geometry-independent. */
@@ -129,11 +128,11 @@ typedef struct {
     double tol;              /* stop when max_i |r_i|/A_ii <= tol on free nodes and
                                 no node held at a bound has a scaled residual
                                 r_i/A_ii pointing inward by more than tol/4
-                                (held nodes beyond that are released) */
+                                (held nodes beyond that are released); with a
+                                polynomial preconditioner a CG run goes on
+                                until |M r| <= tol as well */
     int32_t max_iter;        /* CG rounds per solve, >= 1 (a round is one pass
-                                over the tiles and one reduction; with the
-                                Jacobi preconditioner one matrix-vector
-                                product) */
+                                over the tiles and one reduction) */
     int32_t check_every;     /* > 0: synchronise the stream to stop early: first
                                 after as many CG rounds as the handle's previous
                                 solve of the same kind needed (8 on the first
@@ -168,21 +167,26 @@ typedef struct {
                                 and resume, a step can be captured once as a
                                 HIP graph of a fixed number of rounds and
                                 continued, rarely, by a second graph. */
-    int32_t precond;         /* preconditioner of the CG runs.  0 or 1: Jacobi
+    int32_t precond;         /* preconditioner of the CG runs.  1: Jacobi
                                 (M = D^-1 on the free nodes).  2, 3 or 4: the
                                 Chebyshev-Jacobi polynomial of that degree,
                                 M = p(D^-1 A) D^-1, on the interval
-                                [lmax/10, lmax] where lmax is a Gershgorin
-                                bound of D^-1 A taken at set-up (so M is SPD);
-                                a round then makes `precond` matrix-vector
-                                products and one reduction, and max_iter and
-                                the iteration counts of pf_cg_stats_t count
-                                rounds.  Damage solve and adjoint alike. */
+                                [lmax/30, lmax] where lmax bounds the spectrum
+                                of D^-1 A (from the mesh, so M is SPD).  0: the
+                                degree that is fastest for the instance's size
+                                (the library's choice).  A round makes `degree`
+                                matrix-vector products, in one pass over the
+                                tiles, and one reduction; max_iter and the
+                                iteration counts of pf_cg_stats_t count rounds.
+                                On meshes whose tiles cannot keep that many
+                                rings of neighbours (a node with thousands of
+                                them) the largest degree that fits is used.
+                                Damage solve and adjoint alike. */
 } pf_cg_opts_t;
 
 /* Per-instance solve statistics, written to DEVICE memory by the solve. */
 typedef struct {
-    int32_t iters;           /* matrix-vector products */
+    int32_t iters;           /* CG rounds (passes over the tiles) */
     int32_t restarts;        /* active-set restarts */
     int32_t n_active;        /* nodes held at the lower bound at exit */
     int32_t flags;           /* PF_FLAG_* */
@@ -203,7 +207,7 @@ typedef struct {
     int32_t max_tile_nodes, max_tile_elems;
     int32_t tile_elems_total;        /* element records incl. halo copies */
     size_t device_bytes;             /* device memory held by the handle */
-    int32_t damage_chunks;           /* element chunks of the damage passes (1, 2) */
+    int32_t damage_chunks;           /* element chunks of the damage set-up pass (1, 2) */
 } pf_mesh_totals_t;
 
 /*
@@ -261,7 +265,7 @@ pf_status_t pf_explicit_step(pf_mesh_t m, const pf_params_t* p, const double* dt
  *   AT2: A = Gc l0 K + sum_e (Gc/l0 + 2 H_e) M^e,  b_i = sum 2 H_e A_e/3
  *   AT1: A = 3/4 Gc l0 K + sum_e 2 H_e M^e,        b_i = sum (2 H_e - 3 Gc/(8 l0)) A_e/3
  * K^e = A_e grad phi grad phi', consistent mass M^e_kl = A_e (1 + delta_kl)/12.
- * Solved matrix-free by Jacobi-preconditioned projected CG warm-started from
+ * Solved by preconditioned projected CG (pf_cg_opts_t.precond) warm-started from
  * d_prev: CG runs on the free nodes with the held nodes frozen at their
  * bound, and the held set is updated between CG runs (primal-dual active-set
  * steps, with a monotone projected-CG fallback) until the KKT conditions hold
@@ -483,7 +487,7 @@ pf_status_t pf_timer_read(pf_mesh_t m, int32_t family, double* total_ms, int64_t
  * was given (same layout and ownership; the pass reads d_prev, the bounds).
  * The last call must have stopped mid-solve in a conjugate-gradient
  * iteration (check_every = 0 and a round budget the solve did not reach)
- * with the Jacobi preconditioner, and no pf_step_backward call may have run
+ * with the default or the Jacobi preconditioner, and no pf_step_backward call may have run
  * on the handle since (its adjoint solve reuses the control blocks);
  * otherwise PF_ERR_ARG where the control blocks show it (the test reads them
  * back, a synchronisation of `stream`).  Each launch reads the

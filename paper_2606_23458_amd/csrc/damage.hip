@@ -38,32 +38,39 @@
 //     p = z + beta p,  s = w + beta s,  x += alpha p,  r -= alpha s,
 //     z = M r,  w = A z,  gamma = r'z,  delta = z'w,
 //     beta' = gamma'/gamma,  alpha' = gamma'/(delta' - beta' gamma'/alpha).
-// One round of the solve is one or two launches over the tile grid:
-//   k_dmg      one pass of the current phase for every tile of every
+// The preconditioner is the Chebyshev-Jacobi polynomial of D^-1 A (degree 1 is
+// Jacobi), applied inside the pass: a tile keeps `degree` rings of neighbours,
+// applies A once per degree on shrinking sets of rings, and needs nothing from
+// other tiles in between.  A round of degree 3 reads hardly more than one of
+// degree 1 (the vectors and the rows are read once) and a solve takes about
+// 0.36 times the rounds (CPU count on the 256x128 plate: 60 -> 22 at 1e-12,
+// 22 -> 8 at 1e-6).
+//
+// One round of the solve is one or two launches:
+//   k_cg_setup the solve's first restart: b, the diagonal and the rows of A that
+//              a tile multiplies by (owned nodes and rings) from the element
+//              operator, the start and its true residual;
+//   k_cg       one pass of the current phase for every row tile of every
 //              instance that is not done:
 //                restart / check: x-matvec in FP64, true residual, held-set
-//                  update (the first restart also assembles b, the diagonal
-//                  and the per-solve mass coefficients);
+//                  update;
 //                first: z = M r and w = A z of a new CG run;
-//                iterate: the vector updates above and w = A z, where each
-//                  tile recomputes z on its halo nodes from the previous
-//                  vectors, so no second pass is needed;
-//              and per-tile partial sums.  A pass takes its tile's elements
-//              in one or two chunks (the corner values of a chunk in LDS,
-//              each owned node adding them in its corner-list order), two
-//              where that lets every workgroup of the pass be resident at
-//              once (damage_chunks);
+//                iterate: the vector updates above, z = M r and w = A z, where
+//                  each tile recomputes r on its rings from the previous
+//                  vectors;
+//              both with per-tile partial sums;
 //   k_dmg_red  one workgroup per instance combines its tiles' partials in a
 //              fixed order (bitwise reproducible results) and advances the
 //              instance's state.
-// With the Jacobi preconditioner and instances of up to kFuseMaxTiles tiles
-// the combination instead runs at the end of k_dmg, in the instance's last
-// workgroup to finish (arrivals counted by integer atomics; same order, same
-// bits), so such a round is a single launch.
-// r, w, s and x are ping-pong pairs: a pass reads one half and writes the
-// other, so halo reads never race with the owners' writes.  No floating-point
-// atomics and no device-wide fences are used.  Linear mode (CG_LINEAR) solves
-// A_FF x_F = b_F for a fixed held set and is used by the adjoint step.
+// For instances of up to kFuseMaxTiles tiles the combination instead runs at
+// the end of the pass, in the instance's last workgroup to finish (arrivals
+// counted by integer atomics; same order, same bits), so a round is a single
+// launch.
+// (r, s), (w, z) and x are ping-pong pairs: a pass reads one half and writes
+// the other, so ring reads never race with the owners' writes.  No
+// floating-point atomics and no device-wide fences are used.  Linear mode
+// (CG_LINEAR) solves A_FF x_F = b_F for a fixed held set and is used by the
+// adjoint step.
 #include <climits>
 #include <cstring>
 
@@ -85,42 +92,48 @@ constexpr uint32_t kPartOps = (0u << 0) | (1u << 2) | (0u << 4) | (2u << 6) | (2
                               (0u << 14);
 
 template <typename T>
+struct alignas(2 * sizeof(T)) Two {
+  T x, y;
+};
+
+template <typename T>
 struct DmgArgs {
   DevMesh dm;
+  DevRows dr;
   const InstP<T>* __restrict__ ip;
   Ctl* ctl;
   double* part;
   const T* __restrict__ H;
-  const T* __restrict__ lb;
+  const T* __restrict__ lb;      // the caller's lower bound (internal order)
   const uint8_t* __restrict__ guess;
-  T* x0; T* x1;        // iterate pair (QP: workspaces; linear: the caller's x and a workspace)
-  T* r0; T* r1;        // residual pair
-  T* w0; T* w1;        // A z pair
-  T* s0; T* s1;        // A p pair
-  T* p;                // search direction (read and written by the owner only)
-  T* dout;             // damage solve: output array (read at set-up when start = 1)
-  T* mte;              // per-solve mass coefficient of each tile element
-  T* b; T* dinv;
-  uint8_t* W0; uint8_t* W1;   // held-set pair (flipped by restart and check passes)
+  T* dout;                       // damage solve: output array (read at set-up when start = 1); linear: x
+  const T* __restrict__ bin;     // linear: right-hand side (internal order)
+  const uint8_t* __restrict__ win;   // linear: held set (internal order)
+  // vectors in row order
+  double* x0; double* x1;        // iterate pair: FP64 in either mode, so that its rounding does not bound the
+                                 // true residual (in FP32 a linear solve's would sit at its tolerance)
+  Two<T>* rs0; Two<T>* rs1;      // (r, s = A p) pair
+  Two<T>* wz0; Two<T>* wz1;      // (w = A z, z) pair
+  T* p;                          // search direction (read and written by the owner only)
+  T* dim;                        // D^-1, negative on held nodes
+  T* rsum;                       // row sums of A
+  T* b;
+  T* lbr;                        // lower bound
+  uint8_t* W0; uint8_t* W1;      // held-set pair (flipped by restart and check passes)
   double tol;
   int32_t max_iter;
   int32_t kind;        // CG_QP or CG_LINEAR
   int32_t start;       // 1: extrapolated start for the damage solve
-  // Chebyshev-Jacobi preconditioner (degree cheb >= 2)
-  T* zb;               // z = M r of the current iteration (written by the A z pass)
-  T* y0; T* y1;        // Chebyshev iterate pair
-  T* dv;               // Chebyshev update direction (owner only)
-  int32_t cheb;        // polynomial degree
-  int32_t stage;       // pass within a round: 0 main pass, 1 .. cheb-2 Chebyshev steps, cheb-1 the A z pass
-  // combination of the round in the pass's last workgroup (Jacobi rounds):
-  // 0 none (a k_dmg_red launch follows), 1 combine and advance the solver,
-  // 2 combine and run the state machine without storing it (timing aid)
+  int32_t deg;         // polynomial degree (an instance runs min(deg, Ctl::dmax)); 0: Ctl::ddef
+  // combination of the round in the pass's last workgroup: 0 none (a
+  // k_dmg_red launch follows), 1 combine and advance the solver, 2 combine and
+  // run the state machine without storing it (timing aid)
   int32_t fuse;
   uint32_t* arrive;    // arrival counters (see kArriveGroup)
-  int32_t nch;         // element chunks of a pass (1, 2): the corner-value space holds 3 / nch values per element
+  int32_t nch;         // set-up: the elements' values in LDS together (1) or one after the other (2)
 };
 
-// Chebyshev-Jacobi preconditioner z = p(D^-1 A) D^-1 r: `cheb` steps of the
+// Chebyshev-Jacobi preconditioner z = p(D^-1 A) D^-1 r: `deg` steps of the
 // Chebyshev iteration for A y = r from y = 0 with Jacobi scaling on the
 // interval [lmax/kChebRatio, lmax] (Saad, Iterative Methods for Sparse Linear
 // Systems, Sec. 12.3): with theta, delta the centre and half-width of the
@@ -128,29 +141,12 @@ struct DmgArgs {
 //   y_1 = D^-1 r / theta,  d_0 = y_1,
 //   rho_j = 1/(2 sigma - rho_{j-1}),
 //   d_j = rho_j rho_{j-1} d_{j-1} + (2 rho_j/delta) D^-1 (r - A y_j),  y_{j+1} = y_j + d_j.
-// Every eigenvalue of D^-1 A lies in (0, lmax] (lmax a Gershgorin bound), where
+// Every eigenvalue of D^-1 A lies in (0, lmax] (lmax from pf_mesh_create), where
 // the polynomial is positive, so M is symmetric positive definite and CG
-// applies unchanged.
-constexpr double kChebRatio = 10.0;
-
-struct ChebCoef {
-  double inv_theta, c1, c2;   // 1/theta; c1, c2 of step j: d_j = c1 d_{j-1} + c2 D^-1 res
-};
-
-__device__ __forceinline__ ChebCoef cheb_coef(double lmax, int j) {
-  const double b = fmax(lmax, 1.0), a = b / kChebRatio;
-  const double theta = 0.5 * (b + a), delta = 0.5 * (b - a), sigma = theta / delta;
-  double rp = 1.0 / sigma, rj = rp;
-  for (int i = 1; i <= j; ++i) {
-    rp = rj;
-    rj = 1.0 / (2.0 * sigma - rp);
-  }
-  ChebCoef c;
-  c.inv_theta = 1.0 / theta;
-  c.c1 = rj * rp;
-  c.c2 = 2.0 * rj / delta;
-  return c;
-}
+// applies unchanged.  The ratio suits the operator's condition number of
+// about 30 at l0 = 2h: rounds at 1e-12 for degree 3 with ratios 10, 20, 30 are
+// 23, 22, 21 on the 256x128 plate (CPU).
+constexpr double kChebRatio = 30.0;
 
 __global__ void k_dmg_init(Ctl* ctl, int n_inst, int kind, int monotone) {
   const int k = blockIdx.x * blockDim.x + threadIdx.x;
@@ -176,6 +172,17 @@ __global__ void k_dmg_init(Ctl* ctl, int n_inst, int kind, int monotone) {
   c.resid = 0.0;
   c.pq = 0.0;
   c.ref = (kind == CG_QP) ? 1.0 : 0.0;
+  // steps of the Chebyshev iteration
+  const double lb = c.lmax, la = lb / kChebRatio;
+  const double theta = 0.5 * (lb + la), delta = 0.5 * (lb - la), sigma = theta / delta;
+  c.ith = 1.0 / theta;
+  double rp = 1.0 / sigma;
+  for (int j = 0; j < kMaxRing - 1; ++j) {
+    const double rj = 1.0 / (2.0 * sigma - rp);
+    c.ch1[j] = rj * rp;
+    c.ch2[j] = 2.0 * rj / delta;
+    rp = rj;
+  }
 }
 
 template <typename T>
@@ -183,535 +190,562 @@ __device__ __forceinline__ T clamp01(T v, T lo) {
   return v < lo ? lo : (v > T(1) ? T(1) : v);
 }
 
-template <typename T, int NPT, bool CHEB, bool FUSE, int NCH>
-__global__ __launch_bounds__(kBlock) void k_dmg(DmgArgs<T> a) {
-  __shared__ double red[8 * 4 * kWaves];
-  const int tile = tile_of_block(a.dm.n_tiles);
-  const TileRec t = a.dm.tiles[tile];
-  const Ctl* c = a.ctl + t.inst;
-  const int mode = c->mode;
-  if (mode == MODE_DONE) return;
-  // the corner lists do not depend on the solver state: their loads go
-  // first, once a finished solve's pass has left
-  StagedCorners<2, 12> scn;   // 256 threads: 512 offsets, 3072 corner ids in registers
-  stage_corners_load(a.dm, t, scn);
-  // Chebyshev steps and the A z pass follow the main pass of first / iterate rounds only
-  const int stage = CHEB ? a.stage : 0;
-  if (CHEB && stage > 0 && (mode == MODE_RESTART || mode == MODE_CHECK)) return;
-  const InstP<T> P = a.ip[t.inst];
-  const bool qp = (a.kind == CG_QP);
-  const bool projected = qp && (P.bounds == PF_BOUNDS_PROJECTED);
-  const bool monotone = projected && (c->flavor != 0);
-  const bool xpass = (mode == MODE_RESTART || mode == MODE_CHECK);
-  const bool iter = (mode == MODE_ITER);
-  const bool setup = xpass && (c->setup != 0);
-  const bool cut = xpass && (c->hit != 0);
-  const bool release = c->release != 0;
-  const bool cur1 = c->pbuf != 0;
-  const double alpha = c->alpha, beta = c->beta, amax = c->amax;
-  const T al = T(alpha), be = T(beta);
-  const double tol = a.tol;
-  // current halves (read) and next halves (written) of the pairs
-  const T* __restrict__ xc = cur1 ? a.x1 : a.x0;
-  const T* __restrict__ rc = cur1 ? a.r1 : a.r0;
-  const T* __restrict__ wc = cur1 ? a.w1 : a.w0;
-  const T* __restrict__ sc = cur1 ? a.s1 : a.s0;
-  T* xn_ = cur1 ? a.x0 : a.x1;
-  T* rn_ = cur1 ? a.r0 : a.r1;
-  T* wn_ = cur1 ? a.w0 : a.w1;
-  T* sn_ = cur1 ? a.s0 : a.s1;
-  const bool wcur1 = c->wbuf != 0;
-  const uint8_t* __restrict__ Wc = wcur1 ? a.W1 : a.W0;
-  uint8_t* Wn = wcur1 ? a.W0 : a.W1;
-
-  extern __shared__ __align__(16) unsigned char smem[];
-  const int nloc = t.n_own + t.n_halo;
-  T* sv = reinterpret_cast<T*>(smem);          // [nloc] the vector the pass multiplies by A
-  // after sv (8-byte aligned): iteration passes keep the element corner values
-  // of A^e z^e in T; restart and check passes keep them in FP64 (the true
-  // residual is then accurate to the rounding of x, not of an FP32 matvec) a
-  // chunk of elements at a time; the set-up sweep keeps those FP64 values
-  // beside its diagonal corners and loads
-  uint16_t* coffs = reinterpret_cast<uint16_t*>(sv + nloc);   // [n_own + 1] corner-list offsets
-  uint16_t* clist = coffs + t.n_own + 1;                     // [n_corner] corner ids
-  unsigned char* rest =
-      smem + ((size_t(nloc) * sizeof(T) + 2 * (size_t(t.n_own) + 1 + size_t(t.n_corner)) + 7) & ~size_t(7));
-  T* qc = reinterpret_cast<T*>(rest);          // [3 n_telem] (first, iterate)
-  double* qd = reinterpret_cast<double*>(rest); // [3 chunk]   (restart, check)
-  const int tid = threadIdx.x;
-
-
-  // Chebyshev coefficients of this pass's step (the main pass makes step 1)
-  ChebCoef chc{1.0, 0.0, 0.0};
-  if (CHEB) chc = cheb_coef(c->lmax, stage + 1);
-  const T ith = T(chc.inv_theta);
-  const T* __restrict__ ysrc = ((stage - 1) & 1) ? a.y1 : a.y0;   // y_j read by stage j-1 >= 1
-
-  // ---- phase 1: the vector to multiply, on owned and halo nodes -------------
-  double amin = INFINITY, ch = 0.0;
-  // first / iterate main passes: every owned-node load is issued before any
-  // update, and r, D^-1 and the held flag stay in registers for phase 3
-  const bool fast = !xpass && stage == 0;
-  T rz_r[NPT], di_r[NPT];
-  uint8_t wf_r[NPT];
-  if (fast) {
-    T rv_r[NPT], wc_r[NPT], sc_r[NPT], p_r[NPT], x_r[NPT], zb_r[NPT], lb_r[NPT];
-#pragma unroll
-    for (int r = 0; r < NPT; ++r) {
-      const int i = tid + r * kBlock;
-      const int g = t.node_begin + min(i, t.n_own - 1);
-      wf_r[r] = Wc[g];
-      di_r[r] = a.dinv[g];
-      rv_r[r] = rc[g];
-      if (iter) {
-        wc_r[r] = wc[g];
-        sc_r[r] = (beta == 0.0) ? T(0) : sc[g];
-        p_r[r] = (beta == 0.0) ? T(0) : a.p[g];
-        x_r[r] = xc[g];
-        zb_r[r] = CHEB ? a.zb[g] : T(0);
-        lb_r[r] = projected ? a.lb[g] : T(0);
-      }
-    }
-#pragma unroll
-    for (int r = 0; r < NPT; ++r) {
-      const int i = tid + r * kBlock;
-      if (i >= t.n_own) continue;
-      const int g = t.node_begin + i;
-      const uint8_t wf = wf_r[r];
-      const T di = di_r[r];
-      const T rv = rv_r[r];
-      T v;
-      if (!iter) {
-        v = wf ? T(0) : (CHEB ? di * rv * ith : di * rv);
-        rz_r[r] = rv;
-      } else {
-        const T sn = (beta == 0.0) ? wc_r[r] : wc_r[r] + be * sc_r[r];
-        const T rn = rv - al * sn;
-        v = wf ? T(0) : (CHEB ? di * rn * ith : di * rn);
-        const T zv = wf ? T(0) : (CHEB ? zb_r[r] : di * rv);
-        const T pv = (beta == 0.0) ? zv : zv + be * p_r[r];
-        const T xv = x_r[r];
-        T xn = xv + al * pv;
-        if (monotone && !wf) {
-          const double lbv = double(lb_r[r]);
-          if (pv < T(0)) amin = fmin(amin, (lbv - double(xv)) / double(pv));
-          if (pv > T(0)) amin = fmin(amin, (1.0 - double(xv)) / double(pv));
-          xn = clamp01<T>(xn, T(lbv));
-        } else if (projected && !wf) {
-          const double xd = double(xn);
-          if (double(lb_r[r]) - xd > tol || xd - 1.0 > tol) ch += 1.0;
-        }
-        a.p[g] = pv;
-        sn_[g] = sn;
-        xn_[g] = xn;
-        rn_[g] = rn;
-        rz_r[r] = rn;
-      }
-      sv[i] = v;
-    }
-  }
-  for (int i = fast ? t.n_own + tid : tid; i < nloc; i += kBlock) {
-    const bool own = i < t.n_own;
-    const int g = own ? t.node_begin + i : a.dm.halo_idx[t.halo_begin + (i - t.n_own)];
-    T v;
-    if (CHEB && stage > 0) {
-      v = ysrc[g];   // the Chebyshev iterate of the previous pass (0 on held nodes)
-    } else if (setup && qp) {
-      // start at d_prev (or its extrapolation in time), or at 1 where the guess
-      // holds the node at the upper bound
-      const T lbv = a.lb[g];
-      if (projected && a.guess && (a.guess[g] & PF_ACTIVE_UPPER)) {
-        v = T(1);
-      } else if (a.start) {
-        v = clamp01<T>(T(2) * lbv - a.dout[g], lbv);
-      } else {
-        v = lbv;
-      }
-    } else if (xpass) {
-      v = xc[g];
-      if (cut && Wc[g] == HELD_NONE) {
-        // monotone flavour: the last step cut at the first bound (step amax
-        // along p, whose A p is in the other half of the s pair), then a
-        // projected Jacobi-gradient step
-        const T am = T(amax);
-        const T xh = v + am * a.p[g];
-        const T rh = rc[g] - am * sn_[g];
-        v = clamp01<T>(xh + T(kExpandStep) * a.dinv[g] * rh, a.lb[g]);
-      }
-    } else if (!iter) {
-      // first pass of a CG run: z = M r (Jacobi), or y_1 = D^-1 r / theta (Chebyshev)
-      v = Wc[g] ? T(0) : (CHEB ? a.dinv[g] * rc[g] * ith : a.dinv[g] * rc[g]);
+// Held set, bounds and stopping values of one node at a restart or check: the
+// node's new held state, its iterate moved onto a bound it crossed, and the
+// pass's counts.
+struct NodeCheck {
+  double cf = 0.0, ca = -INFINITY, na = 0.0, ch = 0.0;
+  __device__ __forceinline__ void stop(uint8_t w, double sr) {
+    if (w) {
+      if (w != HELD_FIXED) ca = fmax(ca, w == HELD_UPPER ? -sr : sr);
+      na += 1.0;
     } else {
-      const uint8_t wf = Wc[g];
-      const T di = a.dinv[g];
-      const T rv = rc[g];
-      const T sn = (beta == 0.0) ? wc[g] : wc[g] + be * sc[g];   // s = A p of this iteration
-      const T rn = rv - al * sn;
-      // z of the next iteration (Jacobi), or the first Chebyshev iterate y_1
-      v = wf ? T(0) : (CHEB ? di * rn * ith : di * rn);
-      if (own) {
-        const T zv = wf ? T(0) : (CHEB ? a.zb[g] : di * rv);
-        const T pv = (beta == 0.0) ? zv : zv + be * a.p[g];
-        const T xv = xc[g];
-        T xn = xv + al * pv;
-        if (monotone && !wf) {
-          // largest step that keeps this node inside [d_prev, 1]
-          const double lbv = double(a.lb[g]);
-          if (pv < T(0)) amin = fmin(amin, (lbv - double(xv)) / double(pv));
-          if (pv > T(0)) amin = fmin(amin, (1.0 - double(xv)) / double(pv));
-          xn = clamp01<T>(xn, T(lbv));
-        } else if (projected && !wf) {
-          const double xd = double(xn);
-          if (double(a.lb[g]) - xd > tol || xd - 1.0 > tol) ch += 1.0;   // free node outside the bounds
-        }
-        a.p[g] = pv;
-        sn_[g] = sn;
-        xn_[g] = xn;
-        rn_[g] = rn;
-      }
+      cf = fmax(cf, fabs(sr));
     }
-    sv[i] = v;
   }
-  stage_corners_store(a.dm, t, scn, coffs, clist);
+  // what a check pass of this state would change: it would see the same x, held
+  // set and residual, so a restart whose free residual passes and which counts
+  // nothing here ends the solve itself
+  __device__ __forceinline__ void restart_would_change(uint8_t w, double lbv, double xv, double sr, double tol) {
+    const bool viol = w == HELD_NONE && (lbv - xv > tol || xv - 1.0 > tol);
+    const bool rel = (w == HELD_LOWER && sr > kRelease * tol) || (w == HELD_UPPER && sr < -kRelease * tol);
+    ch += (viol || rel) ? 1.0 : 0.0;
+  }
+};
 
-  // ---- set-up: load vector, Jacobi diagonal, per-solve mass coefficients ----
-  // The space after sv holds the corner values of one pass; restart and check
-  // passes (FP64 values) and the set-up sweep work through the tile's
-  // elements in chunks that fit it, each owned node adding the corners of a
-  // chunk in its fixed corner order.
-  const T* __restrict__ geo = static_cast<const T*>(a.dm.geo);
-  const size_t nte = size_t(a.dm.n_te);
+template <typename T>
+__device__ __forceinline__ void arrive_and_advance(const DmgArgs<T>& a, Ctl* c, int tile, int tile0, int ntiles,
+                                                   int n_tiles, int bnd, double* red);
+
+// Partials of a pass, in PT_* order, stored value-major [8][n_tiles] so the
+// reduction reads them coalesced; thread k holds value k.  FUSE: stored
+// through to the device-coherent level for the combination in this launch's
+// last workgroup.
+template <typename T, bool FUSE>
+__device__ __forceinline__ void finish_pass(const DmgArgs<T>& a, Ctl* c, double (&v)[8], int tile, int tile0, int ntiles,
+                                            int n_tiles, int bnd, double* red) {
+  const double tot = block_reduce_rows<8, kPartOps>(v, red);
+  if constexpr (FUSE) {
+    if (threadIdx.x < 8)
+      __hip_atomic_store(&a.part[size_t(threadIdx.x) * n_tiles + tile], tot, __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_AGENT);
+    arrive_and_advance(a, c, tile, tile0, ntiles, n_tiles, bnd, red);
+  } else {
+    if (threadIdx.x < 8) a.part[size_t(threadIdx.x) * n_tiles + tile] = tot;
+  }
+}
+
+// Stiffness part of the rows, sum phi_e K^e_ij over an entry's elements: once
+// per handle, and again when the toughness field changes (phi_e = 1 without
+// one).  The element operator's entries are kap phi_e K^e + mA (1 + delta_kl)
+// with K^e given by its off-diagonals K01, K02, K12 (its rows sum to zero).
+template <typename T>
+__global__ __launch_bounds__(kBlock) void k_rows_stiffness(DevMesh dm, DevRows dr) {
+  const RowTile* const tp = dr.tiles + blockIdx.x;
+  const T* __restrict__ kw = static_cast<const T*>(dm.kw);
+  const T* __restrict__ gcs = static_cast<const T*>(dm.gcs);
+  auto part = [&](uint32_t cd) {
+    if (cd == kNoCode) return 0.0;
+    const size_t te = dr.ete[tp->el0 + int(cd / 3u)];
+    return (gcs ? double(gcs[te]) : 1.0) * double(kw[size_t(cd % 3u) * size_t(dm.n_te) + te]);
+  };
+  auto entry = [&](uint2 cd) {
+    return Two<T>{T(part(cd.x & 0xffffu) + part(cd.x >> 16)), T(part(cd.y & 0xffffu) + part(cd.y >> 16))};
+  };
+  const size_t base = size_t(tp->slice0) * (kRowPairs * 64);
+  for (int i = threadIdx.x; i < tp->nslice * kRowPairs * 64; i += kBlock)
+    static_cast<Two<T>*>(dr.sv)[base + i] = entry(dr.code[base + i]);
+  const int2 x0 = dr.xs[tp->slice0], x1 = dr.xs[tp->slice0 + tp->nslice - 1];   // the tile's extra pairs are one run
+  for (int i = threadIdx.x; i < (x1.x + x1.y - x0.x) * 64; i += kBlock)
+    static_cast<Two<T>*>(dr.xsv)[size_t(x0.x) * 64 + i] = entry(dr.xcode[size_t(x0.x) * 64 + i]);
+}
+
+void rows_stiffness(pf_mesh_s* m, hipStream_t s) {
+  if (m->dtype == PF_F64)
+    hipLaunchKernelGGL(k_rows_stiffness<double>, dim3(m->dr.n_tiles), dim3(kBlock), 0, s, m->dm, m->dr);
+  else
+    hipLaunchKernelGGL(k_rows_stiffness<float>, dim3(m->dr.n_tiles), dim3(kBlock), 0, s, m->dm, m->dr);
+}
+
+// The first restart of a solve: the rows of this solve, A_ij = kap S_ij + the
+// mass coefficients of the pair's elements, the load and the diagonal, and the
+// true residual of the start,
+//   (A x)_i = sum_j A_ij (x_j - x_i) + x_i sum_e 4 mA_e.
+// The mass coefficients and loads of the tile's elements stand in LDS, together
+// or (nch = 2) one after the other in half the space; no value depends on that.
+// Sums in FP64, rounded once.  Bound by the bytes of the rows (S and the codes
+// read, A written).
+template <typename T, int RPT, bool FUSE>
+__global__ __launch_bounds__(kBlock) void k_cg_setup(DmgArgs<T> a) {
+  __shared__ double red[8 * 4 * kWaves];
+  const int tile = tile_of_block(a.dr.n_tiles);
+  const RowTile* const tp = a.dr.tiles + tile;
+  const int n_own = tp->nl[0], nall = tp->nl[1], node0 = tp->node0, halo0 = tp->halo0, slice0 = tp->slice0;
+  const int el0 = tp->el0;
+  Ctl* const c = a.ctl + tp->inst;
+  const InstP<T>* const P = a.ip + tp->inst;
+  const int bnd = P->bounds;
+  const bool qp = (a.kind == CG_QP);
+  const bool projected = qp && (bnd == PF_BOUNDS_PROJECTED);
+  const bool monotone = projected && (c->flavor != 0);
+  const double tol = a.tol;
+  const int deg = a.deg ? min(a.deg, c->dmax) : c->ddef;
+  const int nrow = tp->nl[deg - 1], nel = tp->nel[deg - 1];
+  const int tid = threadIdx.x;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  extern __shared__ __align__(16) unsigned char smem[];
+  T* const ya = reinterpret_cast<T*>(smem);   // [nall] the start
+  T* const sm = ya + nall;                    // [nel] mass coefficients (nch = 2: then the loads)
+  T* const sb = a.nch == 2 ? sm : sm + nel;   // [nel] loads
+
+  // the start: d_prev (or its extrapolation in time), or 1 where the guess
+  // holds the node at the upper bound; linear solves at the caller's x
+  for (int i = tid; i < nall; i += kBlock) {
+    const int g = a.dr.node[i < n_own ? node0 + i : a.dr.halo[halo0 + i - n_own]];
+    T v;
+    if (!qp) {
+      v = a.dout[g];
+    } else {
+      v = a.lb[g];
+      if (a.start) v = clamp01<T>(T(2) * v - a.dout[g], v);
+      if (projected && a.guess && (a.guess[g] & PF_ACTIVE_UPPER)) v = T(1);
+    }
+    ya[i] = v;
+  }
+  const T* __restrict__ area = static_cast<const T*>(a.dm.geo) + 6 * size_t(a.dm.n_te);
   // per-element toughness factor phi_e (Gc_e = Gc phi_e) scales every Gc
   // term of the element's operator and load; absent, phi_e = 1 exactly
   const T* __restrict__ gcs = static_cast<const T*>(a.dm.gcs);
-  // the element operator is kap phi_e K^e + mA (1 + delta_kl) with K^e given by
-  // its off-diagonals K01, K02, K12 (rows of K^e sum to zero), so a pass reads
-  // three values per element instead of the six gradients and the area:
-  //   (A^e z)_k = kap phi_e sum_{l != k} K_kl (z_l - z_k) + mA (z_k + z_0 + z_1 + z_2)
-  const T* __restrict__ kw = static_cast<const T*>(a.dm.kw);
-  // restart / check: FP64 sums of each owned node's corner values of A x
-  constexpr bool kFusedSetup = sizeof(T) == 8;   // the set-up sweep sums them too
-  double qacc[NPT];
-  // set-up: b and D^-1 of the owned nodes, kept for the true residual
-  T bset[NPT], dset[NPT];
-  if (setup) {
-    T dacc[NPT], bacc[NPT], sacc[NPT];
+  const T c0 = P->c0, cH = P->cH, b0 = P->b0, bH = P->bH;
+  for (int l = tid; l < nel; l += kBlock) {
+    const size_t te = a.dr.ete[el0 + l];
+    const T He = a.H[a.dr.egid[el0 + l]];
+    const T A = area[te];
+    const T ph = gcs ? gcs[te] : T(1);
+    sm[l] = (c0 * ph + cH * He) * A * T(1.0 / 12.0);
+    if (a.nch != 2) sb[l] = (b0 * ph + bH * He) * A * T(1.0 / 3.0);
+  }
+  __syncthreads();
+
+  const Two<T>* const SV = static_cast<const Two<T>*>(a.dr.sv);
+  const Two<T>* const XSV = static_cast<const Two<T>*>(a.dr.xsv);
+  Two<T>* const AV = static_cast<Two<T>*>(a.dr.av);
+  Two<T>* const XAV = static_cast<Two<T>*>(a.dr.xav);
+  const double kap = double(P->kap);
+  double qi[RPT], bs[RPT], rs[RPT], off[RPT];
 #pragma unroll
-    for (int r = 0; r < NPT; ++r) dacc[r] = T(0), bacc[r] = T(0), sacc[r] = T(0), qacc[r] = 0.0;
-    // One sweep over the tile's elements assembles the load, the diagonal and
-    // the mass coefficients and, in FP64, takes the FP64 corner values of A x
-    // with the same element operator (FP32 tiles take them in the restart
-    // sweep below, which measured faster there): per element 4 values of
-    // width w (7 with the Chebyshev preconditioner's absolute row sums), plus
-    // 3 doubles in FP64, as many elements per chunk as the corner space holds
-    // (chunks split each node's corner sequence without reordering it, so no
-    // sum depends on the chunking).
-    constexpr int eb = (kFusedSetup ? 3 * int(sizeof(double)) : 0) + (CHEB ? 7 : 4) * int(sizeof(T));
-    const int space = 3 * int(sizeof(T)) * (NCH == 1 ? t.n_telem : (t.n_telem + 1) / 2);
-    const int chs = max(1, space / eb);
-    double* qs = reinterpret_cast<double*>(rest);   // [3 chunk] FP64 corner values of A x (FP64 tiles)
-    T* dcs = reinterpret_cast<T*>(qs + (kFusedSetup ? 3 * chs : 0));   // [3 chunk] diagonal corners
-    T* bcs = dcs + 3 * chs;                         // [chunk]   load per corner
-    T* scs = bcs + chs;                             // [3 chunk] absolute row sums per corner (Chebyshev)
-    for (int e0 = 0; e0 < t.n_telem; e0 += chs) {
-      const int e1 = min(e0 + chs, t.n_telem);
-      __syncthreads();
-      for (int e = e0 + tid; e < e1; e += kBlock) {
-        const int te = t.telem_begin + e;
-        const T A = geo[6 * nte + te];
-        const T w01 = kw[te], w02 = kw[nte + te], w12 = kw[2 * nte + te];
-        const T ph = gcs ? gcs[te] : T(1);
-        const T kp = P.kap * ph;
-        const T He = a.H[a.dm.te_gid[te]];
-        const T mA = (P.c0 * ph + P.cH * He) * A * T(1.0 / 12.0);
-        a.mte[te] = mA;
-        const int l = e - e0;
-        // diagonal of K^e from the zero row sums
-        dcs[3 * l + 0] = kp * -(w01 + w02) + T(2) * mA;
-        dcs[3 * l + 1] = kp * -(w01 + w12) + T(2) * mA;
-        dcs[3 * l + 2] = kp * -(w02 + w12) + T(2) * mA;
-        bcs[l] = qp ? (P.b0 * ph + P.bH * He) * A * T(1.0 / 3.0) : T(0);
-        if (CHEB) {
-          // off-diagonal entries of the element matrix
-          const T o01 = fabs(kp * w01 + mA);
-          const T o02 = fabs(kp * w02 + mA);
-          const T o12 = fabs(kp * w12 + mA);
-          scs[3 * l + 0] = dcs[3 * l + 0] + o01 + o02;
-          scs[3 * l + 1] = dcs[3 * l + 1] + o01 + o12;
-          scs[3 * l + 2] = dcs[3 * l + 2] + o02 + o12;
-        }
-        if constexpr (kFusedSetup) {
-          const int c0 = a.dm.lc0[te], c1 = a.dm.lc1[te], c2 = a.dm.lc2[te];
-          const double k = double(kp), mm = double(mA);
-          const double d01 = w01, d02 = w02, d12 = w12;
-          const double s0 = sv[c0], s1 = sv[c1], s2 = sv[c2];
-          const double ss = s0 + s1 + s2;
-          qs[3 * l + 0] = k * (d01 * (s1 - s0) + d02 * (s2 - s0)) + mm * (s0 + ss);
-          qs[3 * l + 1] = k * (d01 * (s0 - s1) + d12 * (s2 - s1)) + mm * (s1 + ss);
-          qs[3 * l + 2] = k * (d02 * (s0 - s2) + d12 * (s1 - s2)) + mm * (s2 + ss);
-        }
+  for (int k = 0; k < RPT; ++k) {
+    qi[k] = bs[k] = rs[k] = off[k] = 0.0;
+    if ((wv + k * kWaves) * 64 >= nrow) continue;
+    const int i = tid + k * kBlock;
+    const bool own = i < n_own;
+    const double xi = own ? double(ya[i]) : 0.0;
+    const int sl = slice0 + wv + k * kWaves;
+    const int2 x = a.dr.xs[sl];
+    // one pair of entries; its first elements are those it stands for
+    auto pair = [&](Two<T> sv, uint2 cd, uint32_t cc, Two<T>& out) {
+      auto mass = [&](uint32_t e) { return e == kNoCode ? 0.0 : double(sm[e / 3u]); };
+      const double m0 = mass(cd.x & 0xffffu), m1 = mass(cd.y & 0xffffu);
+      out.x = T(kap * double(sv.x) + (m0 + mass(cd.x >> 16)));
+      out.y = T(kap * double(sv.y) + (m1 + mass(cd.y >> 16)));
+      if (!own) return;
+      rs[k] += m0;
+      rs[k] += m1;
+      if (a.nch != 2) {
+        if ((cd.x & 0xffffu) != kNoCode) bs[k] += double(sb[(cd.x & 0xffffu) / 3u]);
+        if ((cd.y & 0xffffu) != kNoCode) bs[k] += double(sb[(cd.y & 0xffffu) / 3u]);
       }
-      __syncthreads();
+      // from here on the entries as the passes read them
+      qi[k] += double(out.x) * (double(ya[cc & 0xffffu]) - xi);
+      qi[k] += double(out.y) * (double(ya[cc >> 16]) - xi);
+      off[k] += double(out.x) + double(out.y);
+    };
+    const size_t at = size_t(sl) * (kRowPairs * 64) + lane;
+    Two<T> sv[kRowPairs];
+    uint2 cd[kRowPairs];
+    uint32_t cc[kRowPairs];
 #pragma unroll
-      for (int r = 0; r < NPT; ++r) {
-        const int i = tid + r * kBlock;
-        if (i < t.n_own) {
-          const int j0 = coffs[i], j1 = coffs[i + 1];
-          for (int j = j0; j < j1; ++j) {
-            const int cc = clist[j];
-            const int e = cc / 3;
-            if (e >= e0 && e < e1) {
-              dacc[r] += dcs[cc - 3 * e0];
-              bacc[r] += bcs[e - e0];
-              if (CHEB) sacc[r] += scs[cc - 3 * e0];
-              if constexpr (kFusedSetup) qacc[r] += qs[cc - 3 * e0];
-            }
-          }
-        }
-      }
+    for (int q = 0; q < kRowPairs; ++q) sv[q] = SV[at + q * 64], cd[q] = a.dr.code[at + q * 64], cc[q] = a.dr.ac[at + q * 64];
+#pragma unroll
+    for (int q = 0; q < kRowPairs; ++q) {
+      Two<T> v;
+      pair(sv[q], cd[q], own ? cc[q] : 0u, v);
+      AV[at + q * 64] = v;
     }
+    for (int e = 0; e < x.y; ++e) {
+      const size_t xo = (size_t(x.x) + e) * 64 + lane;
+      Two<T> v;
+      pair(XSV[xo], a.dr.xcode[xo], own ? a.dr.xac[xo] : 0u, v);
+      XAV[xo] = v;
+    }
+  }
+  if (a.nch == 2) {
+    __syncthreads();
+    for (int l = tid; l < nel; l += kBlock) {
+      const size_t te = a.dr.ete[el0 + l];
+      sb[l] = (b0 * (gcs ? gcs[te] : T(1)) + bH * a.H[a.dr.egid[el0 + l]]) * area[te] * T(1.0 / 3.0);
+    }
+    __syncthreads();
 #pragma unroll
-    for (int r = 0; r < NPT; ++r) {
-      const int i = tid + r * kBlock;
-      if (i < t.n_own) {
-        const int g = t.node_begin + i;
-        if (qp) a.b[g] = bacc[r];
-        bset[r] = bacc[r];
-        dset[r] = T(1) / dacc[r];
-        a.dinv[g] = dset[r];
-        // Gershgorin bound of D^-1 A, carried to the reduction as -max in the
-        // min-combined slot (unused by restart passes)
-        if (CHEB) amin = fmin(amin, -double(sacc[r]) / double(dacc[r]));
-      }
+    for (int k = 0; k < RPT; ++k) {
+      if (tid + k * kBlock >= n_own) continue;
+      const int sl = slice0 + wv + k * kWaves;
+      const int2 x = a.dr.xs[sl];
+      auto add = [&](uint2 cd) {
+        if ((cd.x & 0xffffu) != kNoCode) bs[k] += double(sb[(cd.x & 0xffffu) / 3u]);
+        if ((cd.y & 0xffffu) != kNoCode) bs[k] += double(sb[(cd.y & 0xffffu) / 3u]);
+      };
+#pragma unroll
+      for (int q = 0; q < kRowPairs; ++q) add(a.dr.code[size_t(sl) * (kRowPairs * 64) + q * 64 + lane]);
+      for (int e = 0; e < x.y; ++e) add(a.dr.xcode[(size_t(x.x) + e) * 64 + lane]);
     }
   }
 
-  // partials: gamma = r'z, delta = z'Az, max free |r|/A_ii, max held "wants
-  // to leave" r/A_ii, held count, max |b|/A_ii (linear set-up), changes
-  double gam = 0.0, del = 0.0, cf = 0.0, ca = -INFINITY, na = 0.0, rb = 0.0;
-  if (xpass) {
-    // ---- restart / check: true residual b - A x with FP64 corner values ----
-    // (in FP64 the set-up sweep above has already summed them)
-    // FP64 corner values: 2 nch chunks in FP32 (3 doubles per element in the
-    // space of 6 floats), nch in FP64
-    const int nxc = (sizeof(T) == 4 ? 2 : 1) * NCH;
-    const int chx = (t.n_telem + nxc - 1) / nxc;
-    const bool summed = kFusedSetup && setup;
-    if (!summed) {
+  NodeCheck nc;
+  double rb = 0.0;   // max |b|/A_ii (linear solves)
 #pragma unroll
-      for (int r = 0; r < NPT; ++r) qacc[r] = 0.0;
-    }
-    for (int e0 = 0; !summed && e0 < t.n_telem; e0 += chx) {
-      const int e1 = min(e0 + chx, t.n_telem);
-      __syncthreads();
-      for (int e = e0 + tid; e < e1; e += kBlock) {
-        const int te = t.telem_begin + e;
-        const int c0 = a.dm.lc0[te], c1 = a.dm.lc1[te], c2 = a.dm.lc2[te];
-        const double w01 = kw[te], w02 = kw[nte + te], w12 = kw[2 * nte + te];
-        const double k = double(P.kap * (gcs ? gcs[te] : T(1))), mm = double(a.mte[te]);
-        const double s0 = sv[c0], s1 = sv[c1], s2 = sv[c2];
-        const double ss = s0 + s1 + s2;
-        const int l = e - e0;
-        qd[3 * l + 0] = k * (w01 * (s1 - s0) + w02 * (s2 - s0)) + mm * (s0 + ss);
-        qd[3 * l + 1] = k * (w01 * (s0 - s1) + w12 * (s2 - s1)) + mm * (s1 + ss);
-        qd[3 * l + 2] = k * (w02 * (s0 - s2) + w12 * (s1 - s2)) + mm * (s2 + ss);
-      }
-      __syncthreads();
-#pragma unroll
-      for (int r = 0; r < NPT; ++r) {
-        const int i = tid + r * kBlock;
-        if (i < t.n_own) {
-          const int j0 = coffs[i], j1 = coffs[i + 1];
-          for (int j = j0; j < j1; ++j) {
-            const int cc = clist[j];
-            const int e = cc / 3;
-            if (e >= e0 && e < e1) qacc[r] += qd[cc - 3 * e0];
-          }
-        }
-      }
-    }
-#pragma unroll
-    for (int r = 0; r < NPT; ++r) {
-      const int i = tid + r * kBlock;
-      if (i >= t.n_own) continue;
-      const int g = t.node_begin + i;
-      // linear solves read the caller's right-hand side
-      const T bi = (summed && qp) ? bset[r] : a.b[g];
-      const T ri = T(double(bi) - qacc[r]);
-      const T di = summed ? dset[r] : a.dinv[g];
-      const double sr = double(ri) * double(di);
-      T xv = sv[i];
-      uint8_t w = HELD_NONE;
-      if (!qp) {
-        w = Wc[g];
-        if (setup && w == HELD_NONE) rb = fmax(rb, fabs(double(bi) * double(di)));
-      } else if (projected) {
-        const T lbv = a.lb[g];
-        const uint8_t wold = Wc[g];
+  for (int k = 0; k < RPT; ++k) {
+    const int i = tid + k * kBlock;
+    if (i >= n_own) continue;
+    const int q0 = node0 + i;
+    const int g = a.dr.node[q0];
+    const T xv = ya[i];
+    const T rsv = T(4.0 * rs[k]);   // the rows of an element's mass matrix sum to 4 mA
+    const T bi = qp ? T(bs[k]) : a.bin[g];   // linear solves read the caller's right-hand side
+    const T ri = T(double(bi) - (double(rsv) * double(xv) + qi[k]));
+    const T di = T(1.0 / (double(rsv) - off[k]));   // the diagonal from the rows' sums
+    const double sr = double(ri) * double(di);
+    uint8_t w = HELD_NONE;
+    if (!qp) {
+      w = a.win[g];
+      if (w == HELD_NONE) rb = fmax(rb, fabs(double(bi) * double(di)));
+    } else {
+      const T lbv = a.lb[g];
+      a.lbr[q0] = lbv;
+      if (projected) {
         if (lbv >= T(1)) {
           w = HELD_FIXED;   // d_prev = 1: the node is fixed
-        } else if (mode == MODE_CHECK) {
-          const bool viol_lo = wold == HELD_NONE && double(lbv) - double(xv) > tol;
-          const bool viol_up = wold == HELD_NONE && double(xv) - 1.0 > tol;
-          const bool rel = (wold == HELD_LOWER && sr > kRelease * tol) || (wold == HELD_UPPER && sr < -kRelease * tol);
-          w = viol_lo ? HELD_LOWER : (viol_up ? HELD_UPPER : (rel ? HELD_NONE : wold));
-          if (viol_lo) xv = lbv;
-          if (viol_up) xv = T(1);
-          ch += (viol_lo || viol_up || rel) ? 1.0 : 0.0;
-        } else if (setup) {
+        } else {
           const uint8_t gs = a.guess ? a.guess[g] : uint8_t(0);
           w = ((gs & PF_ACTIVE_LOWER) && xv <= lbv) ? HELD_LOWER
                                                     : (((gs & PF_ACTIVE_UPPER) && xv >= T(1)) ? HELD_UPPER : HELD_NONE);
+          if (!monotone) nc.restart_would_change(w, double(lbv), double(xv), sr, tol);
+        }
+      }
+    }
+    a.b[q0] = bi;
+    a.rsum[q0] = rsv;
+    a.x1[q0] = double(xv);   // the halves that the state machine makes current
+    a.rs1[q0].x = ri;
+    a.W1[q0] = w;
+    a.dim[q0] = w ? -di : di;
+    nc.stop(w, sr);
+  }
+  double v[8] = {0.0, INFINITY, 0.0, nc.cf, nc.ca, nc.na, rb, nc.ch};   // in PT_* order
+  finish_pass<T, FUSE>(a, c, v, tile, c->rt0, c->nrt, a.dr.n_tiles, bnd, red);
+}
+
+// One pass of a solve over the row tiles, after the set-up.  RPT: rows (owned and
+// ring nodes) per thread.  The rows' entries and column ids sit in registers for the whole
+// pass (a row is multiplied deg times), the vector being multiplied in LDS.
+// With up to two rows per thread (small plates, bound by latency) the rows are
+// loaded with the vectors; with more (large plates, bound by bytes) after the
+// vectors' update, whose registers they then share.
+template <typename T, int RPT, bool FUSE>
+__global__ __launch_bounds__(kBlock, RPT <= 4 ? (RPT <= 2 ? 4 : 3) : 1) void k_cg(DmgArgs<T> a) {
+  __shared__ double red[8 * 4 * kWaves];
+  const int tile = tile_of_block(a.dr.n_tiles);
+  const RowTile* const tp = a.dr.tiles + tile;
+  const int n_own = tp->nl[0], n1 = tp->nl[1], n2 = tp->nl[2], n3 = tp->nl[3], n4 = tp->nl[4];
+  const int node0 = tp->node0, halo0 = tp->halo0, slice0 = tp->slice0, nslice = tp->nslice, inst = tp->inst;
+  auto nl = [&](int k) { return k == 0 ? n_own : (k == 1 ? n1 : (k == 2 ? n2 : (k == 3 ? n3 : n4))); };
+  Ctl* const c = a.ctl + inst;
+  const int mode = c->mode;
+  if (mode == MODE_DONE) return;
+  const InstP<T>* const P = a.ip + inst;
+  const int bnd = P->bounds;
+  const bool qp = (a.kind == CG_QP);
+  const bool projected = qp && (bnd == PF_BOUNDS_PROJECTED);
+  const bool monotone = projected && (c->flavor != 0);
+  const bool xpass = (mode == MODE_RESTART || mode == MODE_CHECK);
+  const bool iter = (mode == MODE_ITER);
+  const int tid = threadIdx.x;
+  if (iter && !monotone && a.dr.idle[tile]) {
+    // no free node here: z, p and the update of x are 0 (see the first pass)
+    double v[8] = {0.0, INFINITY, 0.0, 0.0, -INFINITY, 0.0, 0.0, 0.0};
+    finish_pass<T, FUSE>(a, c, v, tile, c->rt0, c->nrt, a.dr.n_tiles, bnd, red);
+    return;
+  }
+  const bool cur1 = c->pbuf != 0;
+  const double beta = c->beta;
+  const T al = T(c->alpha), be = T(beta);
+  const double tol = a.tol;
+  const int deg = a.deg ? min(a.deg, c->dmax) : c->ddef;
+  // current halves (read) and next halves (written) of the pairs
+  const double* __restrict__ xc = cur1 ? a.x1 : a.x0;
+  double* xn_ = cur1 ? a.x0 : a.x1;
+  const Two<T>* rsc = cur1 ? a.rs1 : a.rs0;
+  Two<T>* rsn = cur1 ? a.rs0 : a.rs1;
+  const Two<T>* wzc = cur1 ? a.wz1 : a.wz0;
+  Two<T>* wzn = iter ? (cur1 ? a.wz0 : a.wz1) : (cur1 ? a.wz1 : a.wz0);
+
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int nall = nl(xpass ? 1 : deg);       // nodes whose values the pass needs
+  T* const ya = reinterpret_cast<T*>(smem);   // the vector the pass multiplies by A, two halves
+  T* const yb = ya + nall;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int nh = nall - n_own;
+
+  // ---- the rows of this thread --------------------------------------------------
+  Two<T> av[RPT][kRowPairs];
+  uint32_t ac[RPT][kRowPairs];
+  int xb[RPT], xk[RPT];
+  T rsu[RPT];
+  Two<T>* const AV = static_cast<Two<T>*>(a.dr.av);
+  Two<T>* const XAV = static_cast<Two<T>*>(a.dr.xav);
+  auto load_rows = [&]() {
+#pragma unroll
+    for (int k = 0; k < RPT; ++k) {
+      const int sl = min(wv + k * kWaves, nslice - 1);
+      const size_t at = size_t(slice0 + sl) * (kRowPairs * 64) + lane;
+      const int2 x = a.dr.xs[slice0 + sl];
+      xb[k] = x.x, xk[k] = x.y;
+#pragma unroll
+      for (int q = 0; q < kRowPairs; ++q) {
+        ac[k][q] = a.dr.ac[at + q * 64];
+        av[k][q] = AV[at + q * 64];
+      }
+      rsu[k] = a.rsum[node0 + min(tid + k * kBlock, n_own - 1)];
+    }
+  };
+  // sum over row k of entry times f(value at the column)
+  auto row_sum = [&](int k, const auto* y, auto zero, auto f) {
+    auto s = zero;
+#pragma unroll
+    for (int q = 0; q < kRowPairs; ++q) {
+      s += f(av[k][q].x, y[ac[k][q] & 0xffffu]);
+      s += f(av[k][q].y, y[ac[k][q] >> 16]);
+    }
+    for (int e = 0; e < xk[k]; ++e) {
+      const size_t xo = (size_t(xb[k]) + e) * 64 + lane;
+      const Two<T> v = XAV[xo];
+      const uint32_t cc = a.dr.xac[xo];
+      s += f(v.x, y[cc & 0xffffu]);
+      s += f(v.y, y[cc >> 16]);
+    }
+    return s;
+  };
+  constexpr bool kEarlyRows = RPT <= 2;
+
+  // ---- loads of the node vectors --------------------------------------------------
+  int pos[RPT];
+#pragma unroll
+  for (int k = 0; k < RPT; ++k) {
+    const int i = tid + k * kBlock;
+    pos[k] = node0 + min(i, n_own - 1);
+    if (i >= n_own && nh > 0) pos[k] = a.dr.halo[halo0 + min(i - n_own, nh - 1)];
+  }
+  T dmv[RPT];
+#pragma unroll
+  for (int k = 0; k < RPT; ++k) dmv[k] = a.dim[pos[k]];
+
+  double amin = INFINITY, gam = 0.0, del = 0.0;
+  NodeCheck nc;
+  if (xpass) {
+    // ---- restart / check: true residual b - A x in FP64 -------------------------
+    double xv_[RPT];
+    T rv_[RPT];
+#pragma unroll
+    for (int k = 0; k < RPT; ++k) xv_[k] = xc[pos[k]], rv_[k] = rsc[pos[k]].x;
+    load_rows();
+    const bool cut = c->hit != 0, release = c->release != 0;
+    const uint8_t* Wc = c->wbuf ? a.W1 : a.W0;
+    uint8_t* Wn = c->wbuf ? a.W0 : a.W1;
+    double* const xs = reinterpret_cast<double*>(smem);
+    auto value = [&](int q, double v, T r, T dm) {
+      if (cut && Wc[q] == HELD_NONE) {
+        // monotone flavour: the last step cut at the first bound (step amax
+        // along p, whose A p is in the other half of its pair), then a
+        // projected Jacobi-gradient step
+        const double xh = v + c->amax * double(a.p[q]);
+        const T rh = r - T(c->amax) * rsn[q].y;
+        v = clamp01<double>(xh + double(T(kExpandStep) * fabs(dm) * rh), double(a.lbr[q]));
+      }
+      return v;
+    };
+#pragma unroll
+    for (int k = 0; k < RPT; ++k) {
+      const int i = tid + k * kBlock;
+      if (i < nall) xs[i] = value(pos[k], xv_[k], rv_[k], dmv[k]);
+    }
+    for (int i = RPT * kBlock + tid; i < nall; i += kBlock) {
+      const int q = a.dr.halo[halo0 + i - n_own];
+      xs[i] = value(q, xc[q], rsc[q].x, a.dim[q]);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < RPT; ++k) {
+      const int i = tid + k * kBlock;
+      if (i >= n_own) continue;
+      const int g = node0 + i;
+      const double xi = xs[i];
+      double xv = xi;
+      const double qi = double(rsu[k]) * xi + row_sum(k, xs, 0.0, [&](T e, double y) { return double(e) * (y - xi); });
+      const T ri = T(double(a.b[g]) - qi);
+      const T di = fabs(dmv[k]);
+      const double sr = double(ri) * double(di);
+      const uint8_t wold = Wc[g];
+      uint8_t w = wold;   // linear solves keep their held set; without bounds no node is held
+      if (projected) {
+        const double lbv = double(a.lbr[g]);
+        if (w == HELD_FIXED) {
+          // d_prev = 1: the node is fixed
+        } else if (mode == MODE_CHECK) {
+          const bool viol_lo = wold == HELD_NONE && lbv - xv > tol;
+          const bool viol_up = wold == HELD_NONE && xv - 1.0 > tol;
+          const bool rel = (wold == HELD_LOWER && sr > kRelease * tol) || (wold == HELD_UPPER && sr < -kRelease * tol);
+          w = viol_lo ? HELD_LOWER : (viol_up ? HELD_UPPER : (rel ? HELD_NONE : wold));
+          if (viol_lo) xv = lbv;
+          if (viol_up) xv = 1.0;
+          nc.ch += (viol_lo || viol_up || rel) ? 1.0 : 0.0;
         } else if (!monotone) {
-          w = wold;
+          nc.restart_would_change(w, lbv, xv, sr, tol);
         } else {
           const bool want_lo = ri < T(0) || (wold == HELD_LOWER && !(release && sr > kRelease * tol));
           const bool want_up = ri > T(0) || (wold == HELD_UPPER && !(release && sr < -kRelease * tol));
-          w = (xv <= lbv && want_lo) ? HELD_LOWER : ((xv >= T(1) && want_up) ? HELD_UPPER : HELD_NONE);
-        }
-        if (mode == MODE_RESTART && !monotone && w != HELD_FIXED) {
-          // what a check pass of this state would change: it would see the
-          // same x, held set and residual, so a restart whose free residual
-          // passes and which counts nothing here ends the solve itself
-          const bool viol = w == HELD_NONE && (double(lbv) - double(xv) > tol || double(xv) - 1.0 > tol);
-          const bool rel = (w == HELD_LOWER && sr > kRelease * tol) || (w == HELD_UPPER && sr < -kRelease * tol);
-          ch += (viol || rel) ? 1.0 : 0.0;
+          w = (xv <= lbv && want_lo) ? HELD_LOWER : ((xv >= 1.0 && want_up) ? HELD_UPPER : HELD_NONE);
         }
       }
       xn_[g] = xv;
-      rn_[g] = ri;
+      rsn[g].x = ri;   // s of this half may still be read by a neighbouring tile's cut
       Wn[g] = w;
-      if (w) {
-        if (w != HELD_FIXED) ca = fmax(ca, w == HELD_UPPER ? -sr : sr);
-        na += 1.0;
-      } else {
-        cf = fmax(cf, fabs(sr));
-      }
+      a.dim[g] = w ? -di : di;
+      nc.stop(w, sr);
     }
   } else {
-    // ---- first / iterate: corner values of A^e z^e in T ----------------------
-    // NCH chunks of the tile's elements; each owned node adds the chunk's
-    // entries of its corner list (ascending) from where the previous chunk
-    // stopped, so every node's sum runs in the same order for any NCH
-    T qacc[NPT];
-    int jc[NPT];
+    // ---- first / iterate ---------------------------------------------------------
+    if (!iter) {
+      // A tile whose owned nodes are all held does nothing in this CG run: z
+      // and p vanish there, x stays (in both halves of its pair), and r and A p
+      // of held nodes are read nowhere (the monotone flavour reads them).  Most
+      // tiles of an AT1 plate are such tiles.
+      bool free_node = monotone;
 #pragma unroll
-    for (int r = 0; r < NPT; ++r) qacc[r] = T(0);
-    const int che = NCH == 1 ? t.n_telem : (t.n_telem + NCH - 1) / NCH;
-#pragma unroll 1
-    for (int e0 = 0; e0 < t.n_telem; e0 += che) {
-      const int e1 = min(e0 + che, t.n_telem);
-      __syncthreads();
-      for (int e = e0 + tid; e < e1; e += kBlock) {
-        const int te = t.telem_begin + e;
-        const int c0 = a.dm.lc0[te], c1 = a.dm.lc1[te], c2 = a.dm.lc2[te];
-        const T w01 = kw[te], w02 = kw[nte + te], w12 = kw[2 * nte + te];
-        const T kp = P.kap * (gcs ? gcs[te] : T(1));
-        const T mA = a.mte[te];
-        const T s0 = sv[c0], s1 = sv[c1], s2 = sv[c2];
-        const T ss = s0 + s1 + s2;
-        const int l = e - e0;
-        qc[3 * l + 0] = kp * (w01 * (s1 - s0) + w02 * (s2 - s0)) + mA * (s0 + ss);
-        qc[3 * l + 1] = kp * (w01 * (s0 - s1) + w12 * (s2 - s1)) + mA * (s1 + ss);
-        qc[3 * l + 2] = kp * (w02 * (s0 - s2) + w12 * (s1 - s2)) + mA * (s2 + ss);
-      }
-      __syncthreads();
-#pragma unroll
-      for (int r = 0; r < NPT; ++r) {
-        const int i = tid + r * kBlock;
-        if (i >= t.n_own) continue;
-        const int j1 = coffs[i + 1];
-        if constexpr (NCH == 1) {
-          T q = T(0);
-          for (int j = coffs[i]; j < j1; ++j) q += qc[clist[j]];
-          qacc[r] = q;
-        } else {
-          const int cend = 3 * e1, cbeg = 3 * e0;
-          int j = (e0 == 0) ? int(coffs[i]) : jc[r];
-          T q = qacc[r];
-          for (; j < j1; ++j) {
-            const int cc = clist[j];
-            if (cc >= cend) break;
-            q += qc[cc - cbeg];
-          }
-          qacc[r] = q;
-          jc[r] = j;
-        }
+      for (int k = 0; k < RPT; ++k) free_node = free_node || (tid + k * kBlock < n_own && !(dmv[k] < T(0)));
+      const bool idle = !__syncthreads_or(free_node);
+      if (tid == 0) a.dr.idle[tile] = idle;
+      if (idle) {
+        for (int i = tid; i < n_own; i += kBlock) xn_[node0 + i] = xc[node0 + i];
+        double v[8] = {0.0, INFINITY, 0.0, 0.0, -INFINITY, 0.0, 0.0, 0.0};
+        finish_pass<T, FUSE>(a, c, v, tile, c->rt0, c->nrt, a.dr.n_tiles, bnd, red);
+        return;
       }
     }
-    T* wn = iter ? wn_ : (cur1 ? a.w1 : a.w0);
-    const T* rz = iter ? rn_ : rc;
-    T* ydst = (stage & 1) ? a.y1 : a.y0;
+    const T ith = deg > 1 ? T(c->ith) : T(1);
+    T r_[RPT], y_[RPT], d_[RPT];   // residual, Chebyshev iterate and its update of this thread's rows
+    Two<T> rsv[RPT], wzv[RPT];
+    T pv_[RPT], lbv_[RPT];
+    double xv_[RPT];
 #pragma unroll
-    for (int r = 0; r < NPT; ++r) {
-      const int i = tid + r * kBlock;
-      if (i >= t.n_own) continue;
-      const int g = t.node_begin + i;
-      const T qi = qacc[r];
-      if (CHEB && stage < a.cheb - 1) {
-        // Chebyshev step stage + 1: qi = A y_j; d_j and y_{j+1} = y_j + d_j (0 on held nodes)
-        const uint8_t w = fast ? wf_r[r] : Wc[g];
-        const T rv = fast ? rz_r[r] : rz[g];
-        const T yv = sv[i];
-        const T res = (fast ? di_r[r] : a.dinv[g]) * (rv - qi);
-        const T dj = w ? T(0) : T(chc.c1) * (stage == 0 ? yv : a.dv[g]) + T(chc.c2) * res;
-        ydst[g] = w ? T(0) : yv + dj;
-        a.dv[g] = dj;
-        if (stage == 0) {
-          const double sr = double(rv) * double(di_r[r]);
-          if (w) {
-            if (w != HELD_FIXED) ca = fmax(ca, w == HELD_UPPER ? -sr : sr);
-          } else {
-            cf = fmax(cf, fabs(sr));
-          }
-        }
-        continue;
-      }
-      wn[g] = qi;
-      if (CHEB) {
-        // the A z pass: z = y_cheb, w = A z; the stopping partials came from the main pass
-        const T zv = sv[i];
-        const T rv = rz[g];   // a later pass of the round: r is read back
-        a.zb[g] = zv;
-        gam += double(rv) * double(zv);
-        del += double(zv) * double(qi);
-        continue;
-      }
-      const T zv = sv[i];
-      const T rv = rz_r[r];   // non-Chebyshev first / iterate passes are main passes
-      gam += double(rv) * double(zv);
-      del += double(zv) * double(qi);
-      const double sr = double(rv) * double(di_r[r]);
-      const uint8_t w = wf_r[r];
-      if (w) {
-        if (w != HELD_FIXED) ca = fmax(ca, w == HELD_UPPER ? -sr : sr);
-      } else {
-        cf = fmax(cf, fabs(sr));
+    for (int k = 0; k < RPT; ++k) {
+      rsv[k] = rsc[pos[k]];
+      if (iter) {
+        const int po = node0 + min(tid + k * kBlock, n_own - 1);
+        wzv[k] = wzc[pos[k]];
+        pv_[k] = a.p[po];
+        xv_[k] = xc[po];
+        lbv_[k] = projected ? a.lbr[po] : T(0);
       }
     }
+    if constexpr (kEarlyRows) load_rows();
+#pragma unroll
+    for (int k = 0; k < RPT; ++k) {
+      const int i = tid + k * kBlock;
+      const bool held = dmv[k] < T(0);
+      T rn = rsv[k].x;
+      if (iter) {
+        const T sn = (beta == 0.0) ? wzv[k].x : wzv[k].x + be * rsv[k].y;   // s = A p of this iteration
+        rn = rn - al * sn;
+        if (i < n_own) {
+          const int g = node0 + i;
+          const T pv = (beta == 0.0) ? wzv[k].y : wzv[k].y + be * pv_[k];
+          const double xv = xv_[k], lbd = double(lbv_[k]);
+          double xn = xv + double(al) * double(pv);
+          if (monotone && !held) {
+            // largest step that keeps this node inside [d_prev, 1]
+            if (pv < T(0)) amin = fmin(amin, (lbd - xv) / double(pv));
+            if (pv > T(0)) amin = fmin(amin, (1.0 - xv) / double(pv));
+            xn = clamp01<double>(xn, lbd);
+          } else if (projected && !held) {
+            if (lbd - xn > tol || xn - 1.0 > tol) nc.ch += 1.0;   // free node outside the bounds
+          }
+          a.p[g] = pv;
+          xn_[g] = xn;
+          rsn[g] = Two<T>{rn, sn};
+        }
+      }
+      if (held && monotone && i < n_own) {
+        const double sr = double(rn) * double(-dmv[k]);
+        const uint8_t w = (c->wbuf ? a.W1 : a.W0)[node0 + i];
+        if (w != HELD_FIXED) nc.ca = fmax(nc.ca, w == HELD_UPPER ? -sr : sr);
+      }
+      // on held nodes z and every Chebyshev iterate are 0
+      if (held) dmv[k] = T(0), rn = T(0);
+      r_[k] = rn;
+      y_[k] = d_[k] = dmv[k] * rn * ith;
+      if (i < nall) ya[i] = y_[k];
+    }
+    for (int i = RPT * kBlock + tid; i < nall; i += kBlock) {   // nodes of the outermost ring without a row here
+      const int q = a.dr.halo[halo0 + i - n_own];
+      const Two<T> rs = rsc[q];
+      const T dm = a.dim[q];
+      T rn = rs.x;
+      if (iter) {
+        const Two<T> wz = wzc[q];
+        const T sn = (beta == 0.0) ? wz.x : wz.x + be * rs.y;
+        rn = rn - al * sn;
+      }
+      ya[i] = dm < T(0) ? T(0) : dm * rn * ith;
+    }
+    if constexpr (!kEarlyRows) load_rows();
+    __syncthreads();
+    const T* ys = ya;
+    for (int j = 1; j < deg; ++j) {
+      const int lim = nl(deg - j);
+      T* const yd = (j & 1) ? yb : ya;
+      const T c1 = T(c->ch1[j - 1]), c2 = T(c->ch2[j - 1]);
+#pragma unroll
+      for (int k = 0; k < RPT; ++k) {
+        const int i = tid + k * kBlock;
+        if (i >= lim) continue;
+        const T s = row_sum(k, ys, T(0), [](T e, T y) { return e * y; });
+        // D^-1 (r - A y): the diagonal's part of D^-1 A y is y itself
+        d_[k] = c1 * d_[k] + c2 * (dmv[k] * (r_[k] - s) - y_[k]);
+        y_[k] += d_[k];
+        yd[i] = y_[k];
+      }
+      __syncthreads();
+      ys = yd;
+    }
+    // w = A z on the owned nodes
+#pragma unroll
+    for (int k = 0; k < RPT; ++k) {
+      const int i = tid + k * kBlock;
+      if (i >= n_own) continue;
+      const T zv = y_[k];
+      const T s = rsu[k] * zv + row_sum(k, ys, T(0), [&](T e, T y) { return e * (y - zv); });
+      wzn[node0 + i] = Two<T>{s, zv};
+      gam += double(r_[k]) * double(zv);
+      del += double(zv) * double(s);
+      // a CG run ends when max |r_i|/A_ii and max |z_i| are at most tol: the
+      // polynomial leaves smooth residuals, whose error is up to
+      // 1/lambda_min(D^-1 A) (about 15) times |r|/A_ii, and z = M r has nearly
+      // the error's size (with Jacobi the two are the same)
+      nc.cf = fmax(nc.cf, fmax(fabs(double(r_[k]) * double(dmv[k])), fabs(double(zv))));
+    }
   }
-  // with the Chebyshev preconditioner the main pass of a first / iterate
-  // round stores every partial but gamma and delta, the A z pass only those
-  // two, and the Chebyshev steps none
-  uint32_t store = 0xffu;
-  if (CHEB && !xpass) {
-    if (stage > 0 && stage < a.cheb - 1) return;
-    const uint32_t gd = (1u << PT_GAMMA) | (1u << PT_DELTA);
-    store = (stage == 0) ? (0xffu & ~gd) : gd;
-  }
-  double v[8] = {del, amin, gam, cf, ca, na, rb, ch};   // in PT_* order
-  const double tot = block_reduce_rows<8, kPartOps>(v, red);
-  // partials are stored value-major, [8][n_tiles], so the reduction reads them
-  // coalesced; thread k holds value k.  FUSE (Jacobi rounds): stored through
-  // to the device-coherent level for the combination in this kernel's last
-  // workgroup.
-  if constexpr (FUSE) {
-    if (tid < 8)
-      __hip_atomic_store(&a.part[size_t(tid) * a.dm.n_tiles + tile], tot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    arrive_and_advance(a, a.ctl + t.inst, tile, P.bounds, red);
-  } else {
-    if (tid < 8 && (store & (1u << tid))) a.part[size_t(tid) * a.dm.n_tiles + tile] = tot;
-  }
+  double v[8] = {del, amin, gam, nc.cf, nc.ca, nc.na, 0.0, nc.ch};   // in PT_* order
+  finish_pass<T, FUSE>(a, c, v, tile, c->rt0, c->nrt, a.dr.n_tiles, bnd, red);
 }
 
 // Combination of an instance's per-tile partials, in a fixed order: thread t
@@ -760,7 +794,6 @@ __device__ __forceinline__ void advance_solver(Ctl* c, const double (&v)[8], int
   c->iters += 1;
   c->inner = (mode == MODE_ITER) ? c->inner + 1 : 0;
   if (setup && !qp) c->ref = srb;   // linear solves stop relative to max |b_i|/A_ii
-  if (setup) c->lmax = (samin < 0.0) ? -samin : 0.0;   // Gershgorin bound of D^-1 A (Chebyshev only)
   const double tl = tol * c->ref;
   const double rs = c->ref > 0.0 ? c->ref : 1.0;
   if (mode == MODE_RESTART || mode == MODE_CHECK) {
@@ -859,8 +892,7 @@ __device__ __forceinline__ void advance_solver(Ctl* c, const double (&v)[8], int
 }
 
 // One workgroup per instance: combine the tiles' partials and advance the
-// state (the rounds of the Chebyshev-preconditioned solver, and passes run
-// without the combination in their last workgroup).
+// state (passes run without the combination in their last workgroup).
 constexpr int kRedBlock = kBlock;
 __global__ __launch_bounds__(kRedBlock) void k_dmg_red(Ctl* ctl, const double* part, int n_tiles, const int* bounds,
                                                        int kind, double tol, int max_iter) {
@@ -874,11 +906,12 @@ __global__ __launch_bounds__(kRedBlock) void k_dmg_red(Ctl* ctl, const double* p
     bnd = bounds[blockIdx.x];
   }
   if (cp->mode == MODE_DONE) return;
-  const int tile_end = cp->tile0 + cp->ntiles;
+  const int tile0 = cp->rt0;
+  const int tile_end = tile0 + cp->nrt;
   double v[8] = {0.0, INFINITY, 0.0, 0.0, -INFINITY, 0.0, 0.0, 0.0};
   const size_t nt = size_t(n_tiles);
 #pragma unroll 1
-  for (int k0 = cp->tile0 + threadIdx.x; k0 < tile_end; k0 += kRedBatch * kRedBlock) {
+  for (int k0 = tile0 + threadIdx.x; k0 < tile_end; k0 += kRedBatch * kRedBlock) {
     double q[kRedBatch][8];
 #pragma unroll
     for (int j = 0; j < kRedBatch; ++j) {
@@ -909,7 +942,7 @@ __global__ __launch_bounds__(kRedBlock) void k_dmg_red(Ctl* ctl, const double* p
   *cp = cc;
 }
 
-// The end of a Jacobi round's pass: each workgroup counts its arrival once its
+// The end of a pass that combines in place: each workgroup counts its arrival once its
 // partial sums are stored, and the instance's last workgroup to arrive
 // combines every tile's partials and advances the solver, so a round is one
 // launch.  Nothing waits for anything: a workgroup that is not last exits.
@@ -918,30 +951,31 @@ __global__ __launch_bounds__(kRedBlock) void k_dmg_red(Ctl* ctl, const double* p
 // the stores have completed; the last workgroup reads them past its L2.  The
 // fixed combination order is that of k_dmg_red, so the bits are the same.
 template <typename T>
-__device__ __forceinline__ void arrive_and_advance(const DmgArgs<T>& a, Ctl* c, int tile, int bnd, double* red) {
+__device__ __forceinline__ void arrive_and_advance(const DmgArgs<T>& a, Ctl* c, int tile, int tile0, int ntiles,
+                                                   int n_tiles, int bnd, double* red) {
   __shared__ int s_last;
   __shared__ double s_tot[8];
   const int tid = threadIdx.x;
-  uint32_t* const top = a.arrive + size_t(c->cbase + c->ngroup) * kArriveStride;
+  uint32_t* const top = a.arrive + size_t(c->ctop) * kArriveStride;
   if (tid < 64) {
     // threads 0-7 of this wave stored the partials: wait for the stores
     __builtin_amdgcn_s_waitcnt(0);
     if (tid == 0) {
-      const int g = (tile - c->tile0) / kArriveGroup;
-      const unsigned gsize = unsigned(min(kArriveGroup, c->ntiles - g * kArriveGroup));
+      const int g = (tile - tile0) / kArriveGroup;
+      const unsigned gsize = unsigned(min(kArriveGroup, ntiles - g * kArriveGroup));
       uint32_t* const gc = a.arrive + size_t(c->cbase + g) * kArriveStride;
       bool last = false;
       if (__hip_atomic_fetch_add(gc, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gsize - 1) {
         __hip_atomic_store(gc, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         last = __hip_atomic_fetch_add(top, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
-               unsigned(c->ngroup) - 1;
+               unsigned((ntiles + kArriveGroup - 1) / kArriveGroup) - 1;
       }
       s_last = last;
     }
   }
   __syncthreads();
   if (!s_last) return;
-  const double vk = combine_partials(a.part, size_t(a.dm.n_tiles), c->tile0, c->ntiles, red);
+  const double vk = combine_partials(a.part, size_t(n_tiles), tile0, ntiles, red);
   if (tid < 8) s_tot[tid] = vk;
   __syncthreads();
   if (tid != 0) return;
@@ -962,22 +996,22 @@ __global__ __launch_bounds__(kBlock) void k_dmg_final(DmgArgs<T> a, uint8_t* act
   const Ctl* c = a.ctl + t.inst;
   const InstP<T> P = a.ip[t.inst];
   const bool projected = (P.bounds == PF_BOUNDS_PROJECTED);
-  const T* xc = c->pbuf ? a.x1 : a.x0;
+  const double* xc = c->pbuf ? a.x1 : a.x0;
   const uint8_t* Wc = c->wbuf ? a.W1 : a.W0;
   if (a.kind != CG_QP) {
-    // the result goes to the caller's array x0
     for (int i = threadIdx.x; i < t.n_own; i += kBlock) {
       const int g = t.node_begin + i;
-      a.x0[g] = (c->ref == 0.0) ? T(0) : xc[g];
+      a.dout[g] = (c->ref == 0.0) ? T(0) : T(xc[a.dr.pos[g]]);
     }
   } else {
     for (int i = threadIdx.x; i < t.n_own; i += kBlock) {
       const int g = t.node_begin + i;
-      T xv = xc[g];
+      const int q = a.dr.pos[g];
+      T xv = T(xc[q]);
       const T lbv = a.lb[g];
       uint8_t act = 0;
       if (projected) {
-        const uint8_t w = Wc[g];
+        const uint8_t w = Wc[q];
         act = (w == HELD_LOWER || w == HELD_FIXED) ? PF_ACTIVE_LOWER : ((w == HELD_UPPER) ? PF_ACTIVE_UPPER : 0);
         xv = clamp01<T>(xv, lbv);   // free nodes within tol outside the bounds
       } else {
@@ -1007,85 +1041,91 @@ __global__ __launch_bounds__(kBlock) void k_dmg_final(DmgArgs<T> a, uint8_t* act
 
 template <typename T>
 static DmgArgs<T> dmg_args(pf_mesh_s* m, int kind, const void* H, const void* d_prev, void* d,
-                           const uint8_t* guess, double tol, int max_iter, int start) {
+                           const uint8_t* guess, const pf_cg_opts_t* o) {
   DmgArgs<T> a;
   a.kind = kind;
-  a.start = (kind == CG_QP) ? start : 0;
-  a.mte = static_cast<T*>(m->dw.mte);
+  a.start = (kind == CG_QP) ? o->start : 0;
   a.dm = m->dm;
+  a.dr = m->dr;
   a.ip = static_cast<const InstP<T>*>(m->dw.instp);
   a.ctl = m->dw.ctl;
   a.part = m->dw.part;
   a.H = static_cast<const T*>(H);
   a.lb = static_cast<const T*>(d_prev);
   a.guess = guess;
-  // the damage solve iterates in workspaces and writes d at the end; linear
-  // solves start from, and end in, the caller's array
-  a.x0 = (kind == CG_QP) ? static_cast<T*>(m->dw.xw0) : static_cast<T*>(d);
-  a.x1 = static_cast<T*>(m->dw.xw1);
+  // linear solves start from, and end in, the caller's array
   a.dout = static_cast<T*>(d);
-  a.r0 = static_cast<T*>(m->dw.r0);
-  a.r1 = static_cast<T*>(m->dw.r1);
-  a.w0 = static_cast<T*>(m->dw.w0);
-  a.w1 = static_cast<T*>(m->dw.w1);
-  a.s0 = static_cast<T*>(m->dw.s0);
-  a.s1 = static_cast<T*>(m->dw.s1);
+  a.bin = static_cast<const T*>(m->dw.b);
+  a.win = m->dw.wset;
+  a.x0 = static_cast<double*>(m->dw.x0);
+  a.x1 = static_cast<double*>(m->dw.x1);
+  a.rs0 = static_cast<Two<T>*>(m->dw.rs0);
+  a.rs1 = static_cast<Two<T>*>(m->dw.rs1);
+  a.wz0 = static_cast<Two<T>*>(m->dw.wz0);
+  a.wz1 = static_cast<Two<T>*>(m->dw.wz1);
   a.p = static_cast<T*>(m->dw.p);
-  a.b = static_cast<T*>(m->dw.b);
-  a.dinv = static_cast<T*>(m->dw.dinv);
-  a.W0 = m->dw.wset;
-  a.W1 = m->dw.wset + m->n_nodes;
-  a.tol = tol;
-  a.max_iter = max_iter;
-  a.zb = a.y0 = a.y1 = a.dv = nullptr;
-  a.cheb = 0;
-  a.stage = 0;
-  a.fuse = 0;
+  a.dim = static_cast<T*>(m->dw.dim);
+  a.rsum = static_cast<T*>(m->dw.rsum);
+  a.b = static_cast<T*>(m->dw.br);
+  a.lbr = static_cast<T*>(m->dw.lbr);
+  a.W0 = m->dw.wr;
+  a.W1 = m->dw.wr + m->n_nodes;
+  a.tol = o->tol;
+  a.max_iter = o->max_iter;
+  a.deg = o->precond;
+  // Instances of up to kFuseMaxTiles tiles combine their partials in the pass's
+  // last workgroup (one launch per round: the last workgroup's combination
+  // takes one memory round trip per 256 tiles, which beats the separate
+  // reduction launch only while there are few)
+  a.fuse = m->max_inst_tiles <= kFuseMaxTiles ? 1 : 0;
   a.arrive = m->dw.arrive;
   a.nch = 1;
   return a;
 }
 
-// The damage pass for npt owned nodes per thread (a tile of up to 256 npt
-// owned nodes) with its elements in nch chunks.
-template <typename T, int NPT, bool CHEB, bool FUSE>
-static void (*dmg_kernel_c(int nch))(DmgArgs<T>) {
-  return nch == 2 ? k_dmg<T, NPT, CHEB, FUSE, 2> : k_dmg<T, NPT, CHEB, FUSE, 1>;
-}
-template <typename T, bool CHEB, bool FUSE>
-static void (*dmg_kernel(int npt, int nch))(DmgArgs<T>) {
-  return npt <= 1 ? dmg_kernel_c<T, 1, CHEB, FUSE>(nch)
-                  : (npt <= 2 ? dmg_kernel_c<T, 2, CHEB, FUSE>(nch)
-                              : (npt <= 4 ? dmg_kernel_c<T, 4, CHEB, FUSE>(nch) : dmg_kernel_c<T, 8, CHEB, FUSE>(nch)));
+// The CG pass for up to 256 rpt rows per row tile.
+template <typename T, bool FUSE>
+static void (*cg_kernel(int rows, bool setup))(DmgArgs<T>) {
+  const int rpt = (rows + kBlock - 1) / kBlock;
+  if (setup)
+    return rpt <= 1 ? k_cg_setup<T, 1, FUSE>
+                    : (rpt <= 2 ? k_cg_setup<T, 2, FUSE>
+                                : (rpt <= 3 ? k_cg_setup<T, 3, FUSE>
+                                            : (rpt <= 4 ? k_cg_setup<T, 4, FUSE> : k_cg_setup<T, 8, FUSE>)));
+  return rpt <= 1 ? k_cg<T, 1, FUSE>
+                  : (rpt <= 2 ? k_cg<T, 2, FUSE>
+                              : (rpt <= 3 ? k_cg<T, 3, FUSE> : (rpt <= 4 ? k_cg<T, 4, FUSE> : k_cg<T, 8, FUSE>)));
 }
 
-// Element chunks of the damage passes: two when halving the corner-value
-// space in LDS lets every tile's workgroup be resident at once where one
-// chunk cannot (the workgroups per CU from the kernel's registers and LDS).
-// A second wave that holds only the tiles the first could not place moves a
-// fraction of the pass's bytes but adds most of a pass's latency; with
-// several waves either way the second chunk's extra barrier and element
-// phase cost more than the shorter tail saves.
+// LDS of a pass: the vector being multiplied, twice for a polynomial; nch > 0:
+// of the set-up pass, the start and the elements' values.
+template <typename T>
+static size_t cg_lds(const pf_mesh_s* m, int deg, int nch) {
+  return size_t(nch > 0 ? m->max_slds[nch - 1][deg] : m->max_rlds[deg]) * sizeof(T);
+}
+
+template <typename T>
+static void launch_cg(const pf_mesh_s* m, DmgArgs<T> a, int nch, hipStream_t s) {
+  const int rows = m->max_rows[a.deg];
+  a.nch = nch;
+  hipLaunchKernelGGL((a.fuse ? cg_kernel<T, true>(rows, nch > 0) : cg_kernel<T, false>(rows, nch > 0)),
+                     dim3(m->dr.n_tiles), dim3(kBlock), cg_lds<T>(m, a.deg, nch), s, a);
+}
+
+// Element chunks of the set-up pass: two (the elements' mass coefficients and
+// their loads one after the other in LDS) when the halved space lets more
+// workgroups share a CU, or when only that fits a workgroup's LDS.
 template <typename T>
 static int damage_chunks(pf_mesh_s* m) {
   if (m->dmg_nch > 0) return m->dmg_nch;
   int nch = m->damage_chunks;
-  if (nch <= 0) {
-    const int npt = (m->max_own + kBlock - 1) / kBlock;
-    const void* k1 = reinterpret_cast<const void*>(dmg_kernel<T, false, false>(npt, 1));
-    const void* k2 = reinterpret_cast<const void*>(dmg_kernel<T, false, false>(npt, 2));
-    int dev = 0, ncu = 0;
-    (void)hipGetDevice(&dev);
-    if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) ncu = 0;
-    auto waves = [&](const void* k, size_t lds) -> long {
-      int occ = 0;
-      if (ncu <= 0 || hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k, kBlock, lds) != hipSuccess || occ <= 0)
-        return LONG_MAX;
-      const long slots = long(occ) * ncu;
-      return (long(m->n_tiles) + slots - 1) / slots;
-    };
-    nch = (waves(k2, size_t(m->max_lds_damage2)) == 1 && waves(k1, size_t(m->max_lds_damage)) > 1) ? 2 : 1;
-  }
+  auto occ = [&](int n) {
+    int o = 0;
+    const void* k = reinterpret_cast<const void*>(cg_kernel<T, false>(m->max_rows[0], true));
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&o, k, kBlock, cg_lds<T>(m, 0, n)) != hipSuccess) o = 0;
+    return o;
+  };
+  if (nch <= 0) nch = occ(2) > occ(1) ? 2 : 1;
   m->dmg_nch = nch;
   return nch;
 }
@@ -1097,58 +1137,36 @@ void damage_plan(pf_mesh_s* m) {
     (void)damage_chunks<float>(m);
 }
 
-static size_t damage_lds(const pf_mesh_s* m, int nch) {
-  return size_t(nch == 2 ? m->max_lds_damage2 : m->max_lds_damage);
-}
-
 template <typename T>
 static pf_status_t run_solve(pf_mesh_s* m, int kind, const void* H, const void* d_prev, void* d,
                              const uint8_t* guess, uint8_t* active_out, const pf_cg_opts_t* o,
                              pf_cg_stats_t* stats, hipStream_t s) {
-  DmgArgs<T> a = dmg_args<T>(m, kind, H, d_prev, d, guess, o->tol, o->max_iter, o->start);
+  DmgArgs<T> a = dmg_args<T>(m, kind, H, d_prev, d, guess, o);
   const dim3 grid(m->n_tiles), block(kBlock), igrid(m->n_inst);
-  a.nch = damage_chunks<T>(m);
-  const size_t lds = damage_lds(m, a.nch);
-  if (!o->resume) {
+  const int nch = damage_chunks<T>(m);
+  bool setup = !o->resume;   // the first round of a solve is its set-up restart
+  if (setup) {
     timer_begin(m, 2, s);
     hipLaunchKernelGGL(k_dmg_init, dim3((m->n_inst + 63) / 64), dim3(64), 0, s, m->dw.ctl, m->n_inst, kind,
                        o->monotone);
     timer_end(m, 2, s);
   }
-  const int npt = (m->max_own + kBlock - 1) / kBlock;
-  const bool cheb = o->precond >= 2;
-  a.cheb = cheb ? o->precond : 0;
-  // Jacobi rounds of instances of up to kFuseMaxTiles tiles combine their
-  // partials in the pass's last workgroup (one launch per round: the last
-  // workgroup's combination takes one memory round trip per 256 tiles, which
-  // beats the separate reduction launch only while there are few); larger
-  // instances and Chebyshev rounds keep the reduction launch
-  a.fuse = (!cheb && m->max_inst_tiles <= kFuseMaxTiles) ? 1 : 0;
-  a.zb = static_cast<T*>(m->dw.zb);
-  a.y0 = static_cast<T*>(m->dw.y0);
-  a.y1 = static_cast<T*>(m->dw.y1);
-  a.dv = static_cast<T*>(m->dw.dv);
-  auto kdmg = cheb ? dmg_kernel<T, true, false>(npt, a.nch)
-                   : (a.fuse ? dmg_kernel<T, false, true>(npt, a.nch) : dmg_kernel<T, false, false>(npt, a.nch));
   if (kind == CG_QP) {
     const unsigned char* ab = reinterpret_cast<const unsigned char*>(&a);
     m->last_qp_args.assign(ab, ab + sizeof(a));
-    m->last_qp_cheb = a.cheb;
+    m->last_qp_precond = o->precond;
   }
   auto round = [&]() {
-    // one pass, or with the Chebyshev preconditioner one pass per matrix-vector product
-    for (int st = 0; st < (cheb ? a.cheb : 1); ++st) {
-      DmgArgs<T> as = a;
-      as.stage = st;
-      timer_begin(m, 1, s);
-      hipLaunchKernelGGL(kdmg, grid, block, lds, s, as);
-      timer_end(m, 1, s);
+    timer_begin(m, 1, s);
+    launch_cg<T>(m, a, setup ? nch : 0, s);
+    timer_end(m, 1, s);
+    if (!a.fuse) {
+      timer_begin(m, 4, s);
+      hipLaunchKernelGGL(k_dmg_red, igrid, dim3(kRedBlock), 0, s, m->dw.ctl, m->dw.part,
+                         m->dr.n_tiles, m->dw.bounds, kind, o->tol, o->max_iter);
+      timer_end(m, 4, s);
     }
-    if (a.fuse) return;
-    timer_begin(m, 4, s);
-    hipLaunchKernelGGL(k_dmg_red, igrid, dim3(kRedBlock), 0, s, m->dw.ctl, m->dw.part, m->n_tiles, m->dw.bounds,
-                       kind, o->tol, o->max_iter);
-    timer_end(m, 4, s);
+    setup = false;
   };
   const int max_rounds = (o->check_every <= 0 && o->rounds > 0) ? std::min(o->rounds, o->max_iter) : o->max_iter;
   int launched = 0;
@@ -1207,7 +1225,8 @@ template <typename T>
 static pf_status_t repeat_pass(pf_mesh_s* m, const void* H, const void* d_prev, void* d, int n, hipStream_t s) {
   DmgArgs<T> a;
   if (m->last_qp_args.size() != sizeof(a)) return fail(PF_ERR_ARG, "no damage solve on this handle");
-  if (m->last_qp_cheb != 0) return fail(PF_ERR_ARG, "repeated passes need the Jacobi preconditioner");
+  if (m->last_qp_precond >= 2)
+    return fail(PF_ERR_ARG, "repeated passes need the default or the Jacobi preconditioner");
   std::memcpy(&a, m->last_qp_args.data(), sizeof(a));
   // the caller's arrays as given now; the workspaces are the handle's
   a.H = static_cast<const T*>(H);
@@ -1222,11 +1241,7 @@ static pf_status_t repeat_pass(pf_mesh_s* m, const void* H, const void* d_prev, 
   for (int k = 0; k < m->n_inst; ++k)
     if (m->ctl_pinned[k].mode != MODE_ITER)
       return fail(PF_ERR_ARG, "the last damage solve did not stop in a CG iteration");
-  const int npt = (m->max_own + kBlock - 1) / kBlock;
-  auto kdmg = a.fuse ? dmg_kernel<T, false, true>(npt, a.nch) : dmg_kernel<T, false, false>(npt, a.nch);
-  a.stage = 0;
-  for (int i = 0; i < n; ++i)
-    hipLaunchKernelGGL(kdmg, dim3(m->n_tiles), dim3(kBlock), damage_lds(m, a.nch), s, a);
+  for (int i = 0; i < n; ++i) launch_cg<T>(m, a, 0, s);
   PF_HIP(hipGetLastError());
   return PF_OK;
 }

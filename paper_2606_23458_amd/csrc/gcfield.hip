@@ -38,7 +38,12 @@ extern "C" pf_status_t pf_set_gc_field(pf_mesh_t m, const void* phi, double* dgc
   if (!m) return fail(PF_ERR_ARG, "NULL mesh");
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (!phi) {
-    m->dm.gcs = nullptr;
+    if (m->dm.gcs) {
+      m->dm.gcs = nullptr;
+      rows_stiffness(m, s);   // the damage rows without the field
+      PF_HIP(hipGetLastError());
+      PF_HIP(hipStreamSynchronize(s));
+    }
     m->dgc_field = dgc_field;
     return PF_OK;
   }
@@ -63,9 +68,11 @@ extern "C" pf_status_t pf_set_gc_field(pf_mesh_t m, const void* phi, double* dgc
     hipLaunchKernelGGL(k_gcs_gather<float>, grid, block, 0, s, m->dm.te_gid, static_cast<const float*>(phi),
                        static_cast<float*>(m->gcs_buf), m->n_te);
   PF_HIP(hipGetLastError());
+  m->dm.gcs = m->gcs_buf;
+  rows_stiffness(m, s);   // the damage rows with the field
+  PF_HIP(hipGetLastError());
   // the caller may release phi on return
   PF_HIP(hipStreamSynchronize(s));
-  m->dm.gcs = m->gcs_buf;
   m->dgc_field = dgc_field;
   return PF_OK;
 }

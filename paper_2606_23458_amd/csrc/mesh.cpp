@@ -33,6 +33,8 @@ struct Geo {
   double area;
 };
 
+}  // namespace
+
 // Recursive coordinate bisection: split [lo, hi) of ids along the longer
 // side of its bounding box until a part holds at most maxn nodes.  The split
 // point is proportional to the number of leaves on each side so that leaves
@@ -60,6 +62,8 @@ void rcb(std::vector<int32_t>& ids, size_t lo, size_t hi, const double* xy, size
   rcb(ids, lo, mid, xy, maxn, leaves);
   rcb(ids, mid, hi, xy, maxn, leaves);
 }
+
+namespace {
 
 template <typename T>
 void to_dtype(const std::vector<double>& src, std::vector<unsigned char>& dst) {
@@ -300,6 +304,14 @@ extern "C" pf_status_t pf_mesh_create(const pf_mesh_desc_t* inst, int32_t n_inst
   std::vector<double> inv_w(n_tot), wl(n_tot);
   std::vector<uint8_t> fixed(n_tot, 0);
   lcorner.reserve(size_t(e_tot) * 3);
+  int dev = 0, lds_limit = 0;
+  (void)hipGetDevice(&dev);
+  if (hipDeviceGetAttribute(&lds_limit, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess || lds_limit <= 0)
+    lds_limit = 65536;
+  RowPlan rows;
+  rows.pos.resize(size_t(n_tot));
+  rows.node.resize(size_t(n_tot));
+  std::vector<double> lmax(n_instances, 2.0);
 
   int32_t node_off = 0, elem_off = 0;
   for (int k = 0; k < n_instances; ++k) {
@@ -485,6 +497,42 @@ extern "C" pf_status_t pf_mesh_create(const pf_mesh_desc_t* inst, int32_t n_inst
       m->tiles_h.push_back(rec);
       node_cursor += rec.n_own;
     }
+    // rows of the damage operator, and a bound of the spectrum of D^-1 A: A is a
+    // stiffness and a mass part with nonnegative element weights, so the bound
+    // is the larger of theirs: 2 for the mass part, and for the stiffness part
+    // that of its worst element (any weights, so also with a toughness field)
+    {
+      std::vector<int32_t> te_of(ne);
+      for (int32_t t = tile0; t < tile0 + nt; ++t) {
+        const TileRec& rec = m->tiles_h[t];
+        for (int32_t j = 0; j < rec.n_own_elem; ++j)
+          te_of[rec.own_elem_begin - elem_off + j] = rec.telem_begin + rec.own_elem_lo + j;
+      }
+      double le = 2.0;
+      for (int32_t e = 0; e < ne; ++e) {
+        const Geo& g = geo[e];
+        const double k01 = g.area * (g.g[0] * g.g[2] + g.g[1] * g.g[3]);
+        const double k02 = g.area * (g.g[0] * g.g[4] + g.g[1] * g.g[5]);
+        const double k12 = g.area * (g.g[2] * g.g[4] + g.g[3] * g.g[5]);
+        const double k00 = -(k01 + k02), k11 = -(k01 + k12), k22 = -(k02 + k12);
+        // eigenvalues of D_e^-1 K_e: 0 and two with sum 3 and product e2
+        const double e2 = 3.0 - k01 * k01 / (k00 * k11) - k02 * k02 / (k00 * k22) - k12 * k12 / (k11 * k22);
+        le = std::max(le, 0.5 * (3.0 + std::sqrt(std::max(0.0, 9.0 - 4.0 * e2))));
+      }
+      lmax[k] = std::min(le, 3.0);
+      RowMesh rm{node_off, elem_off, n, ne, d.xy, tri.data(), node_int.data(), eorder.data(), te_of.data(), &leaves, size_t(tile_nodes)};
+      bool fits = false;
+      try {
+        fits = row_plan_add(rows, rm, k, elem_size(dtype), size_t(lds_limit));
+      } catch (const std::bad_alloc&) {
+        delete m;
+        return fail(PF_ERR_NOMEM, "host allocation failed");
+      }
+      if (!fits) {
+        delete m;
+        return fail(PF_ERR_UNSUPPORTED, "a tile's neighbourhood needs more LDS than the device allows; lower tile_nodes");
+      }
+    }
     pf_instance_info_t& info = m->info[k];
     info.node_offset = node_off;
     info.n_nodes = n;
@@ -596,7 +644,43 @@ extern "C" pf_status_t pf_mesh_create(const pf_mesh_desc_t* inst, int32_t n_inst
   if (dtype == PF_F64) to_dtype<double>(wl, tmp); else to_dtype<float>(wl, tmp);
   UP(tmp, p_wl);
   UP(fixed, p_fixed);
+  void *p_rnode, *p_ete, *p_egid;
+  void *p_rt, *p_rhalo, *p_rpos, *p_ac, *p_code, *p_xs, *p_xac, *p_xcode;
+  UP(rows.tiles, p_rt);
+  UP(rows.halo, p_rhalo);
+  UP(rows.pos, p_rpos);
+  UP(rows.node, p_rnode);
+  UP(rows.ete, p_ete);
+  UP(rows.egid, p_egid);
+  UP(rows.ac, p_ac);
+  UP(rows.code, p_code);
+  UP(rows.xs, p_xs);
+  UP(rows.xac, p_xac);
+  UP(rows.xcode, p_xcode);
 #undef UP
+  m->dr.tiles = static_cast<const RowTile*>(p_rt);
+  m->dr.halo = static_cast<const int32_t*>(p_rhalo);
+  m->dr.pos = static_cast<const int32_t*>(p_rpos);
+  m->dr.node = static_cast<const int32_t*>(p_rnode);
+  m->dr.ete = static_cast<const uint32_t*>(p_ete);
+  m->dr.egid = static_cast<const int32_t*>(p_egid);
+  m->dr.ac = static_cast<const uint32_t*>(p_ac);
+  m->dr.code = static_cast<const uint2*>(p_code);
+  m->dr.xs = static_cast<const int2*>(p_xs);
+  m->dr.xac = static_cast<const uint32_t*>(p_xac);
+  m->dr.xcode = static_cast<const uint2*>(p_xcode);
+  m->dr.n_tiles = int32_t(rows.tiles.size());
+  // rows and LDS values of the largest row tile by degree (an instance whose
+  // tiles hold fewer rings runs with its own largest degree)
+  for (const RowTile& t : rows.tiles)
+    for (int dg = 0; dg <= kMaxRing; ++dg) {
+      const int de = dg == 0 ? rows.ddef[t.inst] : std::min(dg, rows.dmax[t.inst]);
+      m->max_rows[dg] = std::max(m->max_rows[dg], t.nl[de - 1]);
+      // the vector of a pass, twice for a polynomial, or the FP64 iterate of a restart
+      m->max_rlds[dg] = std::max({m->max_rlds[dg], (de > 1 ? 2 : 1) * t.nl[de], dtype == PF_F32 ? 2 * t.nl[1] : t.nl[1]});
+      m->max_slds[0][dg] = std::max(m->max_slds[0][dg], t.nl[1] + 2 * t.nel[de - 1]);
+      m->max_slds[1][dg] = std::max(m->max_slds[1][dg], t.nl[1] + t.nel[de - 1]);
+    }
   m->dm.tiles = static_cast<const TileRec*>(p_tiles);
   m->dm.halo_idx = static_cast<const int32_t*>(p_halo);
   m->dm.lc0 = static_cast<const uint16_t*>(p_lc0);
@@ -617,17 +701,27 @@ extern "C" pf_status_t pf_mesh_create(const pf_mesh_desc_t* inst, int32_t n_inst
 
   // workspaces
   const size_t nb = size_t(m->n_nodes) * w;
-  void** vecs[] = {&m->dw.b,  &m->dw.dinv, &m->dw.r0, &m->dw.r1,  &m->dw.w0,  &m->dw.w1,
-                   &m->dw.s0, &m->dw.s1,   &m->dw.p,  &m->dw.xw0, &m->dw.xw1, &m->dw.lam,
-                   &m->dw.lam_prev, &m->dw.zb, &m->dw.y0, &m->dw.y1, &m->dw.dv};
+  void** vecs[] = {&m->dw.b, &m->dw.p, &m->dw.dim, &m->dw.rsum, &m->dw.br, &m->dw.lbr, &m->dw.lam, &m->dw.lam_prev};
+  for (void** v : {&m->dw.x0, &m->dw.x1})
+    if ((st = dev_alloc(m, size_t(m->n_nodes) * sizeof(double), v)) != PF_OK) { free_all(m); delete m; return st; }
   for (void** v : vecs)
     if ((st = dev_alloc(m, nb, v)) != PF_OK) { free_all(m); delete m; return st; }
+  void** vecs2[] = {&m->dw.rs0, &m->dw.rs1, &m->dw.wz0, &m->dw.wz1};
+  for (void** v : vecs2)
+    if ((st = dev_alloc(m, 2 * nb, v)) != PF_OK) { free_all(m); delete m; return st; }
+  if ((st = dev_alloc(m, rows.ac.size() * 2 * w, &m->dr.sv)) != PF_OK) { free_all(m); delete m; return st; }
+  if ((st = dev_alloc(m, rows.xac.size() * 2 * w, &m->dr.xsv)) != PF_OK) { free_all(m); delete m; return st; }
+  if ((st = dev_alloc(m, rows.ac.size() * 2 * w, &m->dr.av)) != PF_OK) { free_all(m); delete m; return st; }
+  if ((st = dev_alloc(m, rows.xac.size() * 2 * w, &m->dr.xav)) != PF_OK) { free_all(m); delete m; return st; }
+  if ((st = dev_alloc(m, rows.tiles.size() * sizeof(int32_t), (void**)&m->dr.idle)) != PF_OK) { free_all(m); delete m; return st; }
   void* tmpp;
   if ((st = dev_alloc(m, size_t(m->n_elems) * w, &m->dw.hbar)) != PF_OK) { free_all(m); delete m; return st; }
-  if ((st = dev_alloc(m, size_t(m->n_te) * w, &m->dw.mte)) != PF_OK) { free_all(m); delete m; return st; }
-  if ((st = dev_alloc(m, 2 * size_t(m->n_nodes), &tmpp)) != PF_OK) { free_all(m); delete m; return st; }
+  if ((st = dev_alloc(m, size_t(m->n_nodes), &tmpp)) != PF_OK) { free_all(m); delete m; return st; }
   m->dw.wset = static_cast<uint8_t*>(tmpp);
-  if ((st = dev_alloc(m, size_t(m->n_tiles) * 8 * sizeof(double), &tmpp)) != PF_OK) { free_all(m); delete m; return st; }
+  if ((st = dev_alloc(m, 2 * size_t(m->n_nodes), &tmpp)) != PF_OK) { free_all(m); delete m; return st; }
+  m->dw.wr = static_cast<uint8_t*>(tmpp);
+  const size_t npart = size_t(std::max(m->n_tiles, m->dr.n_tiles));
+  if ((st = dev_alloc(m, npart * 8 * sizeof(double), &tmpp)) != PF_OK) { free_all(m); delete m; return st; }
   m->dw.part = static_cast<double*>(tmpp);
   if ((st = dev_alloc(m, size_t(n_instances) * sizeof(Ctl), &tmpp)) != PF_OK) { free_all(m); delete m; return st; }
   m->dw.ctl = static_cast<Ctl*>(tmpp);
@@ -654,10 +748,15 @@ extern "C" pf_status_t pf_mesh_create(const pf_mesh_desc_t* inst, int32_t n_inst
       c[k].tile0 = m->info[k].tile_offset;
       c[k].nnodes = m->info[k].n_nodes;
       c[k].mode = MODE_DONE;
-      c[k].ngroup = (c[k].ntiles + kArriveGroup - 1) / kArriveGroup;
+      c[k].nrt = rows.nrt[k];
+      c[k].rt0 = rows.rt0[k];
+      c[k].dmax = rows.dmax[k];
+      c[k].ddef = rows.ddef[k];
+      c[k].lmax = lmax[k];
       m->max_inst_tiles = std::max(m->max_inst_tiles, c[k].ntiles);
       c[k].cbase = ncnt;
-      ncnt += c[k].ngroup + 1;
+      c[k].ctop = ncnt + (c[k].nrt + kArriveGroup - 1) / kArriveGroup;
+      ncnt = c[k].ctop + 1;
     }
     const size_t cbytes = size_t(ncnt) * kArriveStride * sizeof(uint32_t);
     if ((st = dev_alloc(m, cbytes, &tmpp)) != PF_OK) { free_all(m); delete m; return st; }
@@ -667,24 +766,16 @@ extern "C" pf_status_t pf_mesh_create(const pf_mesh_desc_t* inst, int32_t n_inst
     hipError_t e = hipMemcpy(m->dw.ctl, c.data(), sizeof(Ctl) * n_instances, hipMemcpyHostToDevice);
     if (e != hipSuccess) { free_all(m); delete m; return hip_fail(e, "hipMemcpy"); }
   }
-  // LDS needs: explicit = 3 node values + 6 corner values; damage = 1 node
-  // value + 3 corner values of width w (its FP64 and set-up passes chunk)
+  // LDS needs of the explicit step: 3 node values + 6 corner values
   int32_t max_loc = 0, max_te = 0;
   for (const TileRec& t : m->tiles_h) {
     max_loc = std::max(max_loc, t.n_own + t.n_halo);
     max_te = std::max(max_te, t.n_telem);
   }
-  // plus, in both, the owned nodes' corner lists (16-bit offsets and ids)
+  // plus the owned nodes' corner lists (16-bit offsets and ids)
   const size_t lists = 2 * (size_t(m->max_own) + 1 + size_t(m->max_corner));
   m->max_lds_explicit = int32_t((3 * size_t(max_loc) + 6 * size_t(max_te)) * w + lists + 64);
   m->max_lds_explicit2 = int32_t((3 * size_t(max_loc) + 6 * ((size_t(max_te) + 1) / 2)) * w + lists + 64);
-  m->max_lds_damage = int32_t(((size_t(max_loc) * w + lists + 7) & ~size_t(7)) + size_t(max_te) * 3 * w + 64);
-  m->max_lds_damage2 =
-      int32_t(((size_t(max_loc) * w + lists + 7) & ~size_t(7)) + ((size_t(max_te) + 1) / 2) * 3 * w + 64);
-  int dev = 0, lds_limit = 0;
-  (void)hipGetDevice(&dev);
-  if (hipDeviceGetAttribute(&lds_limit, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess || lds_limit <= 0)
-    lds_limit = 65536;
   {
     int v = 0;
     if (hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, dev) == hipSuccess && v > 0)
@@ -692,8 +783,8 @@ extern "C" pf_status_t pf_mesh_create(const pf_mesh_desc_t* inst, int32_t n_inst
     if (hipDeviceGetAttribute(&v, hipDeviceAttributeMaxThreadsPerMultiProcessor, dev) == hipSuccess && v > 0)
       m->threads_per_cu = v;
   }
-  if (std::max(m->max_lds_explicit, m->max_lds_damage) > lds_limit) {
-    std::string s = "tiles need " + std::to_string(std::max(m->max_lds_explicit, m->max_lds_damage)) +
+  if (m->max_lds_explicit > lds_limit) {
+    std::string s = "tiles need " + std::to_string(m->max_lds_explicit) +
                     " bytes of LDS, device allows " + std::to_string(lds_limit) + "; lower tile_nodes";
     free_all(m);
     delete m;
@@ -701,6 +792,8 @@ extern "C" pf_status_t pf_mesh_create(const pf_mesh_desc_t* inst, int32_t n_inst
   }
   m->device = dev;
   damage_plan(m);
+  rows_stiffness(m, static_cast<hipStream_t>(stream));
+  if (const hipError_t el = hipGetLastError(); el != hipSuccess) { free_all(m); delete m; return hip_fail(el, "k_rows_stiffness launch"); }
   // device address of the static partials of pf_energies_static on this device
   if ((st = energy_scratch_setup(dev)) != PF_OK) { free_all(m); delete m; return st; }
   hipError_t e = hipStreamSynchronize(static_cast<hipStream_t>(stream));

@@ -36,6 +36,24 @@ struct TileRec {
   int32_t own_elem_lo;     // local index of the first owned element
 };
 
+// One workgroup of the damage CG passes: a run of owned nodes in row order (see
+// RowPlan) and the rings of nodes around them.  Local node ids run over the
+// owned nodes, then ring 1 (their neighbours), ring 2, ...; nl[k] counts the
+// nodes up to ring k.
+constexpr int kMaxRing = 4;          // rings a tile may keep (the largest polynomial degree)
+constexpr int kRowMax = 2048;        // rows (owned and ring nodes) that one workgroup can take
+constexpr int kRowPairs = 3;         // base entry pairs per row (6 neighbours); longer rows use extra pairs
+struct RowTile {
+  int32_t node0;                     // row-order position of the first owned node
+  int32_t nl[kMaxRing + 1];          // cumulative local node counts
+  int32_t halo0;                     // offset into halo (row-order positions of the ring nodes)
+  int32_t slice0;                    // first 64-row slice
+  int32_t nslice;
+  int32_t inst;
+  int32_t el0;                       // offset into the element lists
+  int32_t nel[kMaxRing];             // elements at a node up to ring k (those of each further ring at the end)
+};
+
 // Per-instance constants for the kernels, in the arithmetic type T.
 template <typename T>
 struct InstP {
@@ -84,11 +102,16 @@ struct Ctl {
   int32_t inner;      // CG iterations since the last restart or check
   int32_t wbuf;       // which half of the held-set pair is current
   int32_t outer;      // active-set updates so far
-  int32_t cbase;      // first arrival counter of this instance (counters of 32-tile groups, then the top one)
-  int32_t ngroup;     // 32-tile groups of this instance
+  int32_t cbase;      // first arrival counter of this instance (the counters of 32-tile groups)
+  int32_t ctop;       // arrival counter of the groups
+  int32_t nrt;        // row tiles of this instance
+  int32_t rt0;        // first row tile of this instance
+  int32_t dmax;       // largest polynomial degree its row tiles hold rings for
+  int32_t ddef;       // polynomial degree of the default preconditioner
   double rz, alpha, beta, amax, resid, pq;
   double ref;         // scale of the stopping test (1 for the damage QP, max |b_i|/A_ii for linear solves)
-  double lmax;        // upper bound of the spectrum of D^-1 A (set-up pass; Chebyshev preconditioner)
+  double lmax;        // upper bound of the spectrum of D^-1 A (pf_mesh_create)
+  double ith, ch1[kMaxRing - 1], ch2[kMaxRing - 1];   // steps of the Chebyshev iteration (1/theta; d_j = ch1 d_{j-1} + ch2 D^-1 res)
 };
 
 enum { MODE_RESTART = 0, MODE_ITER = 1, MODE_DONE = 2, MODE_CHECK = 3, MODE_FIRST = 4 };
@@ -119,23 +142,56 @@ struct DevMesh {
   int32_t n_nodes, n_elems, n_tiles, n_te;
 };
 
-// Device workspaces of the damage solve and of the adjoint.
+// Device view of the rows of the damage operator.  The nodes are numbered
+// once more for the damage solve ("row order", pos): row tiles own contiguous
+// runs of positions, chosen for the CG passes alone, so neither the caller's
+// tile size nor its node order bounds them.  Rows (the owned nodes of a tile,
+// then its rings but the outermost) stand in slices of 64, one row per lane:
+// kRowPairs pairs of entries and, where a slice has a longer row, extra pairs
+// (xs: first pair and number of pairs of each slice).  An entry holds up to
+// two element contributions: the element that this entry stands for at the
+// row's node (every element at the node has one such entry, and a row's
+// entries are in ascending order of them) and the other element at the pair,
+// each as 3 e + edge (edges 01, 02, 12 of the tile's element e) or kNoCode.
+constexpr uint32_t kNoCode = 0xffffu;
+struct DevRows {
+  const RowTile* tiles;
+  const int32_t* halo;          // [sum] row-order positions of the ring nodes
+  const int32_t* pos;           // [N] row-order position of each internal node
+  const int32_t* node;          // [N] internal node of each row-order position
+  const uint32_t* ete;          // [sum] tile element (owner's copy) of the tiles' elements
+  const int32_t* egid;          // [sum] internal element id
+  const uint32_t* ac;           // [slice][kRowPairs][64] local node ids of a pair's two columns (16 bits each)
+  const uint2* code;            // [slice][kRowPairs][64] contributions of a pair's two entries (16 bits each)
+  const int2* xs;               // [slice] first extra pair, number of extra pairs
+  const uint32_t* xac;          // [xpair][64]
+  const uint2* xcode;           // [xpair][64]
+  void* sv;                     // [slice][kRowPairs][64][2] stiffness part of the entries (mesh dtype)
+  void* xsv;                    // [xpair][64][2]
+  void* av;                     // [slice][kRowPairs][64][2] entries of the running solve (mesh dtype)
+  void* xav;                    // [xpair][64][2]
+  int32_t* idle;                // [tile] 1 where the tile owns no free node of the running CG run
+  int32_t n_tiles;
+};
+
+// Device workspaces of the damage solve and of the adjoint.  Vectors of the
+// CG are in row order.
 struct DevWork {
-  void* b; void* dinv;               // [n_nodes] CG load vector and Jacobi diagonal inverse
-  void* r0; void* r1;                // [n_nodes] residual pair
-  void* w0; void* w1;                // [n_nodes] A z pair
-  void* s0; void* s1;                // [n_nodes] A p pair
+  void* b;                           // [n_nodes] adjoint right-hand side (internal order)
+  uint8_t* wset;                     // [n_nodes] held set of the adjoint (internal order)
+  void* rs0; void* rs1;              // [n_nodes][2] pair of (residual r, s = A p)
+  void* wz0; void* wz1;              // [n_nodes][2] pair of (w = A z, z = M r)
   void* p;                           // [n_nodes] search direction
-  void* xw0; void* xw1;              // [n_nodes] iterate pair of the damage solve
-  void* zb;                          // [n_nodes] z = M r of the current iteration (polynomial preconditioner)
-  void* y0; void* y1;                // [n_nodes] Chebyshev iterate pair (polynomial preconditioner)
-  void* dv;                          // [n_nodes] Chebyshev update direction (polynomial preconditioner)
-  uint8_t* wset;                     // [2][n_nodes] held-set pair
+  void* x0; void* x1;                // [n_nodes] iterate pair (FP64)
+  void* dim;                         // [n_nodes] Jacobi diagonal inverse, negative on held nodes
+  void* rsum;                        // [n_nodes] row sums of A
+  void* br;                          // [n_nodes] load vector
+  void* lbr;                         // [n_nodes] lower bound
+  uint8_t* wr;                       // [2][n_nodes] held-set pair
   void* lam;                         // [n_nodes] adjoint multiplier (warm start of the next adjoint solve)
   void* lam_prev;                    // [n_nodes] the multiplier of the call before (linear extrapolation)
   void* hbar;                        // [n_elems] adjoint of H_{n+1} (adjoint step scratch)
-  void* mte;                         // [n_te] per-solve mass coefficient (c0 + cH H_e) A_e / 12 of each tile element
-  double* part;                      // [n_tiles][8] block partials
+  double* part;                      // [8][tiles] block partials (of the tiles or of the row tiles)
   uint32_t* arrive;                  // arrival counters of the damage passes, kArriveStride apart:
                                      // per instance one per 32-tile group, then one for the groups
   Ctl* ctl;                          // [n_inst]
@@ -155,7 +211,7 @@ struct Timer {
 struct pf_mesh_s {
   pf_dtype_t dtype;
   int32_t n_inst = 0, n_nodes = 0, n_elems = 0, n_tiles = 0, n_te = 0;
-  int32_t max_tile_nodes = 0, max_tile_elems = 0, max_own = 0, max_lds_explicit = 0, max_lds_damage = 0;
+  int32_t max_tile_nodes = 0, max_tile_elems = 0, max_own = 0, max_lds_explicit = 0;
   int32_t max_corner = 0;
   int32_t max_inst_tiles = 0;        // tiles of the largest instance
   size_t adj_lds_damage = 0;         // LDS of the adjoint kernels (set by the first backward step)
@@ -165,9 +221,8 @@ struct pf_mesh_s {
   int32_t explicit_block = 256;      // workgroup size of the explicit-step kernel (256 or 512)
   int32_t max_lds_explicit2 = 0;     // LDS of the explicit step with its elements in two chunks
   int32_t explicit_chunks = 0;       // 1, 2, or 0 = automatic
-  int32_t max_lds_damage2 = 0;       // LDS of the damage passes with their elements in two chunks
   int32_t damage_chunks = 0;         // as requested: 1, 2, or 0 = automatic
-  int32_t dmg_nch = 0;               // element chunks of the damage passes (0: not yet chosen)
+  int32_t dmg_nch = 0;               // element chunks of the damage set-up pass (0: not yet chosen)
   int32_t lds_per_cu = 160 * 1024;   // device limits that set how many workgroups share a CU
   int32_t threads_per_cu = 2048;
   int32_t split = -1;
@@ -176,6 +231,10 @@ struct pf_mesh_s {
   std::vector<pf::TileRec> tiles_h;
   pf::DevMesh dm{};
   pf::DevWork dw{};
+  pf::DevRows dr{};
+  int32_t max_rows[pf::kMaxRing + 1] = {};   // rows of the largest row tile for each polynomial degree (0: the default)
+  int32_t max_rlds[pf::kMaxRing + 1] = {};   // and the values it keeps in LDS
+  int32_t max_slds[2][pf::kMaxRing + 1] = {};// and in the set-up pass with its elements in one and in two chunks
   std::vector<void*> allocs;         // every device allocation, freed at destroy
   size_t device_bytes = 0;
   // host mirror of the current per-instance parameters (bytes of InstP<T>[n_inst])
@@ -188,7 +247,7 @@ struct pf_mesh_s {
   int32_t last_rounds[2] = {0, 0};   // CG rounds the last solve of each kind needed (sets the first poll)
   bool qp_started = false;           // a damage solve has been enqueued (resume is allowed)
   std::vector<unsigned char> last_qp_args;   // kernel arguments of the last damage solve's passes
-  int32_t last_qp_cheb = 0;                  // its polynomial degree (0: Jacobi)
+  int32_t last_qp_precond = 0;               // its pf_cg_opts_t.precond
   pf::Ctl* ctl_pinned = nullptr;     // pinned host copy of the control blocks
   hipEvent_t poll_ev = nullptr;      // marks the copy of the control blocks (convergence polls)
   bool timing = false;
@@ -222,6 +281,31 @@ inline size_t elem_size(pf_dtype_t t) { return t == PF_F64 ? 8 : 4; }
 
 pf_status_t check_params(const pf_mesh_s* m, const pf_params_t* p, const double* dt, bool need_dt);
 
+// Host side of the row plan (rows.cpp), built instance by instance.
+struct RowPlan {
+  std::vector<RowTile> tiles;
+  std::vector<int32_t> halo, pos, node, egid;
+  std::vector<uint32_t> ac, xac, ete;
+  std::vector<uint2> code, xcode;
+  std::vector<int2> xs;
+  std::vector<int32_t> rt0, nrt, dmax, ddef; // per instance
+};
+struct RowMesh {
+  int32_t node_off, elem_off, n, ne;
+  const double* xy;                          // the caller's coordinates
+  const int32_t* tri;                        // [ne][3] the caller's node ids, counter-clockwise
+  const int32_t* node_int;                   // [n] internal id of each node (within the instance)
+  const int32_t* eorder;                     // [ne] elements in ascending internal id
+  const int32_t* te_of;                      // [ne] tile element of each element's owner copy, by internal id
+  const std::vector<std::pair<size_t, size_t>>* leaves;   // the tile plan's node ranges (internal order)
+  size_t tile_nodes;                         // owned nodes per tile asked for
+};
+// Appends an instance; width: bytes of the mesh dtype, lds_limit: LDS of a
+// workgroup.  False when no plan fits (a tile's first ring exceeds the LDS).
+bool row_plan_add(RowPlan& rp, const RowMesh& rm, int inst, size_t width, size_t lds_limit);
+void rcb(std::vector<int32_t>& ids, size_t lo, size_t hi, const double* xy, size_t maxn,
+         std::vector<std::pair<size_t, size_t>>& leaves);
+
 // Matrix-free CG on the damage operator (damage.hip).  kind 0: the bound-
 // constrained damage update (b assembled from H, lower bound lb, result in x).
 // kind 1: the linear system A_FF x_F = b_F on the fixed free set F = {W == 0}
@@ -234,7 +318,9 @@ pf_status_t check_state(const pf_state_t* s, bool need_d, bool need_H, const cha
 // Resolve, once per device (that device current), the device address of the
 // static partials array of pf_energies_static (energy.hip).
 pf_status_t energy_scratch_setup(int device);
-// Choose the element chunks of the damage passes for this handle (damage.hip).
+// The stiffness part of the rows, from the mesh and the toughness field (damage.hip).
+void rows_stiffness(pf_mesh_s* m, hipStream_t s);
+// Choose the element chunks of the damage set-up pass for this handle (damage.hip).
 void damage_plan(pf_mesh_s* m);
 bool states_share(const pf_state_t* a, const pf_state_t* b);
 

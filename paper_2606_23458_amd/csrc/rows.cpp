@@ -1,0 +1,342 @@
+// Row plan of the damage passes: the damage operator's rows by node, for
+// workgroups that own a compact run of nodes and keep rings of their
+// neighbours (pf_internal.hpp: RowTile, DevRows).  Host code, run once per
+// handle.
+#include <algorithm>
+#include <atomic>
+#include <new>
+#include <numeric>
+#include <thread>
+
+#include "pf_internal.hpp"
+
+namespace pf {
+
+namespace {
+
+// Owned nodes per row tile.  Per instance, so that a batched handle gives
+// each instance the tiles, and the bits, of a handle of its own.
+size_t row_tile_nodes(size_t n, size_t tile_nodes) {
+  return std::min<size_t>(704, std::max<size_t>(std::min<size_t>(256, tile_nodes), (n + 767) / 768));
+}
+// Degree of the default preconditioner.
+int default_degree(size_t own) { return own < 128 ? 2 : 3; }
+
+constexpr size_t kThreads = 8;
+// f(i, t) for i < n, t < kThreads the thread that runs it
+template <typename F>
+void parallel_for(size_t n, const F& f) {
+  const size_t nt = std::min<size_t>({kThreads, std::max<unsigned>(1, std::thread::hardware_concurrency()), n / 16 + 1});
+  std::atomic<size_t> next{0};
+  std::atomic<bool> out_of_memory{false};
+  auto work = [&](size_t t) {
+    try {
+      for (;;) {
+        const size_t b = next.fetch_add(16);
+        if (b >= n) return;
+        for (size_t i = b; i < std::min(n, b + 16); ++i) f(i, t);
+      }
+    } catch (const std::bad_alloc&) {
+      out_of_memory = true;   // thrown again below, on the caller's thread
+    }
+  };
+  std::vector<std::thread> pool;
+  try {
+    for (size_t t = 1; t < nt; ++t) pool.emplace_back(work, t);
+  } catch (...) {   // no more threads: the ones there are do the work
+  }
+  work(0);
+  for (auto& t : pool) t.join();
+  if (out_of_memory) throw std::bad_alloc();
+}
+
+// The entries of every node's row, by neighbour (row order), each with the
+// element it stands for (c0) and the other element at the pair (c1), as 3 e +
+// edge with e the internal element id, or kNone.  An element stands at each of
+// its nodes for the neighbour that follows in its counter-clockwise order.
+// Rows are in ascending order of c0 (entries without one last).
+constexpr uint32_t kNone = 0xffffffffu;
+struct Graph {
+  std::vector<int64_t> ptr;
+  std::vector<int32_t> nbr;
+  std::vector<uint32_t> c0, c1;
+};
+
+Graph build_graph(const RowMesh& rm, const std::vector<int32_t>& dloc) {
+  const size_t n = size_t(rm.n), ne = size_t(rm.ne);
+  std::vector<int64_t> start(n + 1, 0);
+  for (size_t i = 0; i < 3 * ne; ++i) start[size_t(dloc[rm.tri[i]]) + 1] += 2;
+  for (size_t i = 0; i < n; ++i) start[i + 1] += start[i];
+  struct Entry { int32_t nbr; uint32_t code; bool own; };
+  std::vector<Entry> ent(6 * ne);
+  {
+    std::vector<int64_t> at(start.begin(), start.end() - 1);
+    for (size_t j = 0; j < ne; ++j) {   // ascending internal element id: a fixed order within every pair
+      const int32_t* t = rm.tri + 3 * size_t(rm.eorder[j]);
+      const int32_t v[3] = {dloc[t[0]], dloc[t[1]], dloc[t[2]]};
+      const uint32_t base = 3u * uint32_t(j);
+      const uint32_t edge[3] = {0, 2, 1};   // edges 01, 12, 20
+      for (int q = 0; q < 3; ++q) {
+        ent[size_t(at[v[q]]++)] = {v[(q + 1) % 3], base + edge[q], true};
+        ent[size_t(at[v[(q + 1) % 3]]++)] = {v[q], base + edge[q], false};
+      }
+    }
+  }
+  struct Slot { int32_t nbr; uint32_t c0, c1; };
+  // slots of node i, appended to out
+  auto slots = [&](size_t i, std::vector<Slot>& out) {
+    Entry* lo = ent.data() + start[i];
+    Entry* hi = ent.data() + start[i + 1];
+    std::stable_sort(lo, hi, [](const Entry& x, const Entry& y) { return x.nbr < y.nbr; });
+    for (Entry* a = lo; a < hi;) {
+      Entry* b = a;
+      while (b < hi && b->nbr == a->nbr) ++b;
+      Entry *o = a, *p = a;   // the next of each kind
+      for (;;) {
+        while (o < b && !o->own) ++o;
+        while (p < b && p->own) ++p;
+        if (o == b && p == b) break;
+        out.push_back({a->nbr, o < b ? (o++)->code : kNone, p < b ? (p++)->code : kNone});
+      }
+      a = b;
+    }
+    std::stable_sort(out.begin(), out.end(), [](const Slot& x, const Slot& y) { return x.c0 < y.c0; });
+  };
+  const size_t blocks = (n + 1023) / 1024;
+  std::vector<std::vector<Slot>> all(blocks);
+  std::vector<int32_t> cnt(n, 0);
+  parallel_for(blocks, [&](size_t blk, size_t) {
+    std::vector<Slot> row;
+    all[blk].reserve(1024 * 7);
+    for (size_t i = blk * 1024; i < std::min(n, (blk + 1) * 1024); ++i) {
+      row.clear();
+      slots(i, row);
+      cnt[i] = int32_t(row.size());
+      all[blk].insert(all[blk].end(), row.begin(), row.end());
+    }
+  });
+  Graph g;
+  g.ptr.assign(n + 1, 0);
+  for (size_t i = 0; i < n; ++i) g.ptr[i + 1] = g.ptr[i] + cnt[i];
+  g.nbr.resize(size_t(g.ptr[n]));
+  g.c0.resize(g.nbr.size());
+  g.c1.resize(g.nbr.size());
+  parallel_for(blocks, [&](size_t blk, size_t) {
+    size_t o = size_t(g.ptr[blk * 1024]);
+    for (const Slot& q : all[blk]) g.nbr[o] = q.nbr, g.c0[o] = q.c0, g.c1[o] = q.c1, ++o;
+  });
+  return g;
+}
+
+struct HostTile {
+  int32_t lo, hi;                  // owned nodes, row order
+  int32_t nl[kMaxRing + 1];
+  int32_t rings;                   // complete rings
+  std::vector<int32_t> ring;       // ring nodes, ring by ring
+  std::vector<int32_t> xcount;     // extra pairs of each slice
+  std::vector<int32_t> elems;      // internal ids of the elements at its nodes, ring by ring
+  int32_t nel[kMaxRing];
+};
+
+}  // namespace
+
+bool row_plan_add(RowPlan& rp, const RowMesh& rm, int inst, size_t width, size_t lds_limit) {
+  const size_t n = size_t(rm.n);
+  const size_t static_lds = 2048;   // the passes' reduction scratch
+  const size_t max1 = std::min<size_t>(65535, (lds_limit - static_lds) / 8);            // nodes, one FP64 vector in LDS
+  const size_t max2 = std::min<size_t>(65535, (lds_limit - static_lds) / (2 * width));  // nodes, two vectors
+  const size_t own = row_tile_nodes(n, rm.tile_nodes);
+  std::vector<int32_t> dloc(n);
+  std::vector<HostTile> tiles;
+  Graph g;
+  int dmax = 0;
+  std::vector<std::vector<int32_t>> scratch(kThreads);   // per thread: the tile's local id of an element, or -1
+  // the second plan takes the handle's own tiles, whose first ring and elements are known to fit
+  for (int plan = 0; plan < 2 && dmax < 1; ++plan) {
+    std::vector<std::pair<size_t, size_t>> leaves;
+    if (plan == 0) {
+      std::vector<int32_t> ids(n);
+      std::iota(ids.begin(), ids.end(), 0);
+      rcb(ids, 0, n, rm.xy, own, leaves);
+      int32_t p = 0;
+      for (auto& l : leaves) {
+        std::sort(ids.begin() + l.first, ids.begin() + l.second);
+        for (size_t i = l.first; i < l.second; ++i) dloc[ids[i]] = p++;
+      }
+    } else {
+      leaves = *rm.leaves;
+      for (size_t i = 0; i < n; ++i) dloc[i] = rm.node_int[i];
+    }
+    g = build_graph(rm, dloc);
+    tiles.assign(leaves.size(), HostTile());
+    parallel_for(tiles.size(), [&](size_t ti, size_t th) {
+      HostTile& t = tiles[ti];
+      std::vector<int32_t>& mark = scratch[th];
+      if (mark.empty()) mark.assign(size_t(rm.ne), -1);
+      t.lo = int32_t(leaves[ti].first);
+      t.hi = int32_t(leaves[ti].second);
+      t.nl[0] = t.hi - t.lo;
+      t.rings = 0;
+      // ring k: unseen neighbours of ring k-1 (of the owned nodes for k = 1).  A
+      // neighbour of ring k-1 lies in ring k-2, k-1 or k, so those are all to
+      // look through
+      std::vector<int32_t> prev2, prev, cur;
+      for (int k = 1; k <= kMaxRing; ++k) {
+        cur.clear();
+        auto grow = [&](int32_t u) {
+          for (int64_t q = g.ptr[u]; q < g.ptr[u + 1]; ++q) {
+            const int32_t v = g.nbr[size_t(q)];
+            if (v < t.lo || v >= t.hi) cur.push_back(v);
+          }
+        };
+        if (k == 1)
+          for (int32_t u = t.lo; u < t.hi; ++u) grow(u);
+        else
+          for (int32_t u : prev) grow(u);
+        std::sort(cur.begin(), cur.end());
+        cur.erase(std::unique(cur.begin(), cur.end()), cur.end());
+        cur.erase(std::remove_if(cur.begin(), cur.end(),
+                                 [&](int32_t v) {
+                                   return std::binary_search(prev.begin(), prev.end(), v) ||
+                                          std::binary_search(prev2.begin(), prev2.end(), v);
+                                 }),
+                  cur.end());
+        // the elements at the nodes of ring k-1 that are not yet listed
+        const size_t e0 = t.elems.size();
+        auto list = [&](int32_t u) {
+          for (int64_t q = g.ptr[u]; q < g.ptr[u + 1]; ++q)
+            if (g.c0[size_t(q)] != kNone && mark[g.c0[size_t(q)] / 3u] < 0) {
+              mark[g.c0[size_t(q)] / 3u] = 0;
+              t.elems.push_back(int32_t(g.c0[size_t(q)] / 3u));
+            }
+        };
+        if (k == 1)
+          for (int32_t u = t.lo; u < t.hi; ++u) list(u);
+        else
+          for (int32_t u : prev) list(u);
+        std::sort(t.elems.begin() + e0, t.elems.end());
+        const size_t total = size_t(t.nl[k - 1]) + cur.size();
+        // rows are the nodes up to ring k-1; degree 1 keeps one vector in LDS;
+        // the set-up pass the start and two values per element; codes have 16 bits
+        if (total > (k == 1 ? max1 : max2) || t.nl[k - 1] > kRowMax || 3 * t.elems.size() > 65535 ||
+            size_t(k == 1 ? total : size_t(t.nl[1])) + 2 * t.elems.size() > max1) {
+          for (size_t q = e0; q < t.elems.size(); ++q) mark[size_t(t.elems[q])] = -1;
+          t.elems.resize(e0);
+          break;
+        }
+        t.nel[k - 1] = int32_t(t.elems.size());
+        t.nl[k] = int32_t(total);
+        t.rings = k;
+        t.ring.insert(t.ring.end(), cur.begin(), cur.end());
+        prev2.swap(prev);
+        prev.swap(cur);
+      }
+      for (int k = t.rings + 1; k <= kMaxRing; ++k) t.nl[k] = t.nl[t.rings];
+      for (int32_t e : t.elems) mark[size_t(e)] = -1;
+    });
+    dmax = kMaxRing;
+    for (const HostTile& t : tiles) dmax = std::min(dmax, int(t.rings));
+  }
+  if (dmax < 1) return false;
+
+  // slices and their extra pairs
+  auto node_at = [](const HostTile& t, int32_t i) { return i < t.nl[0] ? t.lo + i : t.ring[size_t(i - t.nl[0])]; };
+  auto nslices = [&](const HostTile& t) { return (t.nl[dmax - 1] + 63) / 64; };
+  parallel_for(tiles.size(), [&](size_t ti, size_t) {
+    HostTile& t = tiles[ti];
+    t.xcount.assign(size_t(nslices(t)), 0);
+    for (int32_t i = 0; i < t.nl[dmax - 1]; ++i) {
+      const int32_t u = node_at(t, i);
+      const int32_t pairs = int32_t((g.ptr[u + 1] - g.ptr[u] + 1) / 2);
+      t.xcount[size_t(i / 64)] = std::max(t.xcount[size_t(i / 64)], pairs - kRowPairs);
+    }
+  });
+  const size_t tile0 = rp.tiles.size();
+  size_t slice = rp.xs.size(), halo = rp.halo.size(), xp = rp.xac.size() / 64, el = rp.ete.size();
+  for (const HostTile& t : tiles) {
+    RowTile r{};
+    r.node0 = rm.node_off + t.lo;
+    for (int k = 0; k <= kMaxRing; ++k) r.nl[k] = t.nl[std::min(k, dmax)];
+    r.halo0 = int32_t(halo);
+    r.slice0 = int32_t(slice);
+    r.nslice = nslices(t);
+    r.inst = inst;
+    r.el0 = int32_t(el);
+    for (int k = 0; k < kMaxRing; ++k) r.nel[k] = t.nel[std::min(k, dmax - 1)];
+    el += size_t(r.nel[dmax - 1]);
+    rp.tiles.push_back(r);
+    for (int32_t x : t.xcount) {
+      rp.xs.push_back(int2{int32_t(xp), x});
+      xp += size_t(x);
+    }
+    slice += size_t(r.nslice);
+    halo += size_t(r.nl[dmax] - r.nl[0]);
+  }
+  rp.halo.resize(halo);
+  rp.ac.resize(slice * kRowPairs * 64, 0);
+  constexpr uint32_t no2 = kNoCode | (kNoCode << 16);
+  rp.code.resize(slice * kRowPairs * 64, uint2{no2, no2});
+  rp.xac.resize(xp * 64, 0);
+  rp.xcode.resize(xp * 64, uint2{no2, no2});
+  rp.ete.resize(el);
+  rp.egid.resize(el);
+  parallel_for(tiles.size(), [&](size_t ti, size_t th) {
+    const HostTile& t = tiles[ti];
+    const RowTile& r = rp.tiles[tile0 + ti];
+    std::vector<int32_t>& mark = scratch[th];
+    if (mark.empty()) mark.assign(size_t(rm.ne), -1);
+    for (int32_t q = 0; q < r.nel[dmax - 1]; ++q) {
+      const int32_t e = t.elems[size_t(q)];
+      rp.ete[size_t(r.el0 + q)] = uint32_t(rm.te_of[e]);
+      rp.egid[size_t(r.el0 + q)] = rm.elem_off + e;
+      mark[size_t(e)] = q;
+    }
+    auto code16 = [&](uint32_t c) { return c == kNone ? kNoCode : 3u * uint32_t(mark[c / 3u]) + c % 3u; };
+    const int32_t nhalo = r.nl[dmax] - r.nl[0];
+    // ring nodes by position, with their local ids
+    std::vector<std::pair<int32_t, int32_t>> loc(static_cast<size_t>(nhalo));
+    for (int32_t j = 0; j < nhalo; ++j) {
+      rp.halo[size_t(r.halo0 + j)] = rm.node_off + t.ring[size_t(j)];
+      loc[size_t(j)] = {t.ring[size_t(j)], r.nl[0] + j};
+    }
+    std::sort(loc.begin(), loc.end());
+    auto local = [&](int32_t u) -> uint32_t {
+      if (u >= t.lo && u < t.hi) return uint32_t(u - t.lo);
+      return uint32_t(std::lower_bound(loc.begin(), loc.end(), std::make_pair(u, int32_t(0)))->second);
+    };
+    for (int32_t i = 0; i < r.nl[dmax - 1]; ++i) {
+      const int32_t u = node_at(t, i);
+      const size_t s = size_t(r.slice0 + i / 64), lane = size_t(i % 64);
+      int32_t k = 0;
+      for (int64_t q = g.ptr[u]; q < g.ptr[u + 1]; ++q, ++k) {
+        const int32_t pair = k / 2;
+        const bool base = pair < kRowPairs;
+        const size_t at = base ? (s * kRowPairs + size_t(pair)) * 64 + lane
+                               : (size_t(rp.xs[s].x) + size_t(pair - kRowPairs)) * 64 + lane;
+        uint32_t& ac = base ? rp.ac[at] : rp.xac[at];
+        uint2& code = base ? rp.code[at] : rp.xcode[at];
+        const uint32_t cc = code16(g.c0[size_t(q)]) | (code16(g.c1[size_t(q)]) << 16);
+        const uint32_t l = local(g.nbr[size_t(q)]);
+        if (k % 2 == 0) {
+          ac |= l;
+          code.x = cc;
+        } else {
+          ac |= l << 16;
+          code.y = cc;
+        }
+      }
+    }
+    for (int32_t q = 0; q < r.nel[dmax - 1]; ++q) mark[size_t(t.elems[size_t(q)])] = -1;
+  });
+  for (size_t u = 0; u < n; ++u) {
+    rp.pos[size_t(rm.node_off + rm.node_int[u])] = rm.node_off + dloc[u];
+    rp.node[size_t(rm.node_off + dloc[u])] = rm.node_off + rm.node_int[u];
+  }
+  rp.rt0.push_back(int32_t(tile0));
+  rp.nrt.push_back(int32_t(tiles.size()));
+  rp.dmax.push_back(dmax);
+  rp.ddef.push_back(std::min(dmax, default_degree(own)));
+  return true;
+}
+
+}  // namespace pf

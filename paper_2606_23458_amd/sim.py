@@ -211,7 +211,7 @@ class CgConfig:
     monotone: int = 0       # damage solve: 1 = monotone projected CG from the start
     rounds: int = 0         # check_every = 0: CG rounds to enqueue (0 = max_iter)
     resume: int = 0         # damage solve: 1 = continue the handle's previous solve
-    precond: int = 0        # 0: Jacobi; 2-4: Chebyshev-Jacobi polynomial of that degree
+    precond: int = 0        # 0: the library's choice; 1: Jacobi; 2-4: Chebyshev-Jacobi polynomial of that degree
 
     def opts(self) -> L.CgOpts:
         return L.CgOpts(self.tol, self.max_iter, self.check_every, self.start, self.monotone, self.rounds,

@@ -1,0 +1,115 @@
+"""The damage passes over assembled rows against the exact minimiser of the QP: row tiles of
+every number of rows per thread, rows longer than the base entries, tiles with one ring only,
+every polynomial degree, and plates whose tiles are mostly held.  Tolerances: the solver's
+stopping residual (1e-12 FP64, 1e-6 FP32) times the operator's condition number (about 30 at
+l0 = 2h), with a factor of three."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as w
+from oracle.damage import DamageQP
+from oracle.step import Sim as OSim
+
+pytestmark = pytest.mark.gpu
+
+TOL = {"f64": 1e-10, "f32": 1e-4}
+
+
+def _solve(p, dtype, tile, precond, H, lb, damage_chunks=0):
+    from paper_2606_23458_amd import Mesh, Simulator, State
+    from paper_2606_23458_amd.sim import CgConfig, default_tol
+    mesh = Mesh([p], dtype, tile, damage_chunks=damage_chunks)
+    sim = Simulator(p, dtype=dtype, mesh=mesh, cg=CgConfig(tol=default_tol(dtype), precond=precond))
+    z = np.zeros((p.n_nodes, 2))
+    s = State.from_user(mesh, [{"u": z, "v": z, "a": z, "d": lb, "H": H}])
+    d = torch.zeros_like(s.d)
+    sim.damage(s.H, s.d, d, sim.active)
+    torch.cuda.synchronize()
+    return mesh.nodes_from_internal(d.double())[0], sim.cg_stats()[0]
+
+
+def _load(p, seed, held=0.3):
+    r = np.random.default_rng(seed)
+    H = r.uniform(0, 8000.0, p.n_elems) * (r.random(p.n_elems) < 0.5)
+    lb = np.where(r.random(p.n_nodes) < held, r.uniform(0, 0.9, p.n_nodes), 0.0)
+    lb[p.d0 == 1.0] = 1.0
+    return H, lb
+
+
+def _fan(n, rings):
+    """`rings` rings of n nodes around one node of n neighbours."""
+    h = 2.5e-4
+    t = 2 * np.pi * np.arange(n) / n
+    xy = [np.zeros((1, 2))] + [h * (1 + 0.5 * k) * np.stack([np.cos(t), np.sin(t)], 1) for k in range(rings)]
+    i, j = np.arange(n), (np.arange(n) + 1) % n
+    tri = [np.stack([0 * i, 1 + i, 1 + j], 1)]
+    for k in range(1, rings):
+        a, b = 1 + (k - 1) * n, 1 + k * n
+        tri += [np.stack([a + i, b + i, b + j], 1), np.stack([a + i, b + j, a + j], 1)]
+    xy, tri = np.concatenate(xy), np.concatenate(tri).astype(np.int32)
+    z = np.zeros_like(xy)
+    return w.small_plate(4, 2).with_(name="fan", xy=xy, tri=tri, fixed=np.zeros(xy.shape, np.uint8), u0=z, v0=z.copy(),
+                                     a0=z.copy(), d0=np.zeros(len(xy)), H0=np.zeros(len(tri)))
+
+
+# row tiles of 64 and 256 owned nodes, and plates that are one tile with a remainder of every
+# kind: 255, 256, 257 nodes (one or two rows per thread) and 17, 3
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("precond", [0, 1, 2, 3, 4])
+@pytest.mark.parametrize("nx,ny,tile,diag", [(16, 14, 256, False), (15, 15, 256, True), (256, 1, 512, False), (1, 1, 64, False),
+                                             (40, 37, 64, True), (61, 43, 1024, True)])
+def test_row_tiles_match_exact_qp(dtype, precond, nx, ny, tile, diag):
+    p = w.small_plate(nx, ny, jitter=0.15, seed=4, model=2, random_diag=diag)
+    H, lb = _load(p, nx + ny)
+    got, st = _solve(p, dtype, tile, precond, H, lb)
+    ref = DamageQP(OSim(p).mesh, p.l0, 2).solve(H, p.Gc, lb)[0]
+    assert st["flags"] == 0, st
+    assert np.max(np.abs(got - ref)) < TOL[dtype], st
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("n,rings", [(7, 40), (9, 30), (40, 12)])
+def test_long_rows_match_exact_qp(dtype, n, rings):
+    """A hub with 7 (one extra entry), 9 (two extra pairs) and 40 neighbours."""
+    p = _fan(n, rings)
+    H, lb = _load(p, n)
+    for chunks in (1, 2):
+        got, st = _solve(p, dtype, 256, 0, H, lb, chunks)
+        ref = DamageQP(OSim(p).mesh, p.l0, 2).solve(H, p.Gc, lb)[0]
+        assert st["flags"] == 0, st
+        assert np.max(np.abs(got - ref)) < TOL[dtype], st
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("precond", [0, 1, 4])
+def test_mostly_held_plate_matches_exact_qp(dtype, precond):
+    """AT1 above its threshold in one corner only: most row tiles own no free node and sit out
+    the CG runs; the held set moves between them."""
+    p = w.small_plate(120, 60, jitter=0.15, seed=6, model=1, random_diag=True).with_(d0=np.zeros(121 * 61))
+    cen = p.xy[p.tri].mean(1)
+    hc = 3 * p.Gc / (16 * p.l0)
+    H = 0.5 * hc + 40 * hc * np.exp(-((cen - cen.min(0)) ** 2).sum(1) / (12 * 2.5e-4) ** 2)
+    got, st = _solve(p, dtype, 64, precond, H, np.zeros(p.n_nodes))
+    ref = DamageQP(OSim(p).mesh, p.l0, 1).solve(H, p.Gc, np.zeros(p.n_nodes))[0]
+    assert st["flags"] == 0 and 0 < np.count_nonzero(ref) < 0.4 * p.n_nodes, st
+    assert np.max(np.abs(got - ref)) < TOL[dtype], st
+
+
+def test_adjoint_solve_reaches_its_tolerance_in_fp32():
+    """The multiplier of a smooth right-hand side is many times its scaled size; the FP64 iterate
+    keeps its rounding below the FP32 tolerance, so the solve ends in a few rounds."""
+    from paper_2606_23458_amd import Simulator, State
+    from paper_2606_23458_amd.grad import backward_step
+    p = w.small_plate(160, 80, jitter=0.05, seed=3)
+    sim = Simulator(p, dtype="f32")
+    sim.step(3)
+    s0, s1 = sim._next, sim.state
+    adj1, adj0 = State(sim.mesh), State(sim.mesh)
+    pos = sim.mesh.nodes_to_internal([np.cos(p.xy[:, 0] / (20 * 2.5e-4)) + 2.0])
+    adj1.nodes[6].copy_(torch.tensor(pos, dtype=torch.float32))
+    dgc = torch.zeros(1, dtype=torch.float64, device="cuda")
+    backward_step(sim, s0, s1, sim.active, adj1, adj0, dgc)
+    torch.cuda.synchronize()
+    st = sim.cg_stats()[0]
+    assert st["flags"] == 0 and st["iters"] < 40, st
