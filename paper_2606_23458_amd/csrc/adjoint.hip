@@ -123,9 +123,9 @@ __global__ __launch_bounds__(kBlock) void k_adj_damage(DevMesh dm, const InstP<T
 }
 
 // One workgroup per instance: dGc += the instance's tile partials, fixed order.
-__global__ __launch_bounds__(kBlock) void k_adj_reduce(const Ctl* ctl, const double* part, int n_tiles, double* dGc) {
+__global__ __launch_bounds__(kBlock) void k_adj_reduce(const InstFix* fix, const double* part, int n_tiles, double* dGc) {
   __shared__ double red[4 * kWaves];
-  const Ctl* c = ctl + blockIdx.x;
+  const InstFix* c = fix + blockIdx.x;
   double s = 0.0;
   const double* p7 = part + size_t(7) * n_tiles + c->tile0;
   for (int k = threadIdx.x; k < c->ntiles; k += kBlock) s += p7[k];
@@ -343,7 +343,7 @@ static pf_status_t backward_t(pf_mesh_s* m, int split, const pf_state_t* s_n, co
                      static_cast<const T*>(s_np1->d), static_cast<const T*>(s_np1->H),
                      static_cast<const T*>(adj1->d), static_cast<const T*>(adj1->H), m->dw.wset,
                      static_cast<T*>(m->dw.hbar), static_cast<T*>(adj0->d), m->dgc_field);
-  hipLaunchKernelGGL(k_adj_reduce, dim3(m->n_inst), block, 0, s, m->dw.ctl, m->dw.part, m->n_tiles, dGc);
+  hipLaunchKernelGGL(k_adj_reduce, dim3(m->n_inst), block, 0, s, m->dw.fix, m->dw.part, m->n_tiles, dGc);
   const StateIn<T> sn = state_in<T>(s_n), sn1 = state_in<T>(s_np1), a1 = state_in<T>(adj1);
   const StateOut<T> a0 = state_out<T>(adj0);
   const T* hb = static_cast<const T*>(m->dw.hbar);

@@ -102,6 +102,7 @@ struct DmgArgs {
   DevRows dr;
   const InstP<T>* __restrict__ ip;
   Ctl* ctl;
+  const InstFix* __restrict__ fix;
   double* part;
   const T* __restrict__ H;
   const T* __restrict__ lb;      // the caller's lower bound (internal order)
@@ -124,7 +125,7 @@ struct DmgArgs {
   int32_t max_iter;
   int32_t kind;        // CG_QP or CG_LINEAR
   int32_t start;       // 1: extrapolated start for the damage solve
-  int32_t deg;         // polynomial degree (an instance runs min(deg, Ctl::dmax)); 0: Ctl::ddef
+  int32_t deg;         // polynomial degree (an instance runs min(deg, InstFix::dmax)); 0: InstFix::ddef
   // combination of the round in the pass's last workgroup: 0 none (a
   // k_dmg_red launch follows), 1 combine and advance the solver, 2 combine and
   // run the state machine without storing it (timing aid)
@@ -172,15 +173,17 @@ __global__ void k_dmg_init(Ctl* ctl, int n_inst, int kind, int monotone) {
   c.resid = 0.0;
   c.pq = 0.0;
   c.ref = (kind == CG_QP) ? 1.0 : 0.0;
-  // steps of the Chebyshev iteration
-  const double lb = c.lmax, la = lb / kChebRatio;
-  const double theta = 0.5 * (lb + la), delta = 0.5 * (lb - la), sigma = theta / delta;
-  c.ith = 1.0 / theta;
+}
+
+void chebyshev_steps(InstFix& f, double lmax) {
+  const double la = lmax / kChebRatio;
+  const double theta = 0.5 * (lmax + la), delta = 0.5 * (lmax - la), sigma = theta / delta;
+  f.ith = 1.0 / theta;
   double rp = 1.0 / sigma;
   for (int j = 0; j < kMaxRing - 1; ++j) {
     const double rj = 1.0 / (2.0 * sigma - rp);
-    c.ch1[j] = rj * rp;
-    c.ch2[j] = 2.0 * rj / delta;
+    f.ch1[j] = rj * rp;
+    f.ch2[j] = 2.0 * rj / delta;
     rp = rj;
   }
 }
@@ -214,22 +217,33 @@ struct NodeCheck {
 };
 
 template <typename T>
-__device__ __forceinline__ void arrive_and_advance(const DmgArgs<T>& a, Ctl* c, int tile, int tile0, int ntiles,
-                                                   int n_tiles, int bnd, double* red);
+__device__ __forceinline__ void arrive_and_advance(const DmgArgs<T>& a, int inst, int tile, int bnd, double* red);
+
+// The value of v in lane j (the same j in every lane of the wave).
+__device__ __forceinline__ float lane_value(float v, int j) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), j));
+}
+__device__ __forceinline__ double lane_value(double v, int j) {
+  const long long u = __double_as_longlong(v);
+  const uint32_t lo = uint32_t(__builtin_amdgcn_readlane(int(uint32_t(u)), j));
+  const uint32_t hi = uint32_t(__builtin_amdgcn_readlane(int(uint32_t(static_cast<unsigned long long>(u) >> 32)), j));
+  return __longlong_as_double(static_cast<long long>((static_cast<unsigned long long>(hi) << 32) | lo));
+}
 
 // Partials of a pass, in PT_* order, stored value-major [8][n_tiles] so the
 // reduction reads them coalesced; thread k holds value k.  FUSE: stored
 // through to the device-coherent level for the combination in this launch's
 // last workgroup.
 template <typename T, bool FUSE>
-__device__ __forceinline__ void finish_pass(const DmgArgs<T>& a, Ctl* c, double (&v)[8], int tile, int tile0, int ntiles,
-                                            int n_tiles, int bnd, double* red) {
+__device__ __forceinline__ void finish_pass(const DmgArgs<T>& a, int inst, double (&v)[8], int tile, int bnd,
+                                            double* red) {
+  const int n_tiles = a.dr.n_tiles;
   const double tot = block_reduce_rows<8, kPartOps>(v, red);
   if constexpr (FUSE) {
     if (threadIdx.x < 8)
       __hip_atomic_store(&a.part[size_t(threadIdx.x) * n_tiles + tile], tot, __ATOMIC_RELAXED,
                          __HIP_MEMORY_SCOPE_AGENT);
-    arrive_and_advance(a, c, tile, tile0, ntiles, n_tiles, bnd, red);
+    arrive_and_advance(a, inst, tile, bnd, red);
   } else {
     if (threadIdx.x < 8) a.part[size_t(threadIdx.x) * n_tiles + tile] = tot;
   }
@@ -282,14 +296,15 @@ __global__ __launch_bounds__(kBlock) void k_cg_setup(DmgArgs<T> a) {
   const RowTile* const tp = a.dr.tiles + tile;
   const int n_own = tp->nl[0], nall = tp->nl[1], node0 = tp->node0, halo0 = tp->halo0, slice0 = tp->slice0;
   const int el0 = tp->el0;
-  Ctl* const c = a.ctl + tp->inst;
-  const InstP<T>* const P = a.ip + tp->inst;
+  const int inst = tp->inst;
+  const Ctl* const c = a.ctl + inst;
+  const InstP<T>* const P = a.ip + inst;
   const int bnd = P->bounds;
   const bool qp = (a.kind == CG_QP);
   const bool projected = qp && (bnd == PF_BOUNDS_PROJECTED);
   const bool monotone = projected && (c->flavor != 0);
   const double tol = a.tol;
-  const int deg = a.deg ? min(a.deg, c->dmax) : c->ddef;
+  const int deg = a.deg ? min(a.deg, a.fix[inst].dmax) : a.fix[inst].ddef;
   const int nrow = tp->nl[deg - 1], nel = tp->nel[deg - 1];
   const int tid = threadIdx.x;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
@@ -442,7 +457,7 @@ __global__ __launch_bounds__(kBlock) void k_cg_setup(DmgArgs<T> a) {
     nc.stop(w, sr);
   }
   double v[8] = {0.0, INFINITY, 0.0, nc.cf, nc.ca, nc.na, rb, nc.ch};   // in PT_* order
-  finish_pass<T, FUSE>(a, c, v, tile, c->rt0, c->nrt, a.dr.n_tiles, bnd, red);
+  finish_pass<T, FUSE>(a, inst, v, tile, bnd, red);
 }
 
 // One pass of a solve over the row tiles, after the set-up.  RPT: rows (owned and
@@ -456,10 +471,9 @@ __global__ __launch_bounds__(kBlock, RPT <= 4 ? (RPT <= 2 ? 4 : 3) : 1) void k_c
   __shared__ double red[8 * 4 * kWaves];
   const int tile = tile_of_block(a.dr.n_tiles);
   const RowTile* const tp = a.dr.tiles + tile;
-  const int n_own = tp->nl[0], n1 = tp->nl[1], n2 = tp->nl[2], n3 = tp->nl[3], n4 = tp->nl[4];
+  const int n_own = tp->nl[0];
   const int node0 = tp->node0, halo0 = tp->halo0, slice0 = tp->slice0, nslice = tp->nslice, inst = tp->inst;
-  auto nl = [&](int k) { return k == 0 ? n_own : (k == 1 ? n1 : (k == 2 ? n2 : (k == 3 ? n3 : n4))); };
-  Ctl* const c = a.ctl + inst;
+  const Ctl* const c = a.ctl + inst;
   const int mode = c->mode;
   if (mode == MODE_DONE) return;
   const InstP<T>* const P = a.ip + inst;
@@ -473,14 +487,14 @@ __global__ __launch_bounds__(kBlock, RPT <= 4 ? (RPT <= 2 ? 4 : 3) : 1) void k_c
   if (iter && !monotone && a.dr.idle[tile]) {
     // no free node here: z, p and the update of x are 0 (see the first pass)
     double v[8] = {0.0, INFINITY, 0.0, 0.0, -INFINITY, 0.0, 0.0, 0.0};
-    finish_pass<T, FUSE>(a, c, v, tile, c->rt0, c->nrt, a.dr.n_tiles, bnd, red);
+    finish_pass<T, FUSE>(a, inst, v, tile, bnd, red);
     return;
   }
   const bool cur1 = c->pbuf != 0;
   const double beta = c->beta;
   const T al = T(c->alpha), be = T(beta);
   const double tol = a.tol;
-  const int deg = a.deg ? min(a.deg, c->dmax) : c->ddef;
+  const int deg = a.deg ? min(a.deg, a.fix[inst].dmax) : a.fix[inst].ddef;
   // current halves (read) and next halves (written) of the pairs
   const double* __restrict__ xc = cur1 ? a.x1 : a.x0;
   double* xn_ = cur1 ? a.x0 : a.x1;
@@ -490,11 +504,16 @@ __global__ __launch_bounds__(kBlock, RPT <= 4 ? (RPT <= 2 ? 4 : 3) : 1) void k_c
   Two<T>* wzn = iter ? (cur1 ? a.wz0 : a.wz1) : (cur1 ? a.wz1 : a.wz0);
 
   extern __shared__ __align__(16) unsigned char smem[];
-  const int nall = nl(xpass ? 1 : deg);       // nodes whose values the pass needs
+  const int nall = tp->nl[xpass ? 1 : deg];   // nodes whose values the pass needs
   T* const ya = reinterpret_cast<T*>(smem);   // the vector the pass multiplies by A, two halves
   T* const yb = ya + nall;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int nh = nall - n_own;
+  // the steps of the Chebyshev iteration and the rings' sizes, one per lane:
+  // read back lane by lane, so no step waits for memory
+  const int sl_ = min(lane, kMaxRing - 2);
+  const T steps_c1 = T(a.fix[inst].ch1[sl_]), steps_c2 = T(a.fix[inst].ch2[sl_]);
+  const int steps_nl = tp->nl[min(lane, kMaxRing)];
 
   // ---- the rows of this thread --------------------------------------------------
   Two<T> av[RPT][kRowPairs];
@@ -637,11 +656,11 @@ __global__ __launch_bounds__(kBlock, RPT <= 4 ? (RPT <= 2 ? 4 : 3) : 1) void k_c
       if (idle) {
         for (int i = tid; i < n_own; i += kBlock) xn_[node0 + i] = xc[node0 + i];
         double v[8] = {0.0, INFINITY, 0.0, 0.0, -INFINITY, 0.0, 0.0, 0.0};
-        finish_pass<T, FUSE>(a, c, v, tile, c->rt0, c->nrt, a.dr.n_tiles, bnd, red);
+        finish_pass<T, FUSE>(a, inst, v, tile, bnd, red);
         return;
       }
     }
-    const T ith = deg > 1 ? T(c->ith) : T(1);
+    const T ith = deg > 1 ? T(a.fix[inst].ith) : T(1);
     T r_[RPT], y_[RPT], d_[RPT];   // residual, Chebyshev iterate and its update of this thread's rows
     Two<T> rsv[RPT], wzv[RPT];
     T pv_[RPT], lbv_[RPT];
@@ -710,10 +729,11 @@ __global__ __launch_bounds__(kBlock, RPT <= 4 ? (RPT <= 2 ? 4 : 3) : 1) void k_c
     if constexpr (!kEarlyRows) load_rows();
     __syncthreads();
     const T* ys = ya;
+#pragma unroll 1
     for (int j = 1; j < deg; ++j) {
-      const int lim = nl(deg - j);
+      const int lim = __builtin_amdgcn_readlane(steps_nl, deg - j);
       T* const yd = (j & 1) ? yb : ya;
-      const T c1 = T(c->ch1[j - 1]), c2 = T(c->ch2[j - 1]);
+      const T c1 = lane_value(steps_c1, j - 1), c2 = lane_value(steps_c2, j - 1);
 #pragma unroll
       for (int k = 0; k < RPT; ++k) {
         const int i = tid + k * kBlock;
@@ -745,7 +765,7 @@ __global__ __launch_bounds__(kBlock, RPT <= 4 ? (RPT <= 2 ? 4 : 3) : 1) void k_c
     }
   }
   double v[8] = {del, amin, gam, nc.cf, nc.ca, nc.na, 0.0, nc.ch};   // in PT_* order
-  finish_pass<T, FUSE>(a, c, v, tile, c->rt0, c->nrt, a.dr.n_tiles, bnd, red);
+  finish_pass<T, FUSE>(a, inst, v, tile, bnd, red);
 }
 
 // Combination of an instance's per-tile partials, in a fixed order: thread t
@@ -782,7 +802,7 @@ __device__ __forceinline__ double combine_partials(double* part, size_t nt, int 
 
 // The solver's state machine: one round's combined partials advance the
 // instance's control block c (a register copy; the caller stores it).
-__device__ __forceinline__ void advance_solver(Ctl* c, const double (&v)[8], int bnd, int kind, double tol,
+__device__ __forceinline__ void advance_solver(Ctl* c, int nnodes, const double (&v)[8], int bnd, int kind, double tol,
                                                int max_iter) {
   const int mode = c->mode;
   const double sdel = v[PT_DELTA], samin = v[PT_AMIN], sgam = v[PT_GAMMA], scf = v[PT_CF], sca = v[PT_CA];
@@ -864,7 +884,7 @@ __device__ __forceinline__ void advance_solver(Ctl* c, const double (&v)[8], int
     c->resid = scf / rs;
     const double beta = sgam / c->rz;
     const double den = sdel - beta * sgam / c->alpha;
-    const bool early = projected && !monotone && c->inner >= 2 && sch > 0.25 * double(c->nnodes - c->nact);
+    const bool early = projected && !monotone && c->inner >= 2 && sch > 0.25 * double(nnodes - c->nact);
     if (!isfinite(sgam) || !isfinite(sdel)) {
       c->flags |= PF_FLAG_NONFINITE;
       c->mode = MODE_DONE;
@@ -894,20 +914,27 @@ __device__ __forceinline__ void advance_solver(Ctl* c, const double (&v)[8], int
 // One workgroup per instance: combine the tiles' partials and advance the
 // state (passes run without the combination in their last workgroup).
 constexpr int kRedBlock = kBlock;
-__global__ __launch_bounds__(kRedBlock) void k_dmg_red(Ctl* ctl, const double* part, int n_tiles, const int* bounds,
+__global__ __launch_bounds__(kRedBlock) void k_dmg_red(Ctl* ctl, const InstFix* fix, const double* part, int n_tiles, const int* bounds,
                                                        int kind, double tol, int max_iter) {
   __shared__ double red[8 * 4 * (kRedBlock / 64)];
   __shared__ double tot[8];
   Ctl* const cp = ctl + blockIdx.x;
   Ctl cc;
-  int bnd = 0;
+  int bnd = 0, nnodes = 0;
   if (threadIdx.x == 0) {
     cc = *cp;
     bnd = bounds[blockIdx.x];
+    nnodes = fix[blockIdx.x].nnodes;
   }
-  if (cp->mode == MODE_DONE) return;
-  const int tile0 = cp->rt0;
-  const int tile_end = tile0 + cp->nrt;
+  const int mode = cp->mode;
+  // one instance: its tiles are all there are, known without a load, so that the
+  // partials' loads go out with the control block's
+  int tile0 = 0, tile_end = n_tiles;
+  if (gridDim.x > 1) {
+    tile0 = fix[blockIdx.x].rt0;
+    tile_end = tile0 + fix[blockIdx.x].nrt;
+    if (mode == MODE_DONE) return;
+  }
   double v[8] = {0.0, INFINITY, 0.0, 0.0, -INFINITY, 0.0, 0.0, 0.0};
   const size_t nt = size_t(n_tiles);
 #pragma unroll 1
@@ -932,13 +959,14 @@ __global__ __launch_bounds__(kRedBlock) void k_dmg_red(Ctl* ctl, const double* p
       v[PT_CH] += in ? q[j][PT_CH] : 0.0;
     }
   }
+  if (mode == MODE_DONE) return;
   const double vk = block_reduce_rows<8, kPartOps, kRedBlock / 64>(v, red);
   if (threadIdx.x < 8) tot[threadIdx.x] = vk;
   __syncthreads();
   if (threadIdx.x != 0) return;
 #pragma unroll
   for (int k = 0; k < 8; ++k) v[k] = tot[k];
-  advance_solver(&cc, v, bnd, kind, tol, max_iter);
+  advance_solver(&cc, nnodes, v, bnd, kind, tol, max_iter);
   *cp = cc;
 }
 
@@ -951,8 +979,10 @@ __global__ __launch_bounds__(kRedBlock) void k_dmg_red(Ctl* ctl, const double* p
 // the stores have completed; the last workgroup reads them past its L2.  The
 // fixed combination order is that of k_dmg_red, so the bits are the same.
 template <typename T>
-__device__ __forceinline__ void arrive_and_advance(const DmgArgs<T>& a, Ctl* c, int tile, int tile0, int ntiles,
-                                                   int n_tiles, int bnd, double* red) {
+__device__ __forceinline__ void arrive_and_advance(const DmgArgs<T>& a, int inst, int tile, int bnd, double* red) {
+  const InstFix* const c = a.fix + inst;
+  const int tile0 = c->rt0, ntiles = c->nrt, nnodes = c->nnodes;
+  const unsigned ngroup = unsigned((ntiles + kArriveGroup - 1) / kArriveGroup);
   __shared__ int s_last;
   __shared__ double s_tot[8];
   const int tid = threadIdx.x;
@@ -967,24 +997,25 @@ __device__ __forceinline__ void arrive_and_advance(const DmgArgs<T>& a, Ctl* c, 
       bool last = false;
       if (__hip_atomic_fetch_add(gc, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gsize - 1) {
         __hip_atomic_store(gc, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        last = __hip_atomic_fetch_add(top, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
-               unsigned((ntiles + kArriveGroup - 1) / kArriveGroup) - 1;
+        last = ngroup == 1 || __hip_atomic_fetch_add(top, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == ngroup - 1;
       }
       s_last = last;
     }
   }
   __syncthreads();
   if (!s_last) return;
-  const double vk = combine_partials(a.part, size_t(n_tiles), tile0, ntiles, red);
+  Ctl* const cp = a.ctl + inst;
+  Ctl cc;
+  if (tid == 0) cc = *cp;   // loaded beside the partials
+  const double vk = combine_partials(a.part, size_t(a.dr.n_tiles), tile0, ntiles, red);
   if (tid < 8) s_tot[tid] = vk;
   __syncthreads();
   if (tid != 0) return;
-  Ctl cc = *c;
   double v[8];
 #pragma unroll
   for (int k = 0; k < 8; ++k) v[k] = s_tot[k];
-  advance_solver(&cc, v, bnd, a.kind, a.tol, a.max_iter);
-  if (a.fuse == 1) *c = cc;
+  advance_solver(&cc, nnodes, v, bnd, a.kind, a.tol, a.max_iter);
+  if (a.fuse == 1) *cp = cc;
   __hip_atomic_store(top, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
@@ -1028,7 +1059,7 @@ __global__ __launch_bounds__(kBlock) void k_dmg_final(DmgArgs<T> a, uint8_t* act
       if (active_out) active_out[g] = act;
     }
   }
-  if (stats && threadIdx.x == 0 && tile == c->tile0) {
+  if (stats && threadIdx.x == 0 && tile == a.fix[t.inst].tile0) {
     pf_cg_stats_t s;
     s.iters = c->iters;
     s.restarts = c->restarts;
@@ -1049,6 +1080,7 @@ static DmgArgs<T> dmg_args(pf_mesh_s* m, int kind, const void* H, const void* d_
   a.dr = m->dr;
   a.ip = static_cast<const InstP<T>*>(m->dw.instp);
   a.ctl = m->dw.ctl;
+  a.fix = m->dw.fix;
   a.part = m->dw.part;
   a.H = static_cast<const T*>(H);
   a.lb = static_cast<const T*>(d_prev);
@@ -1162,7 +1194,7 @@ static pf_status_t run_solve(pf_mesh_s* m, int kind, const void* H, const void* 
     timer_end(m, 1, s);
     if (!a.fuse) {
       timer_begin(m, 4, s);
-      hipLaunchKernelGGL(k_dmg_red, igrid, dim3(kRedBlock), 0, s, m->dw.ctl, m->dw.part,
+      hipLaunchKernelGGL(k_dmg_red, igrid, dim3(kRedBlock), 0, s, m->dw.ctl, m->dw.fix, m->dw.part,
                          m->dr.n_tiles, m->dw.bounds, kind, o->tol, o->max_iter);
       timer_end(m, 4, s);
     }

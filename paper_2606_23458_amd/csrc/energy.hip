@@ -85,10 +85,10 @@ __global__ __launch_bounds__(kBlock) void k_energy(DevMesh dm, const InstP<T>* _
 }
 
 // One workgroup per instance: fixed-order sums of the tiles' partials.
-__global__ __launch_bounds__(kBlock) void k_energy_reduce(const Ctl* ctl, const double* part, int n_tiles,
+__global__ __launch_bounds__(kBlock) void k_energy_reduce(const InstFix* fix, const double* part, int n_tiles,
                                                           double* out) {
   __shared__ double red[3 * 4 * kWaves];
-  const Ctl* c = ctl + blockIdx.x;
+  const InstFix* c = fix + blockIdx.x;
   double v[3] = {0.0, 0.0, 0.0};
   for (int k = c->tile0 + threadIdx.x; k < c->tile0 + c->ntiles; k += kBlock) {
 #pragma unroll
@@ -151,7 +151,7 @@ static pf_status_t energies_t(pf_mesh_s* m, int split, const pf_state_t* s, doub
       hipLaunchKernelGGL((k_energy<T, SPLIT_STAR>), grid, block, lds, st, m->dm, ip, si, part);
       break;
   }
-  hipLaunchKernelGGL(k_energy_reduce, dim3(m->n_inst), block, 0, st, m->dw.ctl, part, m->n_tiles, out);
+  hipLaunchKernelGGL(k_energy_reduce, dim3(m->n_inst), block, 0, st, m->dw.fix, part, m->n_tiles, out);
   PF_HIP(hipGetLastError());
   return PF_OK;
 }

@@ -673,7 +673,7 @@ extern "C" pf_status_t pf_mesh_create(const pf_mesh_desc_t* inst, int32_t n_inst
   // rows and LDS values of the largest row tile by degree (an instance whose
   // tiles hold fewer rings runs with its own largest degree)
   for (const RowTile& t : rows.tiles)
-    for (int dg = 0; dg <= kMaxRing; ++dg) {
+    for (int dg = 0; dg <= kAskRing; ++dg) {
       const int de = dg == 0 ? rows.ddef[t.inst] : std::min(dg, rows.dmax[t.inst]);
       m->max_rows[dg] = std::max(m->max_rows[dg], t.nl[de - 1]);
       // the vector of a pass, twice for a polynomial, or the FP64 iterate of a restart
@@ -740,19 +740,21 @@ extern "C" pf_status_t pf_mesh_create(const pf_mesh_desc_t* inst, int32_t n_inst
   }
   // tile counts per instance into the control blocks, and the arrival counters
   {
-    std::vector<Ctl> c(n_instances);
-    std::memset(c.data(), 0, sizeof(Ctl) * n_instances);
+    std::vector<Ctl> ctl(n_instances);
+    std::vector<InstFix> c(n_instances);
+    std::memset(ctl.data(), 0, sizeof(Ctl) * n_instances);
+    std::memset(c.data(), 0, sizeof(InstFix) * n_instances);
     int32_t ncnt = 0;
     for (int k = 0; k < n_instances; ++k) {
+      ctl[k].mode = MODE_DONE;
       c[k].ntiles = m->info[k].n_tiles;
       c[k].tile0 = m->info[k].tile_offset;
       c[k].nnodes = m->info[k].n_nodes;
-      c[k].mode = MODE_DONE;
       c[k].nrt = rows.nrt[k];
       c[k].rt0 = rows.rt0[k];
       c[k].dmax = rows.dmax[k];
       c[k].ddef = rows.ddef[k];
-      c[k].lmax = lmax[k];
+      chebyshev_steps(c[k], lmax[k]);
       m->max_inst_tiles = std::max(m->max_inst_tiles, c[k].ntiles);
       c[k].cbase = ncnt;
       c[k].ctop = ncnt + (c[k].nrt + kArriveGroup - 1) / kArriveGroup;
@@ -763,7 +765,10 @@ extern "C" pf_status_t pf_mesh_create(const pf_mesh_desc_t* inst, int32_t n_inst
     m->dw.arrive = static_cast<uint32_t*>(tmpp);
     hipError_t ez = hipMemset(m->dw.arrive, 0, cbytes);
     if (ez != hipSuccess) { free_all(m); delete m; return hip_fail(ez, "hipMemset"); }
-    hipError_t e = hipMemcpy(m->dw.ctl, c.data(), sizeof(Ctl) * n_instances, hipMemcpyHostToDevice);
+    void* p_fix;
+    if ((st = dev_upload(m, c, &p_fix)) != PF_OK) { free_all(m); delete m; return st; }
+    m->dw.fix = static_cast<const InstFix*>(p_fix);
+    hipError_t e = hipMemcpy(m->dw.ctl, ctl.data(), sizeof(Ctl) * n_instances, hipMemcpyHostToDevice);
     if (e != hipSuccess) { free_all(m); delete m; return hip_fail(e, "hipMemcpy"); }
   }
   // LDS needs of the explicit step: 3 node values + 6 corner values

@@ -40,7 +40,8 @@ struct TileRec {
 // RowPlan) and the rings of nodes around them.  Local node ids run over the
 // owned nodes, then ring 1 (their neighbours), ring 2, ...; nl[k] counts the
 // nodes up to ring k.
-constexpr int kMaxRing = 4;          // rings a tile may keep (the largest polynomial degree)
+constexpr int kMaxRing = 8;          // rings a tile may keep (the largest polynomial degree)
+constexpr int kAskRing = 4;          // rings kept where they fit (the largest degree a caller may ask for)
 constexpr int kRowMax = 2048;        // rows (owned and ring nodes) that one workgroup can take
 constexpr int kRowPairs = 3;         // base entry pairs per row (6 neighbours); longer rows use extra pairs
 struct RowTile {
@@ -86,6 +87,23 @@ struct LoadDev {
   const LoadP* par;        // [n_inst]
 };
 
+// What the damage passes need to know of one instance, written once by
+// pf_mesh_create.
+struct InstFix {
+  int32_t ntiles;     // tiles of this instance
+  int32_t tile0;      // first tile of this instance
+  int32_t nnodes;     // nodes of this instance
+  int32_t cbase;      // first arrival counter of this instance (the counters of 32-tile groups)
+  int32_t ctop;       // arrival counter of the groups
+  int32_t nrt;        // row tiles of this instance
+  int32_t rt0;        // first row tile of this instance
+  int32_t dmax;       // largest polynomial degree its row tiles hold rings for
+  int32_t ddef;       // polynomial degree of the default preconditioner
+  // steps of the Chebyshev iteration (see damage.hip): 1/theta, and
+  // d_j = ch1 d_{j-1} + ch2 D^-1 res of step j
+  double ith, ch1[kMaxRing - 1], ch2[kMaxRing - 1];
+};
+
 // CG control block of one instance, in device memory.  Fields are read by
 // every block at kernel start and written only by the instance's last block.
 struct Ctl {
@@ -95,23 +113,12 @@ struct Ctl {
   int32_t hit;        // the current step is cut by a bound
   int32_t iters, restarts, flags, nact;
   int32_t pbuf;       // which half of the vector pairs (x, r, A z, A p) is current
-  int32_t ntiles;     // tiles of this instance
-  int32_t tile0;      // first tile of this instance
   int32_t flavor;     // 0 active-set updates between CG runs, 1 monotone projected CG (fallback)
-  int32_t nnodes;     // nodes of this instance
   int32_t inner;      // CG iterations since the last restart or check
   int32_t wbuf;       // which half of the held-set pair is current
   int32_t outer;      // active-set updates so far
-  int32_t cbase;      // first arrival counter of this instance (the counters of 32-tile groups)
-  int32_t ctop;       // arrival counter of the groups
-  int32_t nrt;        // row tiles of this instance
-  int32_t rt0;        // first row tile of this instance
-  int32_t dmax;       // largest polynomial degree its row tiles hold rings for
-  int32_t ddef;       // polynomial degree of the default preconditioner
   double rz, alpha, beta, amax, resid, pq;
   double ref;         // scale of the stopping test (1 for the damage QP, max |b_i|/A_ii for linear solves)
-  double lmax;        // upper bound of the spectrum of D^-1 A (pf_mesh_create)
-  double ith, ch1[kMaxRing - 1], ch2[kMaxRing - 1];   // steps of the Chebyshev iteration (1/theta; d_j = ch1 d_{j-1} + ch2 D^-1 res)
 };
 
 enum { MODE_RESTART = 0, MODE_ITER = 1, MODE_DONE = 2, MODE_CHECK = 3, MODE_FIRST = 4 };
@@ -195,6 +202,7 @@ struct DevWork {
   uint32_t* arrive;                  // arrival counters of the damage passes, kArriveStride apart:
                                      // per instance one per 32-tile group, then one for the groups
   Ctl* ctl;                          // [n_inst]
+  const InstFix* fix;                // [n_inst]
   void* instp;                       // [n_inst] InstP<T>
   int* bounds;                       // [n_inst] pf_params_t.bounds of each instance
 };
@@ -232,9 +240,9 @@ struct pf_mesh_s {
   pf::DevMesh dm{};
   pf::DevWork dw{};
   pf::DevRows dr{};
-  int32_t max_rows[pf::kMaxRing + 1] = {};   // rows of the largest row tile for each polynomial degree (0: the default)
-  int32_t max_rlds[pf::kMaxRing + 1] = {};   // and the values it keeps in LDS
-  int32_t max_slds[2][pf::kMaxRing + 1] = {};// and in the set-up pass with its elements in one and in two chunks
+  int32_t max_rows[pf::kAskRing + 1] = {};   // rows of the largest row tile for each polynomial degree (0: the default)
+  int32_t max_rlds[pf::kAskRing + 1] = {};   // and the values it keeps in LDS
+  int32_t max_slds[2][pf::kAskRing + 1] = {};// and in the set-up pass with its elements in one and in two chunks
   std::vector<void*> allocs;         // every device allocation, freed at destroy
   size_t device_bytes = 0;
   // host mirror of the current per-instance parameters (bytes of InstP<T>[n_inst])
@@ -320,6 +328,8 @@ pf_status_t check_state(const pf_state_t* s, bool need_d, bool need_H, const cha
 pf_status_t energy_scratch_setup(int device);
 // The stiffness part of the rows, from the mesh and the toughness field (damage.hip).
 void rows_stiffness(pf_mesh_s* m, hipStream_t s);
+// The Chebyshev iteration's steps for spectra in (0, lmax] (damage.hip).
+void chebyshev_steps(InstFix& f, double lmax);
 // Choose the element chunks of the damage set-up pass for this handle (damage.hip).
 void damage_plan(pf_mesh_s* m);
 bool states_share(const pf_state_t* a, const pf_state_t* b);

@@ -14,13 +14,43 @@ namespace pf {
 
 namespace {
 
-// Owned nodes per row tile.  Per instance, so that a batched handle gives
-// each instance the tiles, and the bits, of a handle of its own.
-size_t row_tile_nodes(size_t n, size_t tile_nodes) {
-  return std::min<size_t>(704, std::max<size_t>(std::min<size_t>(256, tile_nodes), (n + 767) / 768));
+// Owned nodes per row tile and the default preconditioner's degree, per
+// instance and from the instance alone, so that a batched handle gives each
+// instance the tiles, and the bits, of a handle of its own.
+//
+// A pass of degree k costs k + 1 products on a tile and its shrinking rings,
+// and one crossing of the chip for the reductions.  With few tiles per XCD the
+// crossing and the memory's latency are most of it, so a high degree and small
+// tiles (few serial rows per thread) win although half of a tile's rows are
+// then rings; on more nodes the rings' rows cost time of their own, so the
+// tiles grow.  Measured as degree / owned nodes, us per step of two plates of
+// each size:
+//   FP64    64x32  8/128 233, 223   6/256 263, 238   (3/256 353)
+//          397x211 8/128 311, 433   6/256 320, 471   4/256 378, 542
+//          512x256 8/128 641, 596   6/256 587, 628   5/512 649, 871
+//         1024x512 8/256 844, 956   6/384 789, 938   5/512 817, 973   (3/685 955, 1374)
+//   FP32   256x128 6/128 167, 225   6/256 175, 234   4/384 213, 258
+//          512x256 8/256 275, 283   6/256 257, 252   4/384 275, 268
+//         1024x512 6/384 378, 361   5/512 387, 361   3/685 409, 353
+//         1448x724 6/384 618, 605   5/512 593, 558   3/685 623, 535
+// A batch of 16 plates in FP32 takes 630 at 6/256 and 657 with 128 owned nodes
+// on its smaller plates, so these take 256 as well.  FP32 rows of a million
+// nodes are bound by memory, which the larger tiles read least of (a
+// perforated plate of that size: 508 at 5/512, 455 at 3/685).
+//
+// Callers that ask for tiles of less than 128 nodes get them, and degree 2:
+// the rings of a higher one would outnumber their nodes.
+struct RowChoice {
+  size_t own;
+  int degree;
+};
+RowChoice row_choice(size_t n, size_t tile_nodes, size_t width) {
+  const bool dbl = width == 8;
+  if (tile_nodes < 128) return {tile_nodes, 2};
+  if (dbl && n <= 100000) return {128, 8};
+  if (dbl || n <= 768 * 1024) return {n <= 192 * 1024 ? 256u : 384u, 6};
+  return {704, 3};
 }
-// Degree of the default preconditioner.
-int default_degree(size_t own) { return own < 128 ? 2 : 3; }
 
 constexpr size_t kThreads = 8;
 // f(i, t) for i < n, t < kThreads the thread that runs it
@@ -145,7 +175,9 @@ bool row_plan_add(RowPlan& rp, const RowMesh& rm, int inst, size_t width, size_t
   const size_t static_lds = 2048;   // the passes' reduction scratch
   const size_t max1 = std::min<size_t>(65535, (lds_limit - static_lds) / 8);            // nodes, one FP64 vector in LDS
   const size_t max2 = std::min<size_t>(65535, (lds_limit - static_lds) / (2 * width));  // nodes, two vectors
-  const size_t own = row_tile_nodes(n, rm.tile_nodes);
+  const RowChoice choice = row_choice(n, rm.tile_nodes, width);
+  const size_t own = choice.own;
+  const int ddef = choice.degree, ask = std::max(kAskRing, ddef);
   std::vector<int32_t> dloc(n);
   std::vector<HostTile> tiles;
   Graph g;
@@ -181,7 +213,7 @@ bool row_plan_add(RowPlan& rp, const RowMesh& rm, int inst, size_t width, size_t
       // neighbour of ring k-1 lies in ring k-2, k-1 or k, so those are all to
       // look through
       std::vector<int32_t> prev2, prev, cur;
-      for (int k = 1; k <= kMaxRing; ++k) {
+      for (int k = 1; k <= ask; ++k) {
         cur.clear();
         auto grow = [&](int32_t u) {
           for (int64_t q = g.ptr[u]; q < g.ptr[u + 1]; ++q) {
@@ -234,7 +266,7 @@ bool row_plan_add(RowPlan& rp, const RowMesh& rm, int inst, size_t width, size_t
       for (int k = t.rings + 1; k <= kMaxRing; ++k) t.nl[k] = t.nl[t.rings];
       for (int32_t e : t.elems) mark[size_t(e)] = -1;
     });
-    dmax = kMaxRing;
+    dmax = ask;
     for (const HostTile& t : tiles) dmax = std::min(dmax, int(t.rings));
   }
   if (dmax < 1) return false;
@@ -335,7 +367,7 @@ bool row_plan_add(RowPlan& rp, const RowMesh& rm, int inst, size_t width, size_t
   rp.rt0.push_back(int32_t(tile0));
   rp.nrt.push_back(int32_t(tiles.size()));
   rp.dmax.push_back(dmax);
-  rp.ddef.push_back(std::min(dmax, default_degree(own)));
+  rp.ddef.push_back(std::min(dmax, ddef));
   return true;
 }
 

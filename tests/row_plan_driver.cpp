@@ -30,10 +30,10 @@ struct Case {
 };
 
 int main() {
-  const Case cases[] = {{"grid", 64, 32, 0, false, false, 256, 4},       {"diagonals", 397, 211, 0, true, false, 256, 4},
-                        {"cell", 1, 1, 0, false, false, 256, 4},         {"strip", 3000, 1, 0, true, false, 256, 4},
-                        {"fan12", 0, 0, 12, false, true, 256, 4},        {"fan3000", 0, 0, 3000, false, true, 256, 1},
-                        {"small tiles", 120, 60, 0, true, false, 64, 4}, {"large", 700, 400, 0, false, false, 512, 4}};
+  const Case cases[] = {{"grid", 64, 32, 0, false, false, 256, 8},       {"diagonals", 397, 211, 0, true, false, 256, 8},
+                        {"cell", 1, 1, 0, false, false, 256, 8},         {"strip", 3000, 1, 0, true, false, 256, 8},
+                        {"fan12", 0, 0, 12, false, true, 256, 8},        {"fan3000", 0, 0, 3000, false, true, 256, 1},
+                        {"small tiles", 120, 60, 0, true, false, 64, 4}, {"large", 700, 400, 0, false, false, 512, 6}};
   std::mt19937 r(1);
   RowPlan rp;
   int off = 0, eoff = 0, teoff = 0, inst = 0;
