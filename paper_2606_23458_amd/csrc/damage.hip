@@ -289,7 +289,7 @@ void rows_stiffness(pf_mesh_s* m, hipStream_t s) {
 // or (nch = 2) one after the other in half the space; no value depends on that.
 // Sums in FP64, rounded once.  Bound by the bytes of the rows (S and the codes
 // read, A written).
-template <typename T, int RPT, bool FUSE>
+template <typename T, int RPT, int OWN, bool FUSE>
 __global__ __launch_bounds__(kBlock) void k_cg_setup(DmgArgs<T> a) {
   __shared__ double red[8 * 4 * kWaves];
   const int tile = tile_of_block(a.dr.n_tiles);
@@ -353,7 +353,7 @@ __global__ __launch_bounds__(kBlock) void k_cg_setup(DmgArgs<T> a) {
     qi[k] = bs[k] = rs[k] = off[k] = 0.0;
     if ((wv + k * kWaves) * 64 >= nrow) continue;
     const int i = tid + k * kBlock;
-    const bool own = i < n_own;
+    const bool own = k < OWN && i < n_own;
     const double xi = own ? double(ya[i]) : 0.0;
     const int sl = slice0 + wv + k * kWaves;
     const int2 x = a.dr.xs[sl];
@@ -403,7 +403,7 @@ __global__ __launch_bounds__(kBlock) void k_cg_setup(DmgArgs<T> a) {
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < RPT; ++k) {
-      if (tid + k * kBlock >= n_own) continue;
+      if (k >= OWN || tid + k * kBlock >= n_own) continue;
       const int sl = slice0 + wv + k * kWaves;
       const int2 x = a.dr.xs[sl];
       auto add = [&](uint2 cd) {
@@ -421,7 +421,7 @@ __global__ __launch_bounds__(kBlock) void k_cg_setup(DmgArgs<T> a) {
 #pragma unroll
   for (int k = 0; k < RPT; ++k) {
     const int i = tid + k * kBlock;
-    if (i >= n_own) continue;
+    if (k >= OWN || i >= n_own) continue;
     const int q0 = node0 + i;
     const int g = a.dr.node[q0];
     const T xv = ya[i];
@@ -461,12 +461,18 @@ __global__ __launch_bounds__(kBlock) void k_cg_setup(DmgArgs<T> a) {
 }
 
 // One pass of a solve over the row tiles, after the set-up.  RPT: rows (owned and
-// ring nodes) per thread.  The rows' entries and column ids sit in registers for the whole
-// pass (a row is multiplied deg times), the vector being multiplied in LDS.
+// ring nodes) per thread, OWN: of which owned nodes (256 owned nodes per tile:
+// 1, which frees the registers and loads of the other rows' iterate, direction
+// and bound).  The rows' entries and column ids sit in registers for the whole
+// pass (a row is multiplied deg times), the vector being multiplied in LDS;
+// PAIRS = 4: the first extra pair of a longer row as well (with random
+// diagonals nearly every slice has one, and each product would load it again).
+// Measured, us per step: FP64 1024x512 plate 764 -> 742 (OWN = 1), with random
+// diagonals 914 -> 855 (both); FP32 397x211 with random diagonals 258 -> 238 (PAIRS = 4).
 // With up to two rows per thread (small plates, bound by latency) the rows are
 // loaded with the vectors; with more (large plates, bound by bytes) after the
 // vectors' update, whose registers they then share.
-template <typename T, int RPT, bool FUSE>
+template <typename T, int RPT, int OWN, int PAIRS, bool FUSE>
 __global__ __launch_bounds__(kBlock, RPT <= 4 ? (RPT <= 2 ? 4 : 3) : 1) void k_cg(DmgArgs<T> a) {
   __shared__ double red[8 * 4 * kWaves];
   const int tile = tile_of_block(a.dr.n_tiles);
@@ -516,8 +522,8 @@ __global__ __launch_bounds__(kBlock, RPT <= 4 ? (RPT <= 2 ? 4 : 3) : 1) void k_c
   const int steps_nl = tp->nl[min(lane, kMaxRing)];
 
   // ---- the rows of this thread --------------------------------------------------
-  Two<T> av[RPT][kRowPairs];
-  uint32_t ac[RPT][kRowPairs];
+  Two<T> av[RPT][PAIRS];
+  uint32_t ac[RPT][PAIRS];
   int xb[RPT], xk[RPT];
   T rsu[RPT];
   Two<T>* const AV = static_cast<Two<T>*>(a.dr.av);
@@ -534,7 +540,12 @@ __global__ __launch_bounds__(kBlock, RPT <= 4 ? (RPT <= 2 ? 4 : 3) : 1) void k_c
         ac[k][q] = a.dr.ac[at + q * 64];
         av[k][q] = AV[at + q * 64];
       }
-      rsu[k] = a.rsum[node0 + min(tid + k * kBlock, n_own - 1)];
+      if constexpr (PAIRS > kRowPairs) {
+        const size_t xo = size_t(xk[k] > 0 ? xb[k] : 0) * 64 + lane;   // a slice without extra pairs loads one it does not use
+        ac[k][kRowPairs] = a.dr.xac[xo];
+        av[k][kRowPairs] = XAV[xo];
+      }
+      if (k < OWN) rsu[k] = a.rsum[node0 + min(tid + k * kBlock, n_own - 1)];
     }
   };
   // sum over row k of entry times f(value at the column)
@@ -545,7 +556,11 @@ __global__ __launch_bounds__(kBlock, RPT <= 4 ? (RPT <= 2 ? 4 : 3) : 1) void k_c
       s += f(av[k][q].x, y[ac[k][q] & 0xffffu]);
       s += f(av[k][q].y, y[ac[k][q] >> 16]);
     }
-    for (int e = 0; e < xk[k]; ++e) {
+    if (PAIRS > kRowPairs && xk[k] > 0) {
+      s += f(av[k][PAIRS - 1].x, y[ac[k][PAIRS - 1] & 0xffffu]);
+      s += f(av[k][PAIRS - 1].y, y[ac[k][PAIRS - 1] >> 16]);
+    }
+    for (int e = PAIRS - kRowPairs; e < xk[k]; ++e) {
       const size_t xo = (size_t(xb[k]) + e) * 64 + lane;
       const Two<T> v = XAV[xo];
       const uint32_t cc = a.dr.xac[xo];
@@ -605,7 +620,7 @@ __global__ __launch_bounds__(kBlock, RPT <= 4 ? (RPT <= 2 ? 4 : 3) : 1) void k_c
 #pragma unroll
     for (int k = 0; k < RPT; ++k) {
       const int i = tid + k * kBlock;
-      if (i >= n_own) continue;
+      if (k >= OWN || i >= n_own) continue;
       const int g = node0 + i;
       const double xi = xs[i];
       double xv = xi;
@@ -650,7 +665,7 @@ __global__ __launch_bounds__(kBlock, RPT <= 4 ? (RPT <= 2 ? 4 : 3) : 1) void k_c
       // tiles of an AT1 plate are such tiles.
       bool free_node = monotone;
 #pragma unroll
-      for (int k = 0; k < RPT; ++k) free_node = free_node || (tid + k * kBlock < n_own && !(dmv[k] < T(0)));
+      for (int k = 0; k < RPT; ++k) free_node = free_node || (k < OWN && tid + k * kBlock < n_own && !(dmv[k] < T(0)));
       const bool idle = !__syncthreads_or(free_node);
       if (tid == 0) a.dr.idle[tile] = idle;
       if (idle) {
@@ -669,8 +684,9 @@ __global__ __launch_bounds__(kBlock, RPT <= 4 ? (RPT <= 2 ? 4 : 3) : 1) void k_c
     for (int k = 0; k < RPT; ++k) {
       rsv[k] = rsc[pos[k]];
       if (iter) {
-        const int po = node0 + min(tid + k * kBlock, n_own - 1);
         wzv[k] = wzc[pos[k]];
+        if (k >= OWN) continue;
+        const int po = node0 + min(tid + k * kBlock, n_own - 1);
         pv_[k] = a.p[po];
         xv_[k] = xc[po];
         lbv_[k] = projected ? a.lbr[po] : T(0);
@@ -685,7 +701,7 @@ __global__ __launch_bounds__(kBlock, RPT <= 4 ? (RPT <= 2 ? 4 : 3) : 1) void k_c
       if (iter) {
         const T sn = (beta == 0.0) ? wzv[k].x : wzv[k].x + be * rsv[k].y;   // s = A p of this iteration
         rn = rn - al * sn;
-        if (i < n_own) {
+        if (k < OWN && i < n_own) {
           const int g = node0 + i;
           const T pv = (beta == 0.0) ? wzv[k].y : wzv[k].y + be * pv_[k];
           const double xv = xv_[k], lbd = double(lbv_[k]);
@@ -703,7 +719,7 @@ __global__ __launch_bounds__(kBlock, RPT <= 4 ? (RPT <= 2 ? 4 : 3) : 1) void k_c
           rsn[g] = Two<T>{rn, sn};
         }
       }
-      if (held && monotone && i < n_own) {
+      if (held && monotone && k < OWN && i < n_own) {
         const double sr = double(rn) * double(-dmv[k]);
         const uint8_t w = (c->wbuf ? a.W1 : a.W0)[node0 + i];
         if (w != HELD_FIXED) nc.ca = fmax(nc.ca, w == HELD_UPPER ? -sr : sr);
@@ -751,7 +767,7 @@ __global__ __launch_bounds__(kBlock, RPT <= 4 ? (RPT <= 2 ? 4 : 3) : 1) void k_c
 #pragma unroll
     for (int k = 0; k < RPT; ++k) {
       const int i = tid + k * kBlock;
-      if (i >= n_own) continue;
+      if (k >= OWN || i >= n_own) continue;
       const T zv = y_[k];
       const T s = rsu[k] * zv + row_sum(k, ys, T(0), [&](T e, T y) { return e * (y - zv); });
       wzn[node0 + i] = Two<T>{s, zv};
@@ -1115,18 +1131,31 @@ static DmgArgs<T> dmg_args(pf_mesh_s* m, int kind, const void* H, const void* d_
   return a;
 }
 
-// The CG pass for up to 256 rpt rows per row tile.
-template <typename T, bool FUSE>
-static void (*cg_kernel(int rows, bool setup))(DmgArgs<T>) {
-  const int rpt = (rows + kBlock - 1) / kBlock;
-  if (setup)
-    return rpt <= 1 ? k_cg_setup<T, 1, FUSE>
-                    : (rpt <= 2 ? k_cg_setup<T, 2, FUSE>
-                                : (rpt <= 3 ? k_cg_setup<T, 3, FUSE>
-                                            : (rpt <= 4 ? k_cg_setup<T, 4, FUSE> : k_cg_setup<T, 8, FUSE>)));
-  return rpt <= 1 ? k_cg<T, 1, FUSE>
-                  : (rpt <= 2 ? k_cg<T, 2, FUSE>
-                              : (rpt <= 3 ? k_cg<T, 3, FUSE> : (rpt <= 4 ? k_cg<T, 4, FUSE> : k_cg<T, 8, FUSE>)));
+// The CG pass for row tiles of up to 256 rpt rows, of which the first 256 own
+// hold the owned nodes.
+template <typename T>
+using CgKernel = void (*)(DmgArgs<T>);
+template <typename T, int RPT, int OWN>
+static CgKernel<T> cg_kernel_of(const pf_mesh_s* m, bool fuse, bool setup) {
+  if (setup) return fuse ? k_cg_setup<T, RPT, OWN, true> : k_cg_setup<T, RPT, OWN, false>;
+  // the first extra pair in registers too, where there are any and the registers suffice
+  if constexpr (RPT <= (sizeof(T) == 4 ? 4 : 3)) {
+    constexpr int X = kRowPairs + 1;
+    if (m->extra_pairs) return fuse ? k_cg<T, RPT, OWN, X, true> : k_cg<T, RPT, OWN, X, false>;
+  }
+  return fuse ? k_cg<T, RPT, OWN, kRowPairs, true> : k_cg<T, RPT, OWN, kRowPairs, false>;
+}
+template <typename T>
+static CgKernel<T> cg_kernel(const pf_mesh_s* m, int deg, bool setup) {
+  const bool fuse = m->max_inst_tiles <= kFuseMaxTiles;
+  const int rpt = (m->max_rows[deg] + kBlock - 1) / kBlock;
+  if (rpt > 4) return cg_kernel_of<T, 8, 8>(m, fuse, setup);
+  if (m->max_row_own <= kBlock) {
+    if (rpt <= 1) return cg_kernel_of<T, 1, 1>(m, fuse, setup);
+    if (rpt <= 2) return cg_kernel_of<T, 2, 1>(m, fuse, setup);
+    if (rpt <= 3) return cg_kernel_of<T, 3, 1>(m, fuse, setup);
+  }
+  return rpt <= 3 ? cg_kernel_of<T, 3, 3>(m, fuse, setup) : cg_kernel_of<T, 4, 4>(m, fuse, setup);
 }
 
 // LDS of a pass: the vector being multiplied, twice for a polynomial; nch > 0:
@@ -1138,10 +1167,8 @@ static size_t cg_lds(const pf_mesh_s* m, int deg, int nch) {
 
 template <typename T>
 static void launch_cg(const pf_mesh_s* m, DmgArgs<T> a, int nch, hipStream_t s) {
-  const int rows = m->max_rows[a.deg];
   a.nch = nch;
-  hipLaunchKernelGGL((a.fuse ? cg_kernel<T, true>(rows, nch > 0) : cg_kernel<T, false>(rows, nch > 0)),
-                     dim3(m->dr.n_tiles), dim3(kBlock), cg_lds<T>(m, a.deg, nch), s, a);
+  hipLaunchKernelGGL(cg_kernel<T>(m, a.deg, nch > 0), dim3(m->dr.n_tiles), dim3(kBlock), cg_lds<T>(m, a.deg, nch), s, a);
 }
 
 // Element chunks of the set-up pass: two (the elements' mass coefficients and
@@ -1153,7 +1180,7 @@ static int damage_chunks(pf_mesh_s* m) {
   int nch = m->damage_chunks;
   auto occ = [&](int n) {
     int o = 0;
-    const void* k = reinterpret_cast<const void*>(cg_kernel<T, false>(m->max_rows[0], true));
+    const void* k = reinterpret_cast<const void*>(cg_kernel<T>(m, 0, true));
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&o, k, kBlock, cg_lds<T>(m, 0, n)) != hipSuccess) o = 0;
     return o;
   };

@@ -672,7 +672,9 @@ extern "C" pf_status_t pf_mesh_create(const pf_mesh_desc_t* inst, int32_t n_inst
   m->dr.n_tiles = int32_t(rows.tiles.size());
   // rows and LDS values of the largest row tile by degree (an instance whose
   // tiles hold fewer rings runs with its own largest degree)
-  for (const RowTile& t : rows.tiles)
+  m->extra_pairs = !rows.xac.empty();
+  for (const RowTile& t : rows.tiles) {
+    m->max_row_own = std::max(m->max_row_own, t.nl[0]);
     for (int dg = 0; dg <= kAskRing; ++dg) {
       const int de = dg == 0 ? rows.ddef[t.inst] : std::min(dg, rows.dmax[t.inst]);
       m->max_rows[dg] = std::max(m->max_rows[dg], t.nl[de - 1]);
@@ -681,6 +683,7 @@ extern "C" pf_status_t pf_mesh_create(const pf_mesh_desc_t* inst, int32_t n_inst
       m->max_slds[0][dg] = std::max(m->max_slds[0][dg], t.nl[1] + 2 * t.nel[de - 1]);
       m->max_slds[1][dg] = std::max(m->max_slds[1][dg], t.nl[1] + t.nel[de - 1]);
     }
+  }
   m->dm.tiles = static_cast<const TileRec*>(p_tiles);
   m->dm.halo_idx = static_cast<const int32_t*>(p_halo);
   m->dm.lc0 = static_cast<const uint16_t*>(p_lc0);

@@ -22,21 +22,23 @@ namespace {
 // and one crossing of the chip for the reductions.  With few tiles per XCD the
 // crossing and the memory's latency are most of it, so a high degree and small
 // tiles (few serial rows per thread) win although half of a tile's rows are
-// then rings; on more nodes the rings' rows cost time of their own, so the
-// tiles grow.  Measured as degree / owned nodes, us per step of two plates of
+// then rings; on more nodes the rings' rows cost time of their own.  256 owned
+// nodes are one per thread: more of them need registers for a second node's
+// vectors.  Measured as degree / owned nodes, us per step of two plates of
 // each size:
-//   FP64    64x32  8/128 233, 223   6/256 263, 238   (3/256 353)
-//          397x211 8/128 311, 433   6/256 320, 471   4/256 378, 542
-//          512x256 8/128 641, 596   6/256 587, 628   5/512 649, 871
-//         1024x512 8/256 844, 956   6/384 789, 938   5/512 817, 973   (3/685 955, 1374)
-//   FP32   256x128 6/128 167, 225   6/256 175, 234   4/384 213, 258
-//          512x256 8/256 275, 283   6/256 257, 252   4/384 275, 268
-//         1024x512 6/384 378, 361   5/512 387, 361   3/685 409, 353
-//         1448x724 6/384 618, 605   5/512 593, 558   3/685 623, 535
-// A batch of 16 plates in FP32 takes 630 at 6/256 and 657 with 128 owned nodes
-// on its smaller plates, so these take 256 as well.  FP32 rows of a million
-// nodes are bound by memory, which the larger tiles read least of (a
-// perforated plate of that size: 508 at 5/512, 455 at 3/685).
+//   FP64    64x32  8/128 228, 212   6/160 248, 221
+//          397x211 8/128 302, 408   6/160 320, 434   6/256 320, 471
+//          512x256 8/192 573, 630   6/256 558, 593   5/256 558, 624   6/384 599, 670
+//         1024x512 8/192 937, 1042  6/256 752, 865   5/256 778, 889   6/384 779, 921
+//   FP32   256x128 8/128 164, 202   6/256 174, 223   4/256 199, 230
+//          512x256 8/128 317, 277   6/256 252, 238   4/256 264, 255   6/384 281, 270
+//         1024x512 8/128 445, 441   6/256 354, 342   4/256 390, 325   6/384 375, 363
+//         1448x724 6/256 545, 562   5/512 580, 553   3/685 614, 532
+// A batch of 16 plates of up to 512x256 in FP32 takes 599 at 6/256 and 660 with
+// 128 owned nodes on its smaller plates, so these take 256 as well.  On a
+// million nodes the set-up pass, which assembles every ring row once, is much
+// of a step with few free nodes, and larger tiles have the fewest (a
+// perforated plate of that size: 508 at 6/256, 458 at 3/685).
 //
 // Callers that ask for tiles of less than 128 nodes get them, and degree 2:
 // the rings of a higher one would outnumber their nodes.
@@ -48,7 +50,7 @@ RowChoice row_choice(size_t n, size_t tile_nodes, size_t width) {
   const bool dbl = width == 8;
   if (tile_nodes < 128) return {tile_nodes, 2};
   if (dbl && n <= 100000) return {128, 8};
-  if (dbl || n <= 768 * 1024) return {n <= 192 * 1024 ? 256u : 384u, 6};
+  if (dbl || n <= 768 * 1024) return {256, 6};
   return {704, 3};
 }
 

@@ -82,6 +82,19 @@ def test_long_rows_match_exact_qp(dtype, n, rings):
 
 
 @pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("diag", [False, True])
+def test_large_tiles_match_exact_qp(dtype, diag):
+    """Above 100 000 nodes FP64 takes tiles of 256 owned nodes and degree 6 too; with random
+    diagonals most slices hold one extra pair."""
+    p = w.small_plate(419, 239, jitter=0.15, seed=8, model=2, random_diag=diag)
+    H, lb = _load(p, 5)
+    got, st = _solve(p, dtype, 256, 0, H, lb)
+    ref = DamageQP(OSim(p).mesh, p.l0, 2).solve(H, p.Gc, lb)[0]
+    assert st["flags"] == 0, st
+    assert np.max(np.abs(got - ref)) < TOL[dtype], st
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
 @pytest.mark.parametrize("precond", [0, 1, 4])
 def test_mostly_held_plate_matches_exact_qp(dtype, precond):
     """AT1 above its threshold in one corner only: most row tiles own no free node and sit out
