@@ -260,8 +260,8 @@ __global__ __launch_bounds__(kBlock) void k_rows_stiffness(DevMesh dm, DevRows d
   const T* __restrict__ gcs = static_cast<const T*>(dm.gcs);
   auto part = [&](uint32_t cd) {
     if (cd == kNoCode) return 0.0;
-    const size_t te = dr.ete[tp->el0 + int(cd / 3u)];
-    return (gcs ? double(gcs[te]) : 1.0) * double(kw[size_t(cd % 3u) * size_t(dm.n_te) + te]);
+    const size_t te = dr.ete[tp->el0 + int(cd & kCodeElem) - 1];
+    return (gcs ? double(gcs[te]) : 1.0) * double(kw[size_t(cd >> kCodeEdge) * size_t(dm.n_te) + te]);
   };
   auto entry = [&](uint2 cd) {
     return Two<T>{T(part(cd.x & 0xffffu) + part(cd.x >> 16)), T(part(cd.y & 0xffffu) + part(cd.y >> 16))};
@@ -272,6 +272,9 @@ __global__ __launch_bounds__(kBlock) void k_rows_stiffness(DevMesh dm, DevRows d
   const int2 x0 = dr.xs[tp->slice0], x1 = dr.xs[tp->slice0 + tp->nslice - 1];   // the tile's extra pairs are one run
   for (int i = threadIdx.x; i < (x1.x + x1.y - x0.x) * 64; i += kBlock)
     static_cast<Two<T>*>(dr.xsv)[size_t(x0.x) * 64 + i] = entry(dr.xcode[size_t(x0.x) * 64 + i]);
+  const T* __restrict__ area = static_cast<const T*>(dm.geo) + 6 * size_t(dm.n_te);
+  for (int i = threadIdx.x; i < tp->nel[kMaxRing - 1]; i += kBlock)
+    static_cast<T*>(dr.earea)[tp->el0 + i] = area[dr.ete[tp->el0 + i]];
 }
 
 void rows_stiffness(pf_mesh_s* m, hipStream_t s) {
@@ -310,13 +313,41 @@ __global__ __launch_bounds__(kBlock) void k_cg_setup(DmgArgs<T> a) {
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   extern __shared__ __align__(16) unsigned char smem[];
   T* const ya = reinterpret_cast<T*>(smem);   // [nall] the start
-  T* const sm = ya + nall;                    // [nel] mass coefficients (nch = 2: then the loads)
-  T* const sb = a.nch == 2 ? sm : sm + nel;   // [nel] loads
+  // [1 + nel] mass coefficients (nch = 2: then the loads) of the elements, 0
+  // first for entries of fewer than two elements
+  T* const sm = ya + nall;
+  T* const sb = a.nch == 2 ? sm : sm + 1 + nel;   // [1 + nel] loads
+  // per-element toughness factor phi_e (Gc_e = Gc phi_e) scales every Gc
+  // term of the element's operator and load; absent, phi_e = 1 exactly
+  const T* __restrict__ gcs = static_cast<const T*>(a.dm.gcs);
+  const T* __restrict__ area = static_cast<const T*>(a.dr.earea) + el0;
+  const int32_t* __restrict__ egid = a.dr.egid + el0;
+  const uint32_t* __restrict__ ete = a.dr.ete + el0;
+  // f(l, area, phi, H) for the tile's elements l: the loads of kBatch elements
+  // per thread go out together, twice (ids and areas, then what the ids index)
+  constexpr int kBatch = 6;
+  auto elements = [&](auto f) {
+    for (int l0 = tid; l0 < nel; l0 += kBatch * kBlock) {
+      int32_t ge[kBatch];
+      T A[kBatch], He[kBatch], ph[kBatch];
+#pragma unroll
+      for (int j = 0; j < kBatch; ++j) {
+        const int l = min(l0 + j * kBlock, nel - 1);
+        ge[j] = egid[l], A[j] = area[l];
+        ph[j] = gcs ? gcs[ete[l]] : T(1);
+      }
+#pragma unroll
+      for (int j = 0; j < kBatch; ++j) He[j] = a.H[ge[j]];
+#pragma unroll
+      for (int j = 0; j < kBatch; ++j)
+        if (l0 + j * kBlock < nel) f(l0 + j * kBlock, A[j], ph[j], He[j]);
+    }
+  };
 
   // the start: d_prev (or its extrapolation in time), or 1 where the guess
   // holds the node at the upper bound; linear solves at the caller's x
   for (int i = tid; i < nall; i += kBlock) {
-    const int g = a.dr.node[i < n_own ? node0 + i : a.dr.halo[halo0 + i - n_own]];
+    const int g = i < n_own ? a.dr.node[node0 + i] : a.dr.hnode[halo0 + i - n_own];
     T v;
     if (!qp) {
       v = a.dout[g];
@@ -327,19 +358,12 @@ __global__ __launch_bounds__(kBlock) void k_cg_setup(DmgArgs<T> a) {
     }
     ya[i] = v;
   }
-  const T* __restrict__ area = static_cast<const T*>(a.dm.geo) + 6 * size_t(a.dm.n_te);
-  // per-element toughness factor phi_e (Gc_e = Gc phi_e) scales every Gc
-  // term of the element's operator and load; absent, phi_e = 1 exactly
-  const T* __restrict__ gcs = static_cast<const T*>(a.dm.gcs);
   const T c0 = P->c0, cH = P->cH, b0 = P->b0, bH = P->bH;
-  for (int l = tid; l < nel; l += kBlock) {
-    const size_t te = a.dr.ete[el0 + l];
-    const T He = a.H[a.dr.egid[el0 + l]];
-    const T A = area[te];
-    const T ph = gcs ? gcs[te] : T(1);
-    sm[l] = (c0 * ph + cH * He) * A * T(1.0 / 12.0);
-    if (a.nch != 2) sb[l] = (b0 * ph + bH * He) * A * T(1.0 / 3.0);
-  }
+  elements([&](int l, T A, T ph, T He) {
+    sm[1 + l] = (c0 * ph + cH * He) * A * T(1.0 / 12.0);
+    if (a.nch != 2) sb[1 + l] = (b0 * ph + bH * He) * A * T(1.0 / 3.0);
+  });
+  if (tid == 0) sm[0] = sb[0] = T(0);
   __syncthreads();
 
   const Two<T>* const SV = static_cast<const Two<T>*>(a.dr.sv);
@@ -359,16 +383,16 @@ __global__ __launch_bounds__(kBlock) void k_cg_setup(DmgArgs<T> a) {
     const int2 x = a.dr.xs[sl];
     // one pair of entries; its first elements are those it stands for
     auto pair = [&](Two<T> sv, uint2 cd, uint32_t cc, Two<T>& out) {
-      auto mass = [&](uint32_t e) { return e == kNoCode ? 0.0 : double(sm[e / 3u]); };
-      const double m0 = mass(cd.x & 0xffffu), m1 = mass(cd.y & 0xffffu);
+      auto mass = [&](uint32_t e) { return double(sm[e & kCodeElem]); };
+      const double m0 = mass(cd.x), m1 = mass(cd.y);
       out.x = T(kap * double(sv.x) + (m0 + mass(cd.x >> 16)));
       out.y = T(kap * double(sv.y) + (m1 + mass(cd.y >> 16)));
       if (!own) return;
       rs[k] += m0;
       rs[k] += m1;
       if (a.nch != 2) {
-        if ((cd.x & 0xffffu) != kNoCode) bs[k] += double(sb[(cd.x & 0xffffu) / 3u]);
-        if ((cd.y & 0xffffu) != kNoCode) bs[k] += double(sb[(cd.y & 0xffffu) / 3u]);
+        bs[k] += double(sb[cd.x & kCodeElem]);
+        bs[k] += double(sb[cd.y & kCodeElem]);
       }
       // from here on the entries as the passes read them
       qi[k] += double(out.x) * (double(ya[cc & 0xffffu]) - xi);
@@ -380,7 +404,7 @@ __global__ __launch_bounds__(kBlock) void k_cg_setup(DmgArgs<T> a) {
     uint2 cd[kRowPairs];
     uint32_t cc[kRowPairs];
 #pragma unroll
-    for (int q = 0; q < kRowPairs; ++q) sv[q] = SV[at + q * 64], cd[q] = a.dr.code[at + q * 64], cc[q] = a.dr.ac[at + q * 64];
+    for (int q = 0; q < kRowPairs; ++q) sv[q] = SV[at + q * 64], cd[q] = i < nrow ? a.dr.code[at + q * 64] : uint2{0, 0}, cc[q] = a.dr.ac[at + q * 64];
 #pragma unroll
     for (int q = 0; q < kRowPairs; ++q) {
       Two<T> v;
@@ -390,16 +414,13 @@ __global__ __launch_bounds__(kBlock) void k_cg_setup(DmgArgs<T> a) {
     for (int e = 0; e < x.y; ++e) {
       const size_t xo = (size_t(x.x) + e) * 64 + lane;
       Two<T> v;
-      pair(XSV[xo], a.dr.xcode[xo], own ? a.dr.xac[xo] : 0u, v);
+      pair(XSV[xo], i < nrow ? a.dr.xcode[xo] : uint2{0, 0}, own ? a.dr.xac[xo] : 0u, v);
       XAV[xo] = v;
     }
   }
   if (a.nch == 2) {
     __syncthreads();
-    for (int l = tid; l < nel; l += kBlock) {
-      const size_t te = a.dr.ete[el0 + l];
-      sb[l] = (b0 * (gcs ? gcs[te] : T(1)) + bH * a.H[a.dr.egid[el0 + l]]) * area[te] * T(1.0 / 3.0);
-    }
+    elements([&](int l, T A, T ph, T He) { sb[1 + l] = (b0 * ph + bH * He) * A * T(1.0 / 3.0); });
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < RPT; ++k) {
@@ -407,8 +428,8 @@ __global__ __launch_bounds__(kBlock) void k_cg_setup(DmgArgs<T> a) {
       const int sl = slice0 + wv + k * kWaves;
       const int2 x = a.dr.xs[sl];
       auto add = [&](uint2 cd) {
-        if ((cd.x & 0xffffu) != kNoCode) bs[k] += double(sb[(cd.x & 0xffffu) / 3u]);
-        if ((cd.y & 0xffffu) != kNoCode) bs[k] += double(sb[(cd.y & 0xffffu) / 3u]);
+        bs[k] += double(sb[cd.x & kCodeElem]);
+        bs[k] += double(sb[cd.y & kCodeElem]);
       };
 #pragma unroll
       for (int q = 0; q < kRowPairs; ++q) add(a.dr.code[size_t(sl) * (kRowPairs * 64) + q * 64 + lane]);

@@ -645,9 +645,14 @@ extern "C" pf_status_t pf_mesh_create(const pf_mesh_desc_t* inst, int32_t n_inst
   UP(tmp, p_wl);
   UP(fixed, p_fixed);
   void *p_rnode, *p_ete, *p_egid;
-  void *p_rt, *p_rhalo, *p_rpos, *p_ac, *p_code, *p_xs, *p_xac, *p_xcode;
+  void *p_rt, *p_rhalo, *p_hnode, *p_rpos, *p_ac, *p_code, *p_xs, *p_xac, *p_xcode;
   UP(rows.tiles, p_rt);
   UP(rows.halo, p_rhalo);
+  {
+    std::vector<int32_t> hnode(rows.halo.size());
+    for (size_t i = 0; i < hnode.size(); ++i) hnode[i] = rows.node[size_t(rows.halo[i])];
+    UP(hnode, p_hnode);
+  }
   UP(rows.pos, p_rpos);
   UP(rows.node, p_rnode);
   UP(rows.ete, p_ete);
@@ -660,6 +665,7 @@ extern "C" pf_status_t pf_mesh_create(const pf_mesh_desc_t* inst, int32_t n_inst
 #undef UP
   m->dr.tiles = static_cast<const RowTile*>(p_rt);
   m->dr.halo = static_cast<const int32_t*>(p_rhalo);
+  m->dr.hnode = static_cast<const int32_t*>(p_hnode);
   m->dr.pos = static_cast<const int32_t*>(p_rpos);
   m->dr.node = static_cast<const int32_t*>(p_rnode);
   m->dr.ete = static_cast<const uint32_t*>(p_ete);
@@ -680,8 +686,8 @@ extern "C" pf_status_t pf_mesh_create(const pf_mesh_desc_t* inst, int32_t n_inst
       m->max_rows[dg] = std::max(m->max_rows[dg], t.nl[de - 1]);
       // the vector of a pass, twice for a polynomial, or the FP64 iterate of a restart
       m->max_rlds[dg] = std::max({m->max_rlds[dg], (de > 1 ? 2 : 1) * t.nl[de], dtype == PF_F32 ? 2 * t.nl[1] : t.nl[1]});
-      m->max_slds[0][dg] = std::max(m->max_slds[0][dg], t.nl[1] + 2 * t.nel[de - 1]);
-      m->max_slds[1][dg] = std::max(m->max_slds[1][dg], t.nl[1] + t.nel[de - 1]);
+      m->max_slds[0][dg] = std::max(m->max_slds[0][dg], t.nl[1] + 2 * (1 + t.nel[de - 1]));
+      m->max_slds[1][dg] = std::max(m->max_slds[1][dg], t.nl[1] + 1 + t.nel[de - 1]);
     }
   }
   m->dm.tiles = static_cast<const TileRec*>(p_tiles);
@@ -712,6 +718,7 @@ extern "C" pf_status_t pf_mesh_create(const pf_mesh_desc_t* inst, int32_t n_inst
   void** vecs2[] = {&m->dw.rs0, &m->dw.rs1, &m->dw.wz0, &m->dw.wz1};
   for (void** v : vecs2)
     if ((st = dev_alloc(m, 2 * nb, v)) != PF_OK) { free_all(m); delete m; return st; }
+  if ((st = dev_alloc(m, rows.ete.size() * w, &m->dr.earea)) != PF_OK) { free_all(m); delete m; return st; }
   if ((st = dev_alloc(m, rows.ac.size() * 2 * w, &m->dr.sv)) != PF_OK) { free_all(m); delete m; return st; }
   if ((st = dev_alloc(m, rows.xac.size() * 2 * w, &m->dr.xsv)) != PF_OK) { free_all(m); delete m; return st; }
   if ((st = dev_alloc(m, rows.ac.size() * 2 * w, &m->dr.av)) != PF_OK) { free_all(m); delete m; return st; }

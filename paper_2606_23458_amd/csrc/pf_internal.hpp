@@ -159,8 +159,11 @@ struct DevMesh {
 // two element contributions: the element that this entry stands for at the
 // row's node (every element at the node has one such entry, and a row's
 // entries are in ascending order of them) and the other element at the pair,
-// each as 3 e + edge (edges 01, 02, 12 of the tile's element e) or kNoCode.
-constexpr uint32_t kNoCode = 0xffffu;
+// each as 1 + e with the edge in the top two bits (edges 01, 02, 12 of the
+// tile's element e) or kNoCode.
+constexpr uint32_t kNoCode = 0;
+constexpr uint32_t kCodeElem = 0x3fffu;
+constexpr int kCodeEdge = 14;
 struct DevRows {
   const RowTile* tiles;
   const int32_t* halo;          // [sum] row-order positions of the ring nodes
@@ -168,6 +171,8 @@ struct DevRows {
   const int32_t* node;          // [N] internal node of each row-order position
   const uint32_t* ete;          // [sum] tile element (owner's copy) of the tiles' elements
   const int32_t* egid;          // [sum] internal element id
+  void* earea;                  // [sum] element area (mesh dtype)
+  const int32_t* hnode;         // [sum] internal nodes of the ring nodes
   const uint32_t* ac;           // [slice][kRowPairs][64] local node ids of a pair's two columns (16 bits each)
   const uint2* code;            // [slice][kRowPairs][64] contributions of a pair's two entries (16 bits each)
   const int2* xs;               // [slice] first extra pair, number of extra pairs

@@ -252,7 +252,7 @@ bool row_plan_add(RowPlan& rp, const RowMesh& rm, int inst, size_t width, size_t
         const size_t total = size_t(t.nl[k - 1]) + cur.size();
         // rows are the nodes up to ring k-1; degree 1 keeps one vector in LDS;
         // the set-up pass the start and two values per element; codes have 16 bits
-        if (total > (k == 1 ? max1 : max2) || t.nl[k - 1] > kRowMax || 3 * t.elems.size() > 65535 ||
+        if (total > (k == 1 ? max1 : max2) || t.nl[k - 1] > kRowMax || t.elems.size() > kCodeElem - 1 ||
             size_t(k == 1 ? total : size_t(t.nl[1])) + 2 * t.elems.size() > max1) {
           for (size_t q = e0; q < t.elems.size(); ++q) mark[size_t(t.elems[q])] = -1;
           t.elems.resize(e0);
@@ -325,7 +325,7 @@ bool row_plan_add(RowPlan& rp, const RowMesh& rm, int inst, size_t width, size_t
       rp.egid[size_t(r.el0 + q)] = rm.elem_off + e;
       mark[size_t(e)] = q;
     }
-    auto code16 = [&](uint32_t c) { return c == kNone ? kNoCode : 3u * uint32_t(mark[c / 3u]) + c % 3u; };
+    auto code16 = [&](uint32_t c) { return c == kNone ? kNoCode : (1u + uint32_t(mark[c / 3u])) | (c % 3u) << kCodeEdge; };
     const int32_t nhalo = r.nl[dmax] - r.nl[0];
     // ring nodes by position, with their local ids
     std::vector<std::pair<int32_t, int32_t>> loc(static_cast<size_t>(nhalo));

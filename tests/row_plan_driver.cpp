@@ -114,7 +114,7 @@ int main() {
               const uint32_t cd = u ? cc >> 16 : cc & 0xffffu;
               if (cd == kNoCode) continue;
               CHECK(ring < dm);
-              const int e = int(cd / 3u);
+              const int e = int(cd & kCodeElem) - 1;
               CHECK(e < t.nel[std::min(ring, dm - 1)]);
               const int gid = rp.egid[t.el0 + e] - eoff;
               CHECK(gid >= 0 && gid < ne && int(rp.ete[t.el0 + e]) == te[gid]);
@@ -122,7 +122,7 @@ int main() {
                 CHECK(gid > last);
                 last = gid, ++stands;
               }
-              got[col].insert(3u * uint32_t(gid) + cd % 3u);
+              got[col].insert(3u * uint32_t(gid) + (cd >> kCodeEdge));
             }
           }
         };
