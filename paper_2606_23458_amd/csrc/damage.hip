@@ -230,22 +230,42 @@ __device__ __forceinline__ double lane_value(double v, int j) {
   return __longlong_as_double(static_cast<long long>((static_cast<unsigned long long>(hi) << 32) | lo));
 }
 
+template <int N>
+struct Int {
+  static constexpr int value = N;
+};
+
 // Partials of a pass, in PT_* order, stored value-major [8][n_tiles] so the
 // reduction reads them coalesced; thread k holds value k.  FUSE: stored
 // through to the device-coherent level for the combination in this launch's
 // last workgroup.
 template <typename T, bool FUSE>
 __device__ __forceinline__ void finish_pass(const DmgArgs<T>& a, int inst, double (&v)[8], int tile, int bnd,
-                                            double* red) {
+                                            double* red, bool cg_only = false) {
   const int n_tiles = a.dr.n_tiles;
-  const double tot = block_reduce_rows<8, kPartOps>(v, red);
+  double tot = 0.0;
+  uint32_t at = threadIdx.x;   // the value that thread k < 8 stores
+  if (cg_only) {
+    // the values of an iteration: the others are their operations' identities
+    constexpr uint32_t ops = ((kPartOps >> (2 * PT_CF)) & 3u) << 4;   // delta, gamma, cf, ch
+    double u[4] = {v[PT_DELTA], v[PT_GAMMA], v[PT_CF], v[PT_CH]};
+    tot = block_reduce_waves<4, ops>(u, red);
+    const int k = threadIdx.x;
+    if (k == 4) tot = INFINITY;
+    if (k == 5) tot = -INFINITY;
+    constexpr uint32_t slot = PT_DELTA | PT_GAMMA << 4 | PT_CF << 8 | PT_CH << 12 | PT_AMIN << 16 | PT_CA << 20 |
+                              PT_NA << 24 | uint32_t(PT_RB) << 28;
+    at = (slot >> (4 * (k & 7))) & 15u;
+  } else {
+    tot = block_reduce_waves<8, kPartOps>(v, red);
+  }
   if constexpr (FUSE) {
     if (threadIdx.x < 8)
-      __hip_atomic_store(&a.part[size_t(threadIdx.x) * n_tiles + tile], tot, __ATOMIC_RELAXED,
+      __hip_atomic_store(&a.part[size_t(at) * n_tiles + tile], tot, __ATOMIC_RELAXED,
                          __HIP_MEMORY_SCOPE_AGENT);
     arrive_and_advance(a, inst, tile, bnd, red);
   } else {
-    if (threadIdx.x < 8) a.part[size_t(threadIdx.x) * n_tiles + tile] = tot;
+    if (threadIdx.x < 8) a.part[size_t(at) * n_tiles + tile] = tot;
   }
 }
 
@@ -488,11 +508,16 @@ __global__ __launch_bounds__(kBlock) void k_cg_setup(DmgArgs<T> a) {
 // pass (a row is multiplied deg times), the vector being multiplied in LDS;
 // PAIRS = 4: the first extra pair of a longer row as well (with random
 // diagonals nearly every slice has one, and each product would load it again).
-// Measured, us per step: FP64 1024x512 plate 764 -> 742 (OWN = 1), with random
-// diagonals 914 -> 855 (both); FP32 397x211 with random diagonals 258 -> 238 (PAIRS = 4).
-// With up to two rows per thread (small plates, bound by latency) the rows are
-// loaded with the vectors; with more (large plates, bound by bytes) after the
-// vectors' update, whose registers they then share.
+// A workgroup's time is latency: on the 256x128 plate (one workgroup per CU) it
+// was 22 thousand clocks, of which the control block and the vectors 5.5, nine
+// products 10.6 and the reduction with the arrival 5.4.  So whatever the
+// start needs is asked for at once, a thread's rows are summed side by side
+// (row_sums), the two halves of the vector in LDS share their addresses, and
+// the reduction ends in DPP (block_reduce_waves) on four values where only four
+// are new: 18.5 thousand clocks.  Measured, us per step: FP64 64x32 227 -> 191,
+// 256x128 246 -> 219, 1024x512 775 -> 733; FP32 397x211 238 -> 209, 16 plates
+// 584 -> 512.  OWN = 1: FP64 1024x512 764 -> 742; PAIRS = 4: FP32 397x211 with
+// random diagonals 258 -> 238.
 template <typename T, int RPT, int OWN, int PAIRS, bool FUSE>
 __global__ __launch_bounds__(kBlock, RPT <= 4 ? (RPT <= 2 ? 4 : 3) : 1) void k_cg(DmgArgs<T> a) {
   __shared__ double red[8 * 4 * kWaves];
@@ -501,27 +526,38 @@ __global__ __launch_bounds__(kBlock, RPT <= 4 ? (RPT <= 2 ? 4 : 3) : 1) void k_c
   const int n_own = tp->nl[0];
   const int node0 = tp->node0, halo0 = tp->halo0, slice0 = tp->slice0, nslice = tp->nslice, inst = tp->inst;
   const Ctl* const c = a.ctl + inst;
-  const int mode = c->mode;
-  if (mode == MODE_DONE) return;
   const InstP<T>* const P = a.ip + inst;
-  const int bnd = P->bounds;
+  const int mode = c->mode, flavor = c->flavor, pbuf = c->pbuf, bnd = P->bounds;
+  const int ddef = a.fix[inst].ddef, dmax = a.fix[inst].dmax, idle_tile = a.dr.idle[tile];
+  const double beta = c->beta, alpha = c->alpha;
+  const int tid = threadIdx.x;
+  // where this thread's rows stand: loaded beside the control block
+  int pos[RPT];
+  const int nring = tp->nl[kMaxRing] - n_own;
+#pragma unroll
+  for (int k = 0; k < RPT; ++k) {
+    const int i = tid + k * kBlock;
+    pos[k] = node0 + min(i, n_own - 1);
+    if (i >= n_own && nring > 0) pos[k] = a.dr.halo[halo0 + min(i - n_own, nring - 1)];
+  }
+  // all of these in one round trip with the mode, not one after the other behind its branch
+  asm volatile("" ::"s"(flavor), "s"(pbuf), "s"(bnd), "s"(ddef), "s"(dmax), "s"(idle_tile), "s"(beta), "s"(alpha));
+  if (mode == MODE_DONE) return;
   const bool qp = (a.kind == CG_QP);
   const bool projected = qp && (bnd == PF_BOUNDS_PROJECTED);
-  const bool monotone = projected && (c->flavor != 0);
+  const bool monotone = projected && (flavor != 0);
   const bool xpass = (mode == MODE_RESTART || mode == MODE_CHECK);
   const bool iter = (mode == MODE_ITER);
-  const int tid = threadIdx.x;
-  if (iter && !monotone && a.dr.idle[tile]) {
+  if (iter && !monotone && idle_tile) {
     // no free node here: z, p and the update of x are 0 (see the first pass)
     double v[8] = {0.0, INFINITY, 0.0, 0.0, -INFINITY, 0.0, 0.0, 0.0};
     finish_pass<T, FUSE>(a, inst, v, tile, bnd, red);
     return;
   }
-  const bool cur1 = c->pbuf != 0;
-  const double beta = c->beta;
-  const T al = T(c->alpha), be = T(beta);
+  const bool cur1 = pbuf != 0;
+  const T al = T(alpha), be = T(beta);
   const double tol = a.tol;
-  const int deg = a.deg ? min(a.deg, a.fix[inst].dmax) : a.fix[inst].ddef;
+  const int deg = a.deg ? min(a.deg, dmax) : ddef;
   // current halves (read) and next halves (written) of the pairs
   const double* __restrict__ xc = cur1 ? a.x1 : a.x0;
   double* xn_ = cur1 ? a.x0 : a.x1;
@@ -533,9 +569,10 @@ __global__ __launch_bounds__(kBlock, RPT <= 4 ? (RPT <= 2 ? 4 : 3) : 1) void k_c
   extern __shared__ __align__(16) unsigned char smem[];
   const int nall = tp->nl[xpass ? 1 : deg];   // nodes whose values the pass needs
   T* const ya = reinterpret_cast<T*>(smem);   // the vector the pass multiplies by A, two halves
-  T* const yb = ya + nall;
+  // the other half stands at a fixed distance, so that a column's address serves
+  // both (degree 1 has one vector, of any length)
+  T* const yb = ya + (RPT + 1) * kBlock;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-  const int nh = nall - n_own;
   // the steps of the Chebyshev iteration and the rings' sizes, one per lane:
   // read back lane by lane, so no step waits for memory
   const int sl_ = min(lane, kMaxRing - 2);
@@ -545,7 +582,7 @@ __global__ __launch_bounds__(kBlock, RPT <= 4 ? (RPT <= 2 ? 4 : 3) : 1) void k_c
   // ---- the rows of this thread --------------------------------------------------
   Two<T> av[RPT][PAIRS];
   uint32_t ac[RPT][PAIRS];
-  int xb[RPT], xk[RPT];
+  int xb[RPT], xk[RPT], longest = 0;   // extra pairs, and the most of this wave's rows
   T rsu[RPT];
   Two<T>* const AV = static_cast<Two<T>*>(a.dr.av);
   Two<T>* const XAV = static_cast<Two<T>*>(a.dr.xav);
@@ -556,50 +593,53 @@ __global__ __launch_bounds__(kBlock, RPT <= 4 ? (RPT <= 2 ? 4 : 3) : 1) void k_c
       const size_t at = size_t(slice0 + sl) * (kRowPairs * 64) + lane;
       const int2 x = a.dr.xs[slice0 + sl];
       xb[k] = x.x, xk[k] = x.y;
+      longest = max(longest, x.y);
 #pragma unroll
       for (int q = 0; q < kRowPairs; ++q) {
         ac[k][q] = a.dr.ac[at + q * 64];
         av[k][q] = AV[at + q * 64];
       }
       if constexpr (PAIRS > kRowPairs) {
-        const size_t xo = size_t(xk[k] > 0 ? xb[k] : 0) * 64 + lane;   // a slice without extra pairs loads one it does not use
-        ac[k][kRowPairs] = a.dr.xac[xo];
-        av[k][kRowPairs] = XAV[xo];
+        // a slice without extra pairs gets entries of 0
+        const size_t xo = size_t(xk[k] > 0 ? xb[k] : 0) * 64 + lane;
+        const Two<T> v = XAV[xo];
+        ac[k][kRowPairs] = xk[k] > 0 ? a.dr.xac[xo] : 0u;
+        av[k][kRowPairs] = Two<T>{xk[k] > 0 ? v.x : T(0), xk[k] > 0 ? v.y : T(0)};
       }
       if (k < OWN) rsu[k] = a.rsum[node0 + min(tid + k * kBlock, n_own - 1)];
     }
   };
-  // sum over row k of entry times f(value at the column)
-  auto row_sum = [&](int k, const auto* y, auto zero, auto f) {
-    auto s = zero;
+  // s[k] = sum over row k < N of f(k, entry, value at the column), the rows side
+  // by side: their LDS reads go out together and their sums do not wait for
+  // each other
+  auto row_sums = [&](auto n, const auto* y, auto& s, auto f) {
+    constexpr int N = decltype(n)::value;
 #pragma unroll
-    for (int q = 0; q < kRowPairs; ++q) {
-      s += f(av[k][q].x, y[ac[k][q] & 0xffffu]);
-      s += f(av[k][q].y, y[ac[k][q] >> 16]);
-    }
-    if (PAIRS > kRowPairs && xk[k] > 0) {
-      s += f(av[k][PAIRS - 1].x, y[ac[k][PAIRS - 1] & 0xffffu]);
-      s += f(av[k][PAIRS - 1].y, y[ac[k][PAIRS - 1] >> 16]);
-    }
-    for (int e = PAIRS - kRowPairs; e < xk[k]; ++e) {
-      const size_t xo = (size_t(xb[k]) + e) * 64 + lane;
-      const Two<T> v = XAV[xo];
-      const uint32_t cc = a.dr.xac[xo];
-      s += f(v.x, y[cc & 0xffffu]);
-      s += f(v.y, y[cc >> 16]);
-    }
-    return s;
+    for (int k = 0; k < N; ++k) s[k] = 0;
+    constexpr int G = RPT >= 4 ? 2 : N;   // rows at a time: the registers of four are not there
+#pragma unroll
+    for (int g = 0; g < N; g += G)
+#pragma unroll
+      for (int q = 0; q < PAIRS; ++q)
+#pragma unroll
+        for (int k = g; k < (g + G < N ? g + G : N); ++k) {
+          s[k] += f(k, av[k][q].x, y[ac[k][q] & 0xffffu]);
+          s[k] += f(k, av[k][q].y, y[ac[k][q] >> 16]);
+        }
+    if (longest <= PAIRS - kRowPairs) return;
+#pragma unroll
+    for (int k = 0; k < N; ++k)
+      for (int e = PAIRS - kRowPairs; e < xk[k]; ++e) {
+        const size_t xo = (size_t(xb[k]) + e) * 64 + lane;
+        const Two<T> v = XAV[xo];
+        const uint32_t cc = a.dr.xac[xo];
+        s[k] += f(k, v.x, y[cc & 0xffffu]);
+        s[k] += f(k, v.y, y[cc >> 16]);
+      }
   };
-  constexpr bool kEarlyRows = RPT <= 2;
+  constexpr bool kEarlyRows = RPT <= 2 || (RPT <= 3 && OWN == 1);
 
   // ---- loads of the node vectors --------------------------------------------------
-  int pos[RPT];
-#pragma unroll
-  for (int k = 0; k < RPT; ++k) {
-    const int i = tid + k * kBlock;
-    pos[k] = node0 + min(i, n_own - 1);
-    if (i >= n_own && nh > 0) pos[k] = a.dr.halo[halo0 + min(i - n_own, nh - 1)];
-  }
   T dmv[RPT];
 #pragma unroll
   for (int k = 0; k < RPT; ++k) dmv[k] = a.dim[pos[k]];
@@ -638,14 +678,18 @@ __global__ __launch_bounds__(kBlock, RPT <= 4 ? (RPT <= 2 ? 4 : 3) : 1) void k_c
       xs[i] = value(q, xc[q], rsc[q].x, a.dim[q]);
     }
     __syncthreads();
+    double q_[OWN], xo_[OWN];
 #pragma unroll
-    for (int k = 0; k < RPT; ++k) {
+    for (int k = 0; k < OWN; ++k) xo_[k] = xs[min(tid + k * kBlock, n_own - 1)];
+    row_sums(Int<OWN>{}, xs, q_, [&](int k, T e, double y) { return double(e) * (y - xo_[k]); });
+#pragma unroll
+    for (int k = 0; k < OWN; ++k) {
       const int i = tid + k * kBlock;
-      if (k >= OWN || i >= n_own) continue;
+      if (i >= n_own) continue;
       const int g = node0 + i;
-      const double xi = xs[i];
+      const double xi = xo_[k];
       double xv = xi;
-      const double qi = double(rsu[k]) * xi + row_sum(k, xs, 0.0, [&](T e, double y) { return double(e) * (y - xi); });
+      const double qi = double(rsu[k]) * xi + q_[k];
       const T ri = T(double(a.b[g]) - qi);
       const T di = fabs(dmv[k]);
       const double sr = double(ri) * double(di);
@@ -765,32 +809,52 @@ __global__ __launch_bounds__(kBlock, RPT <= 4 ? (RPT <= 2 ? 4 : 3) : 1) void k_c
     }
     if constexpr (!kEarlyRows) load_rows();
     __syncthreads();
-    const T* ys = ya;
-#pragma unroll 1
-    for (int j = 1; j < deg; ++j) {
+    // One step of the Chebyshev iteration from the values in ys to yd, over the
+    // rows that the steps still to come read.  A wave takes those of its rows
+    // whose slice holds any; what it computes past the last of them is not
+    // read (rows of outer rings, columns inside the tile).
+    auto step = [&](int j, const T* ys, T* yd) {
       const int lim = __builtin_amdgcn_readlane(steps_nl, deg - j);
-      T* const yd = (j & 1) ? yb : ya;
       const T c1 = lane_value(steps_c1, j - 1), c2 = lane_value(steps_c2, j - 1);
+      auto rows = [&](auto n) {
+        constexpr int N = decltype(n)::value;
+        T s_[N];
+        row_sums(n, ys, s_, [](int, T e, T y) { return e * y; });
 #pragma unroll
-      for (int k = 0; k < RPT; ++k) {
-        const int i = tid + k * kBlock;
-        if (i >= lim) continue;
-        const T s = row_sum(k, ys, T(0), [](T e, T y) { return e * y; });
-        // D^-1 (r - A y): the diagonal's part of D^-1 A y is y itself
-        d_[k] = c1 * d_[k] + c2 * (dmv[k] * (r_[k] - s) - y_[k]);
-        y_[k] += d_[k];
-        yd[i] = y_[k];
+        for (int k = 0; k < N; ++k) {
+          // D^-1 (r - A y): the diagonal's part of D^-1 A y is y itself
+          d_[k] = c1 * d_[k] + c2 * (dmv[k] * (r_[k] - s_[k]) - y_[k]);
+          y_[k] += d_[k];
+          yd[tid + k * kBlock] = y_[k];
+        }
+      };
+      const int nk = (lim - wv * 64 + kBlock - 1) / kBlock;   // rows of this wave with a node below lim
+      if constexpr (RPT > 4) {
+        if (nk > 4) rows(Int<RPT>{});
+        else if (nk > 0) rows(Int<4>{});
+      } else {
+        if (nk >= RPT) rows(Int<RPT>{});
+        if constexpr (RPT > 3) { if (nk == 3) rows(Int<3>{}); }
+        if constexpr (RPT > 2) { if (nk == 2) rows(Int<2>{}); }
+        if constexpr (RPT > 1) { if (nk == 1) rows(Int<1>{}); }
       }
       __syncthreads();
-      ys = yd;
+    };
+#pragma unroll 1
+    for (int j = 1; j < deg; j += 2) {
+      step(j, ya, yb);
+      if (j + 1 < deg) step(j + 1, yb, ya);
     }
+    const T* const ys = (deg & 1) ? ya : yb;
     // w = A z on the owned nodes
+    T w_[OWN];
+    row_sums(Int<OWN>{}, ys, w_, [&](int k, T e, T y) { return e * (y - y_[k]); });
 #pragma unroll
-    for (int k = 0; k < RPT; ++k) {
+    for (int k = 0; k < OWN; ++k) {
       const int i = tid + k * kBlock;
-      if (k >= OWN || i >= n_own) continue;
+      if (i >= n_own) continue;
       const T zv = y_[k];
-      const T s = rsu[k] * zv + row_sum(k, ys, T(0), [&](T e, T y) { return e * (y - zv); });
+      const T s = rsu[k] * zv + w_[k];
       wzn[node0 + i] = Two<T>{s, zv};
       gam += double(r_[k]) * double(zv);
       del += double(zv) * double(s);
@@ -802,7 +866,7 @@ __global__ __launch_bounds__(kBlock, RPT <= 4 ? (RPT <= 2 ? 4 : 3) : 1) void k_c
     }
   }
   double v[8] = {del, amin, gam, nc.cf, nc.ca, nc.na, 0.0, nc.ch};   // in PT_* order
-  finish_pass<T, FUSE>(a, inst, v, tile, bnd, red);
+  finish_pass<T, FUSE>(a, inst, v, tile, bnd, red, !xpass && !monotone);
 }
 
 // Combination of an instance's per-tile partials, in a fixed order: thread t
@@ -834,7 +898,7 @@ __device__ __forceinline__ double combine_partials(double* part, size_t nt, int 
     v[PT_RB] = fmax(v[PT_RB], q[PT_RB]);
     v[PT_CH] += q[PT_CH];
   }
-  return block_reduce_rows<8, kPartOps>(v, red);
+  return block_reduce_waves<8, kPartOps>(v, red);
 }
 
 // The solver's state machine: one round's combined partials advance the
@@ -997,7 +1061,7 @@ __global__ __launch_bounds__(kRedBlock) void k_dmg_red(Ctl* ctl, const InstFix* 
     }
   }
   if (mode == MODE_DONE) return;
-  const double vk = block_reduce_rows<8, kPartOps, kRedBlock / 64>(v, red);
+  const double vk = block_reduce_waves<8, kPartOps, kRedBlock / 64>(v, red);
   if (threadIdx.x < 8) tot[threadIdx.x] = vk;
   __syncthreads();
   if (threadIdx.x != 0) return;
@@ -1166,24 +1230,33 @@ static CgKernel<T> cg_kernel_of(const pf_mesh_s* m, bool fuse, bool setup) {
   }
   return fuse ? k_cg<T, RPT, OWN, kRowPairs, true> : k_cg<T, RPT, OWN, kRowPairs, false>;
 }
+// Rows per thread: for the rows, and for the fixed distance between the two
+// halves of the vector in LDS.
+static int cg_rows(const pf_mesh_s* m, int deg) {
+  const int rpt = std::max((m->max_rows[deg] + kBlock - 1) / kBlock, (m->max_nodes[deg] + kBlock - 1) / kBlock - 1);
+  if (rpt > 4) return 8;
+  return m->max_row_own <= kBlock ? std::max(rpt, 1) : std::max(rpt, 3);
+}
 template <typename T>
 static CgKernel<T> cg_kernel(const pf_mesh_s* m, int deg, bool setup) {
   const bool fuse = m->max_inst_tiles <= kFuseMaxTiles;
-  const int rpt = (m->max_rows[deg] + kBlock - 1) / kBlock;
-  if (rpt > 4) return cg_kernel_of<T, 8, 8>(m, fuse, setup);
-  if (m->max_row_own <= kBlock) {
-    if (rpt <= 1) return cg_kernel_of<T, 1, 1>(m, fuse, setup);
-    if (rpt <= 2) return cg_kernel_of<T, 2, 1>(m, fuse, setup);
-    if (rpt <= 3) return cg_kernel_of<T, 3, 1>(m, fuse, setup);
+  const bool one = m->max_row_own <= kBlock;
+  switch (cg_rows(m, deg)) {
+    case 1: return cg_kernel_of<T, 1, 1>(m, fuse, setup);
+    case 2: return cg_kernel_of<T, 2, 1>(m, fuse, setup);
+    case 3: return one ? cg_kernel_of<T, 3, 1>(m, fuse, setup) : cg_kernel_of<T, 3, 3>(m, fuse, setup);
+    case 4: return cg_kernel_of<T, 4, 4>(m, fuse, setup);
+    default: return cg_kernel_of<T, 8, 8>(m, fuse, setup);
   }
-  return rpt <= 3 ? cg_kernel_of<T, 3, 3>(m, fuse, setup) : cg_kernel_of<T, 4, 4>(m, fuse, setup);
 }
 
 // LDS of a pass: the vector being multiplied, twice for a polynomial; nch > 0:
 // of the set-up pass, the start and the elements' values.
 template <typename T>
 static size_t cg_lds(const pf_mesh_s* m, int deg, int nch) {
-  return size_t(nch > 0 ? m->max_slds[nch - 1][deg] : m->max_rlds[deg]) * sizeof(T);
+  if (nch > 0) return size_t(m->max_slds[nch - 1][deg]) * sizeof(T);
+  const int halves = m->max_nodes[deg] > 0 ? 2 * (cg_rows(m, deg) + 1) * kBlock : 0;
+  return size_t(std::max(halves, m->max_rlds[deg])) * sizeof(T);
 }
 
 template <typename T>

@@ -182,6 +182,52 @@ __device__ __forceinline__ double block_reduce_rows(double (&v)[K], double* sh) 
   return s;
 }
 
+// Reduce x over the wave: the row results, then rows 0 and 2 onto rows 1 and 3
+// and row 1 onto row 3 by DPP broadcasts; lane 63 holds the result.
+constexpr int kDppBcast15 = 0x142;     // lane 15 of each row to the next row
+constexpr int kDppBcast31 = 0x143;     // lane 31 to rows 2 and 3
+template <int CTRL>
+__device__ __forceinline__ double dpp_bcast(double x) {
+  const unsigned long long u = static_cast<unsigned long long>(__double_as_longlong(x));
+  const int l = int(uint32_t(u)), h = int(uint32_t(u >> 32));
+  const int lo = __builtin_amdgcn_update_dpp(l, l, CTRL, CTRL == kDppBcast15 ? 0xa : 0xc, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(h, h, CTRL, CTRL == kDppBcast15 ? 0xa : 0xc, 0xf, false);
+  return __longlong_as_double(
+      static_cast<long long>((static_cast<unsigned long long>(uint32_t(hi)) << 32) | uint32_t(lo)));
+}
+template <int K, uint32_t OPS, int k = 0>
+__device__ __forceinline__ void wave_reduce_all(double (&v)[K]) {
+  if constexpr (k < K) {
+    constexpr uint32_t op = (OPS >> (2 * k)) & 3u;
+    v[k] = row_reduce<op>(v[k]);
+    v[k] = combine_op(op, v[k], dpp_bcast<kDppBcast15>(v[k]));
+    v[k] = combine_op(op, v[k], dpp_bcast<kDppBcast31>(v[k]));
+    wave_reduce_all<K, OPS, k + 1>(v);
+  }
+}
+
+// Several block-wide reductions at once, as block_reduce_rows but with the
+// rows of a wave combined by DPP as well: thread k < K is left with NW values
+// to combine instead of 4 NW.  `sh` holds K * NW doubles.
+template <int K, uint32_t OPS, int NW = kWaves>
+__device__ __forceinline__ double block_reduce_waves(double (&v)[K], double* sh) {
+  wave_reduce_all<K, OPS>(v);
+  if ((threadIdx.x & 63) == 63) {
+#pragma unroll
+    for (int k = 0; k < K; ++k) sh[k * NW + (threadIdx.x >> 6)] = v[k];
+  }
+  __syncthreads();
+  const int k = threadIdx.x;
+  if (k >= K) return 0.0;
+  const uint32_t op = (OPS >> (2 * k)) & 3u;
+  double r[NW];
+#pragma unroll
+  for (int j = 0; j < NW; ++j) r[j] = sh[k * NW + j];
+#pragma unroll
+  for (int j = 1; j < NW; ++j) r[0] = combine_op(op, r[0], r[j]);
+  return r[0];
+}
+
 // Block-wide sum; every thread gets the result.  `sh` holds 4 kWaves doubles
 // (one per 16-lane row); the rows' sums are added in a fixed order.
 __device__ __forceinline__ double block_sum(double v, double* sh) {

@@ -684,8 +684,9 @@ extern "C" pf_status_t pf_mesh_create(const pf_mesh_desc_t* inst, int32_t n_inst
     for (int dg = 0; dg <= kAskRing; ++dg) {
       const int de = dg == 0 ? rows.ddef[t.inst] : std::min(dg, rows.dmax[t.inst]);
       m->max_rows[dg] = std::max(m->max_rows[dg], t.nl[de - 1]);
-      // the vector of a pass, twice for a polynomial, or the FP64 iterate of a restart
-      m->max_rlds[dg] = std::max({m->max_rlds[dg], (de > 1 ? 2 : 1) * t.nl[de], dtype == PF_F32 ? 2 * t.nl[1] : t.nl[1]});
+      if (de > 1) m->max_nodes[dg] = std::max(m->max_nodes[dg], t.nl[de]);
+      // the vector of a pass without a polynomial, or the FP64 iterate of a restart
+      m->max_rlds[dg] = std::max(m->max_rlds[dg], dtype == PF_F32 ? 2 * t.nl[1] : t.nl[1]);
       m->max_slds[0][dg] = std::max(m->max_slds[0][dg], t.nl[1] + 2 * (1 + t.nel[de - 1]));
       m->max_slds[1][dg] = std::max(m->max_slds[1][dg], t.nl[1] + 1 + t.nel[de - 1]);
     }

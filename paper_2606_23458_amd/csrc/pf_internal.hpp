@@ -246,7 +246,8 @@ struct pf_mesh_s {
   pf::DevWork dw{};
   pf::DevRows dr{};
   int32_t max_rows[pf::kAskRing + 1] = {};   // rows of the largest row tile for each polynomial degree (0: the default)
-  int32_t max_rlds[pf::kAskRing + 1] = {};   // and the values it keeps in LDS
+  int32_t max_nodes[pf::kAskRing + 1] = {};  // nodes of the largest one with a polynomial
+  int32_t max_rlds[pf::kAskRing + 1] = {};   // values the largest one keeps in LDS without a polynomial
   int32_t max_slds[2][pf::kAskRing + 1] = {};// and in the set-up pass with its elements in one and in two chunks
   int32_t max_row_own = 0;                   // owned nodes of the largest row tile
   bool extra_pairs = false;                  // some rows are longer than the base pairs

@@ -176,7 +176,7 @@ bool row_plan_add(RowPlan& rp, const RowMesh& rm, int inst, size_t width, size_t
   const size_t n = size_t(rm.n);
   const size_t static_lds = 2048;   // the passes' reduction scratch
   const size_t max1 = std::min<size_t>(65535, (lds_limit - static_lds) / 8);            // nodes, one FP64 vector in LDS
-  const size_t max2 = std::min<size_t>(65535, (lds_limit - static_lds) / (2 * width));  // nodes, two vectors
+  const size_t max2 = std::min<size_t>(kRowMax + kBlock, (lds_limit - static_lds) / (2 * width));  // nodes, two vectors
   const RowChoice choice = row_choice(n, rm.tile_nodes, width);
   const size_t own = choice.own;
   const int ddef = choice.degree, ask = std::max(kAskRing, ddef);
