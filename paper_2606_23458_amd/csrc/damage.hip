@@ -1,6 +1,6 @@
 // Damage update (Sec. 2.2, eq. damage_pde_at2 / eq. damage_pde_at1; Sec. 2.4):
-// minimise 1/2 d'Ad - b'd over d_prev <= d <= 1 by a matrix-free, Jacobi-
-// preconditioned projected CG.
+// minimise 1/2 d'Ad - b'd over d_prev <= d <= 1 by a projected CG over the
+// assembled rows of A, preconditioned by a Chebyshev-Jacobi polynomial.
 //
 // The system is scaled by l0/Gc (the minimiser is unchanged), so that its
 // entries are of the order of the element areas in either precision; every
@@ -41,10 +41,9 @@
 // The preconditioner is the Chebyshev-Jacobi polynomial of D^-1 A (degree 1 is
 // Jacobi), applied inside the pass: a tile keeps `degree` rings of neighbours,
 // applies A once per degree on shrinking sets of rings, and needs nothing from
-// other tiles in between.  A round of degree 3 reads hardly more than one of
-// degree 1 (the vectors and the rows are read once) and a solve takes about
-// 0.36 times the rounds (CPU count on the 256x128 plate: 60 -> 22 at 1e-12,
-// 22 -> 8 at 1e-6).
+// other tiles in between.  A round of degree 8 crosses the chip once, as one of
+// degree 1 does, and a solve takes about a fifth of the rounds (256x128 plate at
+// 1e-12: 60 Jacobi, 22 degree 3, 12 degree 8).
 //
 // One round of the solve is one or two launches:
 //   k_cg_setup the solve's first restart: b, the diagonal and the rows of A that
@@ -1013,7 +1012,10 @@ __device__ __forceinline__ void advance_solver(Ctl* c, int nnodes, const double 
 }
 
 // One workgroup per instance: combine the tiles' partials and advance the
-// state (passes run without the combination in their last workgroup).
+// state (passes run without the combination in their last workgroup).  Bound by
+// what one CU can load: the mode is read first, so that an iteration loads four
+// values per tile instead of eight, in one batch up to 4096 tiles, and a finished
+// solve none (1024x512 FP64 step 743 -> 716 us, FP32 350 -> 338).
 constexpr int kRedBlock = kBlock;
 __global__ __launch_bounds__(kRedBlock) void k_dmg_red(Ctl* ctl, const InstFix* fix, const double* part, int n_tiles, const int* bounds,
                                                        int kind, double tol, int max_iter) {
@@ -1027,40 +1029,43 @@ __global__ __launch_bounds__(kRedBlock) void k_dmg_red(Ctl* ctl, const InstFix* 
     bnd = bounds[blockIdx.x];
     nnodes = fix[blockIdx.x].nnodes;
   }
-  const int mode = cp->mode;
-  // one instance: its tiles are all there are, known without a load, so that the
-  // partials' loads go out with the control block's
-  int tile0 = 0, tile_end = n_tiles;
-  if (gridDim.x > 1) {
-    tile0 = fix[blockIdx.x].rt0;
-    tile_end = tile0 + fix[blockIdx.x].nrt;
-    if (mode == MODE_DONE) return;
-  }
+  const int mode = cp->mode, flavor = cp->flavor;
+  const int tile0 = fix[blockIdx.x].rt0, tile_end = tile0 + fix[blockIdx.x].nrt;
+  if (mode == MODE_DONE) return;
   double v[8] = {0.0, INFINITY, 0.0, 0.0, -INFINITY, 0.0, 0.0, 0.0};
   const size_t nt = size_t(n_tiles);
+  // B tiles per thread at a time, of them the values in `set`
+  auto add = [&](auto batch, auto set) {
+    constexpr int B = decltype(batch)::value;
+    constexpr uint32_t S = decltype(set)::value;
 #pragma unroll 1
-  for (int k0 = tile0 + threadIdx.x; k0 < tile_end; k0 += kRedBatch * kRedBlock) {
-    double q[kRedBatch][8];
+    for (int k0 = tile0 + threadIdx.x; k0 < tile_end; k0 += B * kRedBlock) {
+      double q[B][8];
 #pragma unroll
-    for (int j = 0; j < kRedBatch; ++j) {
-      const int k = min(k0 + j * kRedBlock, tile_end - 1);   // clamped: loaded, not added
+      for (int j = 0; j < B; ++j) {
+        const int k = min(k0 + j * kRedBlock, tile_end - 1);   // clamped: loaded, not added
 #pragma unroll
-      for (int f = 0; f < 8; ++f) q[j][f] = part[size_t(f) * nt + k];
+        for (int f = 0; f < 8; ++f)
+          if (S >> f & 1u) q[j][f] = part[size_t(f) * nt + k];
+      }
+#pragma unroll
+      for (int j = 0; j < B; ++j) {
+        const bool in = k0 + j * kRedBlock < tile_end;
+#pragma unroll
+        for (int f = 0; f < 8; ++f) {
+          if (!(S >> f & 1u)) continue;
+          const uint32_t op = (kPartOps >> (2 * f)) & 3u;
+          const double x = in ? q[j][f] : (op == 0 ? 0.0 : (op == 1 ? INFINITY : -INFINITY));
+          v[f] = combine_op(op, v[f], x);
+        }
+      }
     }
-#pragma unroll
-    for (int j = 0; j < kRedBatch; ++j) {
-      const bool in = k0 + j * kRedBlock < tile_end;
-      v[PT_DELTA] += in ? q[j][PT_DELTA] : 0.0;
-      v[PT_AMIN] = fmin(v[PT_AMIN], in ? q[j][PT_AMIN] : INFINITY);
-      v[PT_GAMMA] += in ? q[j][PT_GAMMA] : 0.0;
-      v[PT_CF] = fmax(v[PT_CF], in ? q[j][PT_CF] : -INFINITY);
-      v[PT_CA] = fmax(v[PT_CA], in ? q[j][PT_CA] : -INFINITY);
-      v[PT_NA] += in ? q[j][PT_NA] : 0.0;
-      v[PT_RB] = fmax(v[PT_RB], in ? q[j][PT_RB] : -INFINITY);
-      v[PT_CH] += in ? q[j][PT_CH] : 0.0;
-    }
-  }
-  if (mode == MODE_DONE) return;
+  };
+  // an iteration's pass stores constants in the other four: half the bytes
+  if ((mode == MODE_ITER || mode == MODE_FIRST) && flavor == 0)
+    add(Int<2 * kRedBatch>{}, Int<(1 << PT_DELTA | 1 << PT_GAMMA | 1 << PT_CF | 1 << PT_CH)>{});
+  else
+    add(Int<kRedBatch>{}, Int<255>{});
   const double vk = block_reduce_waves<8, kPartOps, kRedBlock / 64>(v, red);
   if (threadIdx.x < 8) tot[threadIdx.x] = vk;
   __syncthreads();
