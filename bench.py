@@ -39,7 +39,7 @@ and, unless --no-extras: the explicit step alone, graph-replayed stepping, damag
 preconditioners, and the explicit step and CG pass on a 2048x1024 plate.
 Tiles hold 512 owned nodes in FP32 and 448 in FP64 (--tile-nodes changes it;
 'auto' lets the autotuner pick the tile size too); the autotuner picks the
-explicit step's workgroup shape, the library the damage passes' element chunks.
+explicit step's workgroup shape, the library the damage solve's own tiles and degree.
 """
 from __future__ import annotations
 
@@ -61,20 +61,19 @@ WIDTH = {"f32": 4, "f64": 8}
 #   explicit step: nodes 14w + 4 (u, v, a read and written, m^-1, d, row
 #   pointer), elements 24 + 9w (connectivity, 6 grad phi + area, H read and
 #   written, 3 corner ids); with N ~ N_e/2 that is 90 B (w = 4), 154 B (w = 8).
-#   damage CG iteration pass: nodes 11w + 1 (r, A z, A p, p, x, D^-1 and the
-#   held flag read; p, A p, x, r, A z written), elements 4w + 24 (the three
-#   off-diagonal entries of the element stiffness, which the pass reads in
-#   place of the gradients and the area, the per-solve mass coefficient,
-#   connectivity, corner ids): 62.5 B (w = 4), 100.5 B (w = 8).  The restart
-#   and check passes move fewer bytes; the family is costed at the iteration
-#   pass, which is most of its launches.
+#   damage CG iteration pass over assembled rows: nodes 13w + 16 (r, A p, A z,
+#   z, p, the FP64 x, D^-1, the row sum and the bound read; p, x, r, A p, A z, z
+#   written), rows 6w + 12 (6 entries and their 16-bit columns): 52 B (w = 4)
+#   and 90 B (w = 8) per element, the rows of the tiles' rings not counted.
+#   The set-up, restart and check passes differ; the family is costed at the
+#   iteration pass, which is most of its launches.
 BYTES_BASIS = {
     0: "explicit step, paper layout: nodes 14w+4 B (u, v, a read and written, 1/m, d, CSR row pointer) "
        "at N = N_e/2, elements 24+9w B (int32 connectivity, 6 grad phi + area, H read and written, "
        "3 int32 corner ids)",
-    1: "damage CG iterate pass, the library's arrays costed with 32-bit indices: nodes 11w+1 B (r, Az, Ap, p, "
-       "x, 1/diag and the held flag read; p, Ap, x, r, Az written) at N = N_e/2, elements 4w+24 B "
-       "(3 stiffness off-diagonals, the mass coefficient, connectivity, corner ids); intermediates "
+    1: "damage CG iterate pass over assembled rows: nodes 13w+16 B (r, Ap, Az, z, p, the FP64 x, 1/diag, the row sum "
+       "and the bound read; p, x, r, Ap, Az, z written) and rows 6w+12 B (6 entries, 6 16-bit columns) "
+       "at N = N_e/2; the ring rows that a tile's polynomial needs, and intermediates "
        "kept in LDS are not counted",
 }
 
@@ -83,11 +82,11 @@ def alg_bytes_per_elem(family: int, w: int) -> float:
     if family == 0:
         return (14 * w + 4) / 2 + 24 + 9 * w
     if family == 1:
-        return (11 * w + 1) / 2 + 4 * w + 24
+        return (13 * w + 16) / 2 + (6 * w + 12) / 2
     raise ValueError(family)
 
 
-FAMILY = {0: "k_explicit", 1: "k_dmg (damage CG pass)", 2: "k_dmg_init / k_dmg_final", 3: "adjoint",
+FAMILY = {0: "k_explicit", 1: "k_cg (damage CG pass)", 2: "k_dmg_init / k_dmg_final", 3: "adjoint",
           4: "k_dmg_red (per-instance CG reductions)"}
 
 
@@ -481,7 +480,7 @@ def gc_field(steps: int) -> dict:
 
 
 def preconditioners(steps: int) -> dict:
-    """Jacobi against the Chebyshev-Jacobi polynomials of degree 2-4 on the 1024x512 plate (FP32):
+    """The default against Jacobi and the Chebyshev-Jacobi polynomials of degree 2-4 on the 1024x512 plate (FP32):
     time per step and CG rounds (one reduction each) per solve."""
     import workloads as w
     from paper_2606_23458_amd import Simulator
@@ -489,7 +488,7 @@ def preconditioners(steps: int) -> dict:
     p = w.config1()
     out = {}
     dt = None
-    for deg in (0, 2, 3, 4):
+    for deg in (0, 1, 2, 3, 4):
         sim = Simulator(p, dtype="f32", dt=dt, cg=CgConfig(tol=default_tol("f32"), precond=deg))
         dt = list(sim.dt)
         sim.run(20)
@@ -503,10 +502,9 @@ def preconditioners(steps: int) -> dict:
         ev1.record()
         gpu_sync()
         mean = sum(rounds) / len(rounds)
-        out["jacobi" if deg == 0 else f"chebyshev{deg}"] = {
+        out[("default", "jacobi")[deg] if deg < 2 else f"chebyshev{deg}"] = {
             "ms_per_step": round(ev0.elapsed_time(ev1) / steps, 4), "rounds_per_solve": round(mean, 2)}
-    out["note"] = ("polled steps (Simulator.step); a round is one reduction and, with a degree-k "
-                   "polynomial, k passes (restart and check rounds make one)")
+    out["note"] = "polled steps (Simulator.step); a round is one pass and one reduction at every degree"
     return out
 
 

@@ -145,7 +145,8 @@ struct DmgArgs {
 // the polynomial is positive, so M is symmetric positive definite and CG
 // applies unchanged.  The ratio suits the operator's condition number of
 // about 30 at l0 = 2h: rounds at 1e-12 for degree 3 with ratios 10, 20, 30 are
-// 23, 22, 21 on the 256x128 plate (CPU).
+// 23, 22, 21 on the 256x128 plate (CPU), for degree 8 with ratios 15, 20, 30, 40
+// and 60 14, 13, 12, 12 and 15.
 constexpr double kChebRatio = 30.0;
 
 __global__ void k_dmg_init(Ctl* ctl, int n_inst, int kind, int monotone) {
