@@ -300,6 +300,11 @@ pf_status_t pf_damage_solve(pf_mesh_t m, const pf_params_t* p, const void* H, co
  * (from the previous one on the second call); opts->start = 0 starts it from
  * zero and counts calls afresh (a fresh handle's first call starts from zero
  * too).  Projected bounds only.
+ * dGc sums the elements' Gc terms; with H = 0 around the free nodes (an AT1
+ * notch before any wave reaches it) A and b both scale with Gc, the true
+ * derivative is 0, and the terms cancel to lambda'(A d - b)/Gc: what is left is
+ * the forward solve's residual, at most (tol/Gc) sum_i |lambda_i| A_ii, and
+ * none of its digits means anything.
  * adj_np1 is read only; adj_n must not alias adj_np1, s_n or s_np1.
  */
 pf_status_t pf_step_backward(pf_mesh_t m, const pf_params_t* p, const double* dt,

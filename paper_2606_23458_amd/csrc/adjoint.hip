@@ -104,7 +104,9 @@ __global__ __launch_bounds__(kBlock) void k_adj_damage(DevMesh dm, const InstP<T
                          (double(l0v) * double(d0) + double(l1v) * double(d1) + double(l2v) * double(d2) +
                           double(ls) * double(ds));
       const double lw = double(A) / 3.0 * double(ls);
-      // dL/dGc_e of this element; the instance's Gc scales every Gc_e by phi_e
+      // dL/dGc_e of this element; the instance's Gc scales every Gc_e by phi_e.
+      // With H = 0 around the free nodes the terms sum to lambda'(A d - b)/Gc,
+      // that is to 0 up to the forward solve's residual.
       const double ge = -(double(P.gK) * lKd + double(P.gM) * lMd + double(P.gW) * lw);
       gsum += gcs ? double(ph) * ge : ge;
       if (dgc_field) dgc_field[gid] += ge;

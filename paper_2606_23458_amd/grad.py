@@ -77,6 +77,10 @@ class TrajectoryRunner:
                  timing: dict | None = None) -> torch.Tensor:
         """Reverse sweep from the adjoint of the final damage; returns dL/dGc per instance (float64).
 
+        Where the damage does not depend on Gc (AT1 before any wave reaches the
+        notch) the derivative is 0, and what is returned is the solves' residual:
+        at most tol/Gc times the sum of |lambda_i| A_ii over the steps.
+
         field_grad (float64 device [n_elems], internal order) also receives
         dL/dGc_e of every element (the toughness field Gc_e = Gc phi_e).
         timing, if given, receives the wall seconds spent recomputing segments
