@@ -568,6 +568,7 @@ __global__ __launch_bounds__(kBlock, RPT <= 4 ? (RPT <= 2 ? 4 : 3) : 1) void k_c
 
   extern __shared__ __align__(16) unsigned char smem[];
   const int nall = tp->nl[xpass ? 1 : deg];   // nodes whose values the pass needs
+  const int nrow = cg_row_limit(*tp, deg, xpass);   // rows whose columns lie among them
   T* const ya = reinterpret_cast<T*>(smem);   // the vector the pass multiplies by A, two halves
   // the other half stands at a fixed distance, so that a column's address serves
   // both (degree 1 has one vector, of any length)
@@ -596,14 +597,16 @@ __global__ __launch_bounds__(kBlock, RPT <= 4 ? (RPT <= 2 ? 4 : 3) : 1) void k_c
       longest = max(longest, x.y);
 #pragma unroll
       for (int q = 0; q < kRowPairs; ++q) {
-        ac[k][q] = a.dr.ac[at + q * 64];
+        const uint32_t cc = a.dr.ac[at + q * 64];
+        ac[k][q] = tid + k * kBlock < nrow ? cc : 0u;
         av[k][q] = AV[at + q * 64];
       }
       if constexpr (PAIRS > kRowPairs) {
         // a slice without extra pairs gets entries of 0
         const size_t xo = size_t(xk[k] > 0 ? xb[k] : 0) * 64 + lane;
         const Two<T> v = XAV[xo];
-        ac[k][kRowPairs] = xk[k] > 0 ? a.dr.xac[xo] : 0u;
+        const uint32_t cc = a.dr.xac[xo];
+        ac[k][kRowPairs] = xk[k] > 0 && tid + k * kBlock < nrow ? cc : 0u;
         av[k][kRowPairs] = Two<T>{xk[k] > 0 ? v.x : T(0), xk[k] > 0 ? v.y : T(0)};
       }
       if (k < OWN) rsu[k] = a.rsum[node0 + min(tid + k * kBlock, n_own - 1)];
@@ -632,7 +635,7 @@ __global__ __launch_bounds__(kBlock, RPT <= 4 ? (RPT <= 2 ? 4 : 3) : 1) void k_c
       for (int e = PAIRS - kRowPairs; e < xk[k]; ++e) {
         const size_t xo = (size_t(xb[k]) + e) * 64 + lane;
         const Two<T> v = XAV[xo];
-        const uint32_t cc = a.dr.xac[xo];
+        const uint32_t cx = a.dr.xac[xo], cc = tid + k * kBlock < nrow ? cx : 0u;
         s[k] += f(k, v.x, y[cc & 0xffffu]);
         s[k] += f(k, v.y, y[cc >> 16]);
       }
@@ -812,7 +815,7 @@ __global__ __launch_bounds__(kBlock, RPT <= 4 ? (RPT <= 2 ? 4 : 3) : 1) void k_c
     // One step of the Chebyshev iteration from the values in ys to yd, over the
     // rows that the steps still to come read.  A wave takes those of its rows
     // whose slice holds any; what it computes past the last of them is not
-    // read (rows of outer rings, columns inside the tile).
+    // read (its columns lie in the pass's LDS, see cg_row_limit).
     auto step = [&](int j, const T* ys, T* yd) {
       const int lim = __builtin_amdgcn_readlane(steps_nl, deg - j);
       const T c1 = lane_value(steps_c1, j - 1), c2 = lane_value(steps_c2, j - 1);
@@ -1232,22 +1235,15 @@ static CgKernel<T> cg_kernel_of(const pf_mesh_s* m, bool fuse, bool setup) {
   // the first extra pair in registers too, where there are any and the registers suffice
   if constexpr (RPT <= (sizeof(T) == 4 ? 4 : 3)) {
     constexpr int X = kRowPairs + 1;
-    if (m->extra_pairs) return fuse ? k_cg<T, RPT, OWN, X, true> : k_cg<T, RPT, OWN, X, false>;
+    if (m->cg.extra_pairs) return fuse ? k_cg<T, RPT, OWN, X, true> : k_cg<T, RPT, OWN, X, false>;
   }
   return fuse ? k_cg<T, RPT, OWN, kRowPairs, true> : k_cg<T, RPT, OWN, kRowPairs, false>;
-}
-// Rows per thread: for the rows, and for the fixed distance between the two
-// halves of the vector in LDS.
-static int cg_rows(const pf_mesh_s* m, int deg) {
-  const int rpt = std::max((m->max_rows[deg] + kBlock - 1) / kBlock, (m->max_nodes[deg] + kBlock - 1) / kBlock - 1);
-  if (rpt > 4) return 8;
-  return m->max_row_own <= kBlock ? std::max(rpt, 1) : std::max(rpt, 3);
 }
 template <typename T>
 static CgKernel<T> cg_kernel(const pf_mesh_s* m, int deg, bool setup) {
   const bool fuse = m->max_inst_tiles <= kFuseMaxTiles;
-  const bool one = m->max_row_own <= kBlock;
-  switch (cg_rows(m, deg)) {
+  const bool one = m->cg.max_row_own <= kBlock;
+  switch (cg_rows(m->cg, deg)) {
     case 1: return cg_kernel_of<T, 1, 1>(m, fuse, setup);
     case 2: return cg_kernel_of<T, 2, 1>(m, fuse, setup);
     case 3: return one ? cg_kernel_of<T, 3, 1>(m, fuse, setup) : cg_kernel_of<T, 3, 3>(m, fuse, setup);
@@ -1256,19 +1252,10 @@ static CgKernel<T> cg_kernel(const pf_mesh_s* m, int deg, bool setup) {
   }
 }
 
-// LDS of a pass: the vector being multiplied, twice for a polynomial; nch > 0:
-// of the set-up pass, the start and the elements' values.
-template <typename T>
-static size_t cg_lds(const pf_mesh_s* m, int deg, int nch) {
-  if (nch > 0) return size_t(m->max_slds[nch - 1][deg]) * sizeof(T);
-  const int halves = m->max_nodes[deg] > 0 ? 2 * (cg_rows(m, deg) + 1) * kBlock : 0;
-  return size_t(std::max(halves, m->max_rlds[deg])) * sizeof(T);
-}
-
 template <typename T>
 static void launch_cg(const pf_mesh_s* m, DmgArgs<T> a, int nch, hipStream_t s) {
   a.nch = nch;
-  hipLaunchKernelGGL(cg_kernel<T>(m, a.deg, nch > 0), dim3(m->dr.n_tiles), dim3(kBlock), cg_lds<T>(m, a.deg, nch), s, a);
+  hipLaunchKernelGGL(cg_kernel<T>(m, a.deg, nch > 0), dim3(m->dr.n_tiles), dim3(kBlock), cg_lds(m->cg, a.deg, nch, sizeof(T)), s, a);
 }
 
 // Element chunks of the set-up pass: two (the elements' mass coefficients and
@@ -1281,7 +1268,7 @@ static int damage_chunks(pf_mesh_s* m) {
   auto occ = [&](int n) {
     int o = 0;
     const void* k = reinterpret_cast<const void*>(cg_kernel<T>(m, 0, true));
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&o, k, kBlock, cg_lds<T>(m, 0, n)) != hipSuccess) o = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&o, k, kBlock, cg_lds(m->cg, 0, n, sizeof(T))) != hipSuccess) o = 0;
     return o;
   };
   if (nch <= 0) nch = occ(2) > occ(1) ? 2 : 1;

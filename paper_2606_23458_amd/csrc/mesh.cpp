@@ -676,21 +676,7 @@ extern "C" pf_status_t pf_mesh_create(const pf_mesh_desc_t* inst, int32_t n_inst
   m->dr.xac = static_cast<const uint32_t*>(p_xac);
   m->dr.xcode = static_cast<const uint2*>(p_xcode);
   m->dr.n_tiles = int32_t(rows.tiles.size());
-  // rows and LDS values of the largest row tile by degree (an instance whose
-  // tiles hold fewer rings runs with its own largest degree)
-  m->extra_pairs = !rows.xac.empty();
-  for (const RowTile& t : rows.tiles) {
-    m->max_row_own = std::max(m->max_row_own, t.nl[0]);
-    for (int dg = 0; dg <= kAskRing; ++dg) {
-      const int de = dg == 0 ? rows.ddef[t.inst] : std::min(dg, rows.dmax[t.inst]);
-      m->max_rows[dg] = std::max(m->max_rows[dg], t.nl[de - 1]);
-      if (de > 1) m->max_nodes[dg] = std::max(m->max_nodes[dg], t.nl[de]);
-      // the vector of a pass without a polynomial, or the FP64 iterate of a restart
-      m->max_rlds[dg] = std::max(m->max_rlds[dg], dtype == PF_F32 ? 2 * t.nl[1] : t.nl[1]);
-      m->max_slds[0][dg] = std::max(m->max_slds[0][dg], t.nl[1] + 2 * (1 + t.nel[de - 1]));
-      m->max_slds[1][dg] = std::max(m->max_slds[1][dg], t.nl[1] + 1 + t.nel[de - 1]);
-    }
-  }
+  m->cg = cg_shape(rows, w);
   m->dm.tiles = static_cast<const TileRec*>(p_tiles);
   m->dm.halo_idx = static_cast<const int32_t*>(p_halo);
   m->dm.lc0 = static_cast<const uint16_t*>(p_lc0);

@@ -149,6 +149,22 @@ struct DevMesh {
   int32_t n_nodes, n_elems, n_tiles, n_te;
 };
 
+// What the launches of the damage passes are sized by: the largest row tile for
+// each polynomial degree that a caller may ask for (0: the default).
+struct CgShape {
+  int32_t max_rows[kAskRing + 1];      // rows
+  int32_t max_nodes[kAskRing + 1];     // nodes, of tiles with a polynomial
+  int32_t max_rlds[kAskRing + 1];      // values in LDS without a polynomial, or in a restart
+  int32_t max_slds[2][kAskRing + 1];   // and in the set-up pass with its elements in one and in two chunks
+  int32_t max_row_own;                 // owned nodes
+  bool extra_pairs;                    // some rows are longer than the base pairs
+};
+// The rows of a tile whose sums a pass of degree `deg` uses: the owned ones in a
+// restart or check, else those up to ring deg - 1.  Their columns are what the
+// pass holds in LDS (nl[1], nl[deg] nodes); a lane past them multiplies by
+// column 0, since its row's columns may lie on any ring.
+constexpr int cg_row_limit(const RowTile& t, int deg, bool xpass) { return xpass ? t.nl[0] : t.nl[deg - 1]; }
+
 // Device view of the rows of the damage operator.  The nodes are numbered
 // once more for the damage solve ("row order", pos): row tiles own contiguous
 // runs of positions, chosen for the CG passes alone, so neither the caller's
@@ -245,12 +261,7 @@ struct pf_mesh_s {
   pf::DevMesh dm{};
   pf::DevWork dw{};
   pf::DevRows dr{};
-  int32_t max_rows[pf::kAskRing + 1] = {};   // rows of the largest row tile for each polynomial degree (0: the default)
-  int32_t max_nodes[pf::kAskRing + 1] = {};  // nodes of the largest one with a polynomial
-  int32_t max_rlds[pf::kAskRing + 1] = {};   // values the largest one keeps in LDS without a polynomial
-  int32_t max_slds[2][pf::kAskRing + 1] = {};// and in the set-up pass with its elements in one and in two chunks
-  int32_t max_row_own = 0;                   // owned nodes of the largest row tile
-  bool extra_pairs = false;                  // some rows are longer than the base pairs
+  pf::CgShape cg{};
   std::vector<void*> allocs;         // every device allocation, freed at destroy
   size_t device_bytes = 0;
   // host mirror of the current per-instance parameters (bytes of InstP<T>[n_inst])
@@ -322,7 +333,15 @@ bool row_plan_add(RowPlan& rp, const RowMesh& rm, int inst, size_t width, size_t
 void rcb(std::vector<int32_t>& ids, size_t lo, size_t hi, const double* xy, size_t maxn,
          std::vector<std::pair<size_t, size_t>>& leaves);
 
-// Matrix-free CG on the damage operator (damage.hip).  kind 0: the bound-
+CgShape cg_shape(const RowPlan& rp, size_t width);
+// Rows per thread of the CG pass: for the rows, and for the fixed distance
+// between the two halves of the vector in LDS.
+int cg_rows(const CgShape& c, int deg);
+// LDS bytes of a pass: the vector being multiplied, twice for a polynomial;
+// nch > 0: of the set-up pass, the start and the elements' values.
+size_t cg_lds(const CgShape& c, int deg, int nch, size_t width);
+
+// CG on the damage operator (damage.hip).  kind 0: the bound-
 // constrained damage update (b assembled from H, lower bound lb, result in x).
 // kind 1: the linear system A_FF x_F = b_F on the fixed free set F = {W == 0}
 // (b, W and the starting x prepared by the caller in the workspaces; the

@@ -373,4 +373,35 @@ bool row_plan_add(RowPlan& rp, const RowMesh& rm, int inst, size_t width, size_t
   return true;
 }
 
+CgShape cg_shape(const RowPlan& rp, size_t width) {
+  CgShape c{};
+  c.extra_pairs = !rp.xac.empty();
+  for (const RowTile& t : rp.tiles) {
+    c.max_row_own = std::max(c.max_row_own, t.nl[0]);
+    for (int dg = 0; dg <= kAskRing; ++dg) {
+      // an instance whose tiles hold fewer rings runs with its own largest degree
+      const int de = dg == 0 ? rp.ddef[size_t(t.inst)] : std::min(dg, rp.dmax[size_t(t.inst)]);
+      c.max_rows[dg] = std::max(c.max_rows[dg], t.nl[de - 1]);
+      if (de > 1) c.max_nodes[dg] = std::max(c.max_nodes[dg], t.nl[de]);
+      // the vector of a pass without a polynomial, or the FP64 iterate of a restart
+      c.max_rlds[dg] = std::max(c.max_rlds[dg], t.nl[1] * int32_t(sizeof(double) / width));
+      c.max_slds[0][dg] = std::max(c.max_slds[0][dg], t.nl[1] + 2 * (1 + t.nel[de - 1]));
+      c.max_slds[1][dg] = std::max(c.max_slds[1][dg], t.nl[1] + 1 + t.nel[de - 1]);
+    }
+  }
+  return c;
+}
+
+int cg_rows(const CgShape& c, int deg) {
+  const int rpt = std::max((c.max_rows[deg] + kBlock - 1) / kBlock, (c.max_nodes[deg] + kBlock - 1) / kBlock - 1);
+  if (rpt > 4) return 8;
+  return c.max_row_own <= kBlock ? std::max(rpt, 1) : std::max(rpt, 3);
+}
+
+size_t cg_lds(const CgShape& c, int deg, int nch, size_t width) {
+  if (nch > 0) return size_t(c.max_slds[nch - 1][deg]) * width;
+  const int halves = c.max_nodes[deg] > 0 ? 2 * (cg_rows(c, deg) + 1) * kBlock : 0;
+  return size_t(std::max(halves, c.max_rlds[deg])) * width;
+}
+
 }  // namespace pf

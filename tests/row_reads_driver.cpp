@@ -1,0 +1,114 @@
+// Checks on the CPU that every LDS read of the damage passes lies inside the
+// bytes that their launch asks for: run by test_row_reads.py.
+#include <algorithm>
+#include <cmath>
+#include <cstdio>
+#include <cstdlib>
+#include <numeric>
+#include <random>
+
+#include "../paper_2606_23458_amd/csrc/pf_internal.hpp"
+
+using namespace pf;
+
+#define CHECK(c)                                                              \
+  do {                                                                        \
+    if (!(c)) {                                                               \
+      std::printf("FAILED line %d: %s\n", __LINE__, #c);                      \
+      std::exit(1);                                                           \
+    }                                                                         \
+  } while (0)
+
+struct Plate {
+  int nx, ny, fan;       // a grid, or `fan` triangles around one node
+  bool diag;             // random diagonals
+  size_t tile_nodes;
+};
+
+static std::mt19937 rng(1);
+
+static void add(RowPlan& rp, const Plate& c, int inst, size_t width) {
+  std::vector<double> xy;
+  std::vector<int32_t> tri;
+  if (c.fan) {
+    xy = {0.0, 0.0};
+    for (int i = 0; i < c.fan; ++i) xy.push_back(std::cos(6.283185 * i / c.fan)), xy.push_back(std::sin(6.283185 * i / c.fan));
+    for (int i = 0; i < c.fan; ++i) tri.insert(tri.end(), {0, 1 + i, 1 + (i + 1) % c.fan});
+  } else {
+    for (int j = 0; j <= c.ny; ++j)
+      for (int i = 0; i <= c.nx; ++i) xy.push_back(i), xy.push_back(j);
+    for (int j = 0; j < c.ny; ++j)
+      for (int i = 0; i < c.nx; ++i) {
+        const int a = j * (c.nx + 1) + i, b = a + 1, d = a + c.nx + 1, e = d + 1;
+        if (c.diag && (rng() & 1))
+          tri.insert(tri.end(), {a, b, d, b, e, d});
+        else
+          tri.insert(tri.end(), {a, b, e, a, e, d});
+      }
+  }
+  const int n = int(xy.size() / 2), ne = int(tri.size() / 3), off = int(rp.pos.size());
+  std::vector<int32_t> ni(n), eo(ne), te(ne);
+  std::iota(ni.begin(), ni.end(), 0);
+  std::iota(eo.begin(), eo.end(), 0);
+  std::iota(te.begin(), te.end(), 0);
+  std::vector<std::pair<size_t, size_t>> leaves;
+  for (size_t lo = 0; lo < size_t(n); lo += c.tile_nodes) leaves.emplace_back(lo, std::min<size_t>(n, lo + c.tile_nodes));
+  rp.pos.resize(size_t(off) + n);
+  rp.node.resize(size_t(off) + n);
+  RowMesh rm{off, 0, n, ne, xy.data(), tri.data(), ni.data(), eo.data(), te.data(), &leaves, c.tile_nodes};
+  CHECK(row_plan_add(rp, rm, inst, width, 163840));
+}
+
+static void check(const RowPlan& rp, size_t width) {
+  const CgShape cg = cg_shape(rp, width);
+  for (int ask = 0; ask <= kAskRing; ++ask) {
+    const int rpt = cg_rows(cg, ask);
+    const long lds = long(cg_lds(cg, ask, 0, width)), half = long((rpt + 1) * kBlock * int(width));
+    for (const RowTile& t : rp.tiles) {
+      const int deg = ask ? std::min(ask, rp.dmax[size_t(t.inst)]) : rp.ddef[size_t(t.inst)];
+      CHECK(rpt * kBlock >= t.nl[deg - 1]);
+      // the vectors' own nodes, and the other half's stores of a polynomial
+      CHECK(long(t.nl[1]) * 8 <= lds && long(t.nl[deg]) * long(width) <= (deg > 1 ? half : lds));
+      if (deg > 1) CHECK(2 * half <= lds && rpt <= kRowMax / kBlock);
+      for (int i = 0; i < rpt * kBlock; ++i) {
+        // the row that a lane loads (past the last slice: that slice's), and the columns it multiplies by
+        const size_t s = size_t(t.slice0) + size_t(std::min(i / 64, t.nslice - 1)), lane = size_t(i % 64);
+        auto pair = [&](uint32_t cc, bool xpass) {
+          if (i >= cg_row_limit(t, deg, xpass)) cc = 0;
+          for (uint32_t col : {cc & 0xffffu, cc >> 16}) {
+            CHECK(int(col) < t.nl[xpass ? 1 : deg]);
+            CHECK(xpass ? long(col + 1) * 8 <= lds : long(col + 1) * long(width) <= (deg > 1 ? half : lds));
+          }
+        };
+        for (bool xpass : {true, false}) {
+          for (int q = 0; q < kRowPairs; ++q) pair(rp.ac[(s * kRowPairs + size_t(q)) * 64 + lane], xpass);
+          for (int q = 0; q < rp.xs[s].y; ++q) pair(rp.xac[(size_t(rp.xs[s].x) + size_t(q)) * 64 + lane], xpass);
+        }
+      }
+      // the set-up pass: the start, then the elements' values behind a zero
+      for (int nch : {1, 2})
+        CHECK(size_t(t.nl[1] + nch % 2 * (1 + t.nel[deg - 1]) + 1 + t.nel[deg - 1]) * width <= cg_lds(cg, ask, nch, width));
+    }
+  }
+}
+
+int main() {
+  const Plate plates[] = {{64, 32, 0, false, 256}, {397, 211, 0, true, 256}, {120, 60, 0, true, 64},
+                          {1, 1, 0, false, 256},   {3000, 1, 0, true, 256},  {0, 0, 12, false, 256},
+                          {0, 0, 3000, false, 256}, {1448, 724, 0, true, 512}, {700, 300, 0, false, 256}};
+  for (size_t width : {sizeof(double), sizeof(float)}) {
+    for (const Plate& c : plates) {
+      RowPlan rp;
+      add(rp, c, 0, width);
+      check(rp, width);
+      std::printf("plate ok\n");
+    }
+    // instances of different degrees in one handle: the launch is sized by the largest
+    RowPlan rp;
+    int inst = 0;
+    for (const Plate& c : {plates[0], plates[6], plates[2], plates[3]}) add(rp, c, inst++, width);
+    check(rp, width);
+    std::printf("batch ok\n");
+  }
+  return 0;
+}
