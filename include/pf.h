@@ -163,7 +163,9 @@ typedef struct {
                                 (no set-up pass; iterate, held set and CG
                                 scalars are kept).  Every call ends with the
                                 final pass, so d, active_out and stats always
-                                hold the current iterate.  With check_every = 0
+                                hold the current iterate.  A precond above that
+                                of the call that began the solve runs as that
+                                one.  With check_every = 0
                                 and resume, a step can be captured once as a
                                 HIP graph of a fixed number of rounds and
                                 continued, rarely, by a second graph. */

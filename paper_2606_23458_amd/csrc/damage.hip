@@ -124,7 +124,7 @@ struct DmgArgs {
   int32_t max_iter;
   int32_t kind;        // CG_QP or CG_LINEAR
   int32_t start;       // 1: extrapolated start for the damage solve
-  int32_t deg;         // polynomial degree (an instance runs min(deg, InstFix::dmax)); 0: InstFix::ddef
+  int32_t deg;         // polynomial degree asked for (see cg_degree)
   // combination of the round in the pass's last workgroup: 0 none (a
   // k_dmg_red launch follows), 1 combine and advance the solver, 2 combine and
   // run the state machine without storing it (timing aid)
@@ -149,7 +149,7 @@ struct DmgArgs {
 // and 60 14, 13, 12, 12 and 15.
 constexpr double kChebRatio = 30.0;
 
-__global__ void k_dmg_init(Ctl* ctl, int n_inst, int kind, int monotone) {
+__global__ void k_dmg_init(Ctl* ctl, const InstFix* fix, int n_inst, int kind, int monotone, int ask) {
   const int k = blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= n_inst) return;
   Ctl& c = ctl[k];
@@ -165,6 +165,7 @@ __global__ void k_dmg_init(Ctl* ctl, int n_inst, int kind, int monotone) {
   c.wbuf = 0;
   c.flavor = (kind == CG_QP && monotone) ? 1 : 0;
   c.outer = 0;
+  c.deg = cg_degree(fix[k], ask);
   c.inner = 0;
   c.rz = 0.0;
   c.alpha = 0.0;
@@ -327,7 +328,7 @@ __global__ __launch_bounds__(kBlock) void k_cg_setup(DmgArgs<T> a) {
   const bool projected = qp && (bnd == PF_BOUNDS_PROJECTED);
   const bool monotone = projected && (c->flavor != 0);
   const double tol = a.tol;
-  const int deg = a.deg ? min(a.deg, a.fix[inst].dmax) : a.fix[inst].ddef;
+  const int deg = cg_degree(a.fix[inst], a.deg);
   const int nrow = tp->nl[deg - 1], nel = tp->nel[deg - 1];
   const int tid = threadIdx.x;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
@@ -528,7 +529,7 @@ __global__ __launch_bounds__(kBlock, RPT <= 4 ? (RPT <= 2 ? 4 : 3) : 1) void k_c
   const Ctl* const c = a.ctl + inst;
   const InstP<T>* const P = a.ip + inst;
   const int mode = c->mode, flavor = c->flavor, pbuf = c->pbuf, bnd = P->bounds;
-  const int ddef = a.fix[inst].ddef, dmax = a.fix[inst].dmax, idle_tile = a.dr.idle[tile];
+  const int ask = cg_degree(a.fix[inst], a.deg), dset = c->deg, idle_tile = a.dr.idle[tile];
   const double beta = c->beta, alpha = c->alpha;
   const int tid = threadIdx.x;
   // where this thread's rows stand: loaded beside the control block
@@ -541,7 +542,7 @@ __global__ __launch_bounds__(kBlock, RPT <= 4 ? (RPT <= 2 ? 4 : 3) : 1) void k_c
     if (i >= n_own && nring > 0) pos[k] = a.dr.halo[halo0 + min(i - n_own, nring - 1)];
   }
   // all of these in one round trip with the mode, not one after the other behind its branch
-  asm volatile("" ::"s"(flavor), "s"(pbuf), "s"(bnd), "s"(ddef), "s"(dmax), "s"(idle_tile), "s"(beta), "s"(alpha));
+  asm volatile("" ::"s"(flavor), "s"(pbuf), "s"(bnd), "s"(ask), "s"(dset), "s"(idle_tile), "s"(beta), "s"(alpha));
   if (mode == MODE_DONE) return;
   const bool qp = (a.kind == CG_QP);
   const bool projected = qp && (bnd == PF_BOUNDS_PROJECTED);
@@ -557,7 +558,8 @@ __global__ __launch_bounds__(kBlock, RPT <= 4 ? (RPT <= 2 ? 4 : 3) : 1) void k_c
   const bool cur1 = pbuf != 0;
   const T al = T(alpha), be = T(beta);
   const double tol = a.tol;
-  const int deg = a.deg ? min(a.deg, dmax) : ddef;
+  // a resumed call may ask for more rings than the set-up assembled rows for
+  const int deg = min(ask, dset);
   // current halves (read) and next halves (written) of the pairs
   const double* __restrict__ xc = cur1 ? a.x1 : a.x0;
   double* xn_ = cur1 ? a.x0 : a.x1;
@@ -1293,8 +1295,8 @@ static pf_status_t run_solve(pf_mesh_s* m, int kind, const void* H, const void* 
   bool setup = !o->resume;   // the first round of a solve is its set-up restart
   if (setup) {
     timer_begin(m, 2, s);
-    hipLaunchKernelGGL(k_dmg_init, dim3((m->n_inst + 63) / 64), dim3(64), 0, s, m->dw.ctl, m->n_inst, kind,
-                       o->monotone);
+    hipLaunchKernelGGL(k_dmg_init, dim3((m->n_inst + 63) / 64), dim3(64), 0, s, m->dw.ctl, m->dw.fix, m->n_inst,
+                       kind, o->monotone, o->precond);
     timer_end(m, 2, s);
   }
   if (kind == CG_QP) {

@@ -117,6 +117,7 @@ struct Ctl {
   int32_t inner;      // CG iterations since the last restart or check
   int32_t wbuf;       // which half of the held-set pair is current
   int32_t outer;      // active-set updates so far
+  int32_t deg;        // polynomial degree that the solve's set-up assembled rows for
   double rz, alpha, beta, amax, resid, pq;
   double ref;         // scale of the stopping test (1 for the damage QP, max |b_i|/A_ii for linear solves)
 };
@@ -159,6 +160,9 @@ struct CgShape {
   int32_t max_row_own;                 // owned nodes
   bool extra_pairs;                    // some rows are longer than the base pairs
 };
+// The degree that an instance runs at: the asked one as far as its tiles hold
+// rings for it, or its default.
+constexpr int cg_degree(const InstFix& f, int ask) { return ask ? (ask < f.dmax ? ask : f.dmax) : f.ddef; }
 // The rows of a tile whose sums a pass of degree `deg` uses: the owned ones in a
 // restart or check, else those up to ring deg - 1.  Their columns are what the
 // pass holds in LDS (nl[1], nl[deg] nodes); a lane past them multiplies by
