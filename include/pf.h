@@ -366,10 +366,11 @@ pf_status_t pf_energies_static(pf_mesh_t m, const pf_params_t* p, const pf_state
  *        its per-instance dGc output is then sum_e phi_e dL/dGc_e (the
  *        derivative along a common scaling of the field).
  * The explicit step does not depend on Gc.  A set-up call: the first call
- * with a field allocates n_te values of the mesh dtype in the handle; the
- * field is read back to the host and checked (PF_ERR_ARG names the first bad
- * element and leaves the previous field in place), and the call synchronises
- * `stream`.  Work already enqueued on other streams must be ordered before
+ * with a field allocates n_te values of the mesh dtype and a second copy of
+ * the damage rows' stiffness part in the handle; the field is read back to the
+ * host and checked (PF_ERR_ARG names the first bad element and leaves the
+ * previous field in place), and the call synchronises `stream` (NULL enqueues
+ * nothing).  Work already enqueued on other streams must be ordered before
  * this call by the caller; HIP graphs captured before the call are not
  * updated (capture them again).
  */

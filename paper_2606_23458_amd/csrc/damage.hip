@@ -271,8 +271,8 @@ __device__ __forceinline__ void finish_pass(const DmgArgs<T>& a, int inst, doubl
 }
 
 // Stiffness part of the rows, sum phi_e K^e_ij over an entry's elements: once
-// per handle, and again when the toughness field changes (phi_e = 1 without
-// one).  The element operator's entries are kap phi_e K^e + mA (1 + delta_kl)
+// per handle with phi_e = 1, and in a copy of its own whenever a toughness
+// field is set, so that a graph captured with or without one keeps its rows.  The element operator's entries are kap phi_e K^e + mA (1 + delta_kl)
 // with K^e given by its off-diagonals K01, K02, K12 (its rows sum to zero).
 template <typename T>
 __global__ __launch_bounds__(kBlock) void k_rows_stiffness(DevMesh dm, DevRows dr) {
@@ -298,11 +298,11 @@ __global__ __launch_bounds__(kBlock) void k_rows_stiffness(DevMesh dm, DevRows d
     static_cast<T*>(dr.earea)[tp->el0 + i] = area[dr.ete[tp->el0 + i]];
 }
 
-void rows_stiffness(pf_mesh_s* m, hipStream_t s) {
-  if (m->dtype == PF_F64)
-    hipLaunchKernelGGL(k_rows_stiffness<double>, dim3(m->dr.n_tiles), dim3(kBlock), 0, s, m->dm, m->dr);
+void rows_stiffness(pf_dtype_t dtype, const DevMesh& dm, const DevRows& dr, hipStream_t s) {
+  if (dtype == PF_F64)
+    hipLaunchKernelGGL(k_rows_stiffness<double>, dim3(dr.n_tiles), dim3(kBlock), 0, s, dm, dr);
   else
-    hipLaunchKernelGGL(k_rows_stiffness<float>, dim3(m->dr.n_tiles), dim3(kBlock), 0, s, m->dm, m->dr);
+    hipLaunchKernelGGL(k_rows_stiffness<float>, dim3(dr.n_tiles), dim3(kBlock), 0, s, dm, dr);
 }
 
 // The first restart of a solve: the rows of this solve, A_ij = kap S_ij + the

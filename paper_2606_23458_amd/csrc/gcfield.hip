@@ -2,7 +2,9 @@
 // Gc(x) inverse problem named as the next step in Sec. 4).  The handle keeps
 // phi in tile-element order next to the element geometry, so the damage,
 // adjoint and energy kernels read it with the same coalesced index as the
-// geometry; the adjoint can also accumulate dL/dGc_e per element.
+// geometry; the adjoint can also accumulate dL/dGc_e per element.  The damage
+// rows' stiffness part, which carries phi, is kept once with the field and once
+// without: a graph captured before a call names the arrays of its own kind.
 #include <cmath>
 #include <vector>
 
@@ -38,12 +40,9 @@ extern "C" pf_status_t pf_set_gc_field(pf_mesh_t m, const void* phi, double* dgc
   if (!m) return fail(PF_ERR_ARG, "NULL mesh");
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (!phi) {
-    if (m->dm.gcs) {
-      m->dm.gcs = nullptr;
-      rows_stiffness(m, s);   // the damage rows without the field
-      PF_HIP(hipGetLastError());
-      PF_HIP(hipStreamSynchronize(s));
-    }
+    m->dm.gcs = nullptr;
+    m->dr.sv = m->sv_plain;
+    m->dr.xsv = m->xsv_plain;
     m->dgc_field = dgc_field;
     return PF_OK;
   }
@@ -51,15 +50,21 @@ extern "C" pf_status_t pf_set_gc_field(pf_mesh_t m, const void* phi, double* dgc
   const size_t w = f64 ? sizeof(double) : sizeof(float);
   pf_status_t st = f64 ? check_field<double>(phi, m->n_elems, s) : check_field<float>(phi, m->n_elems, s);
   if (st != PF_OK) return st;
-  if (!m->gcs_buf) {
-    void* p = nullptr;
-    const size_t bytes = std::max<size_t>(size_t(m->n_te) * w, 16);
+  auto once = [&](void*& p, size_t bytes) {
+    if (p) return PF_OK;
+    bytes = std::max<size_t>(bytes, 16);
     const hipError_t e = hipMalloc(&p, bytes);
-    if (e != hipSuccess) return fail(PF_ERR_NOMEM, std::string("hipMalloc: ") + hipGetErrorString(e));
+    if (e != hipSuccess) {
+      p = nullptr;
+      return fail(PF_ERR_NOMEM, std::string("hipMalloc: ") + hipGetErrorString(e));
+    }
     m->allocs.push_back(p);   // freed with the handle
     m->device_bytes += bytes;
-    m->gcs_buf = p;
-  }
+    return PF_OK;
+  };
+  if ((st = once(m->gcs_buf, size_t(m->n_te) * w)) != PF_OK || (st = once(m->sv_field, m->sv_bytes)) != PF_OK ||
+      (st = once(m->xsv_field, m->xsv_bytes)) != PF_OK)
+    return st;
   const dim3 grid((m->n_te + kBlock - 1) / kBlock), block(kBlock);
   if (f64)
     hipLaunchKernelGGL(k_gcs_gather<double>, grid, block, 0, s, m->dm.te_gid, static_cast<const double*>(phi),
@@ -68,11 +73,17 @@ extern "C" pf_status_t pf_set_gc_field(pf_mesh_t m, const void* phi, double* dgc
     hipLaunchKernelGGL(k_gcs_gather<float>, grid, block, 0, s, m->dm.te_gid, static_cast<const float*>(phi),
                        static_cast<float*>(m->gcs_buf), m->n_te);
   PF_HIP(hipGetLastError());
-  m->dm.gcs = m->gcs_buf;
-  rows_stiffness(m, s);   // the damage rows with the field
+  DevMesh dm = m->dm;
+  DevRows dr = m->dr;
+  dm.gcs = m->gcs_buf;
+  dr.sv = m->sv_field;
+  dr.xsv = m->xsv_field;
+  rows_stiffness(m->dtype, dm, dr, s);
   PF_HIP(hipGetLastError());
   // the caller may release phi on return
   PF_HIP(hipStreamSynchronize(s));
+  m->dm = dm;
+  m->dr = dr;
   m->dgc_field = dgc_field;
   return PF_OK;
 }

@@ -706,10 +706,14 @@ extern "C" pf_status_t pf_mesh_create(const pf_mesh_desc_t* inst, int32_t n_inst
   for (void** v : vecs2)
     if ((st = dev_alloc(m, 2 * nb, v)) != PF_OK) { free_all(m); delete m; return st; }
   if ((st = dev_alloc(m, rows.ete.size() * w, &m->dr.earea)) != PF_OK) { free_all(m); delete m; return st; }
-  if ((st = dev_alloc(m, rows.ac.size() * 2 * w, &m->dr.sv)) != PF_OK) { free_all(m); delete m; return st; }
-  if ((st = dev_alloc(m, rows.xac.size() * 2 * w, &m->dr.xsv)) != PF_OK) { free_all(m); delete m; return st; }
-  if ((st = dev_alloc(m, rows.ac.size() * 2 * w, &m->dr.av)) != PF_OK) { free_all(m); delete m; return st; }
-  if ((st = dev_alloc(m, rows.xac.size() * 2 * w, &m->dr.xav)) != PF_OK) { free_all(m); delete m; return st; }
+  m->sv_bytes = rows.ac.size() * 2 * w;
+  m->xsv_bytes = rows.xac.size() * 2 * w;
+  if ((st = dev_alloc(m, m->sv_bytes, &m->sv_plain)) != PF_OK) { free_all(m); delete m; return st; }
+  if ((st = dev_alloc(m, m->xsv_bytes, &m->xsv_plain)) != PF_OK) { free_all(m); delete m; return st; }
+  m->dr.sv = m->sv_plain;
+  m->dr.xsv = m->xsv_plain;
+  if ((st = dev_alloc(m, m->sv_bytes, &m->dr.av)) != PF_OK) { free_all(m); delete m; return st; }
+  if ((st = dev_alloc(m, m->xsv_bytes, &m->dr.xav)) != PF_OK) { free_all(m); delete m; return st; }
   if ((st = dev_alloc(m, rows.tiles.size() * sizeof(int32_t), (void**)&m->dr.idle)) != PF_OK) { free_all(m); delete m; return st; }
   void* tmpp;
   if ((st = dev_alloc(m, size_t(m->n_elems) * w, &m->dw.hbar)) != PF_OK) { free_all(m); delete m; return st; }
@@ -794,7 +798,7 @@ extern "C" pf_status_t pf_mesh_create(const pf_mesh_desc_t* inst, int32_t n_inst
   }
   m->device = dev;
   damage_plan(m);
-  rows_stiffness(m, static_cast<hipStream_t>(stream));
+  rows_stiffness(dtype, m->dm, m->dr, static_cast<hipStream_t>(stream));
   if (const hipError_t el = hipGetLastError(); el != hipSuccess) { free_all(m); delete m; return hip_fail(el, "k_rows_stiffness launch"); }
   // device address of the static partials of pf_energies_static on this device
   if ((st = energy_scratch_setup(dev)) != PF_OK) { free_all(m); delete m; return st; }

@@ -283,7 +283,12 @@ struct pf_mesh_s {
   hipEvent_t poll_ev = nullptr;      // marks the copy of the control blocks (convergence polls)
   bool timing = false;
   pf::Timer timers[5];
-  void* gcs_buf = nullptr;           // device storage of dm.gcs (allocated by the first pf_set_gc_field)
+  // device storage of dm.gcs and of the rows' stiffness part with a toughness
+  // field (allocated by the first pf_set_gc_field), and that part without one
+  void* gcs_buf = nullptr;
+  void* sv_field = nullptr; void* xsv_field = nullptr;
+  void* sv_plain = nullptr; void* xsv_plain = nullptr;
+  size_t sv_bytes = 0, xsv_bytes = 0;
   double* dgc_field = nullptr;       // caller's per-element dL/dGc_e accumulator, or null
   void* load_buf = nullptr;          // device storage of the loads (allocated by the first pf_set_loading)
   pf::LoadDev ld{};                  // the registered loads (ld.par null: none)
@@ -357,8 +362,9 @@ pf_status_t check_state(const pf_state_t* s, bool need_d, bool need_H, const cha
 // Resolve, once per device (that device current), the device address of the
 // static partials array of pf_energies_static (energy.hip).
 pf_status_t energy_scratch_setup(int device);
-// The stiffness part of the rows, from the mesh and the toughness field (damage.hip).
-void rows_stiffness(pf_mesh_s* m, hipStream_t s);
+// The stiffness part of the rows into dr.sv and dr.xsv, with the toughness field
+// dm.gcs (NULL: without one) (damage.hip).
+void rows_stiffness(pf_dtype_t dtype, const DevMesh& dm, const DevRows& dr, hipStream_t s);
 // The Chebyshev iteration's steps for spectra in (0, lmax] (damage.hip).
 void chebyshev_steps(InstFix& f, double lmax);
 // Choose the element chunks of the damage set-up pass for this handle (damage.hip).
