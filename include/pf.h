@@ -130,7 +130,10 @@ typedef struct {
                                 r_i/A_ii pointing inward by more than tol/4
                                 (held nodes beyond that are released); with a
                                 polynomial preconditioner a CG run goes on
-                                until |M r| <= tol as well */
+                                until |M r| <= tol as well.  The damage solve
+                                tests d as the mesh dtype holds it; an adjoint
+                                solve's multiplier is tested in FP64 and then
+                                rounded */
     int32_t max_iter;        /* CG rounds per solve, >= 1 (a round is one pass
                                 over the tiles and one reduction) */
     int32_t check_every;     /* > 0: synchronise the stream to stop early: first

@@ -111,7 +111,8 @@ struct DmgArgs {
   const uint8_t* __restrict__ win;   // linear: held set (internal order)
   // vectors in row order
   double* x0; double* x1;        // iterate pair: FP64 in either mode, so that its rounding does not bound the
-                                 // true residual (in FP32 a linear solve's would sit at its tolerance)
+                                 // true residual (in FP32 a linear solve's would sit at its tolerance); a
+                                 // damage solve's restarts and checks round it to T, the result's type
   Two<T>* rs0; Two<T>* rs1;      // (r, s = A p) pair
   Two<T>* wz0; Two<T>* wz1;      // (w = A z, z) pair
   T* p;                          // search direction (read and written by the owner only)
@@ -671,7 +672,8 @@ __global__ __launch_bounds__(kBlock, RPT <= 4 ? (RPT <= 2 ? 4 : 3) : 1) void k_c
         const T rh = r - T(c->amax) * rsn[q].y;
         v = clamp01<double>(xh + double(T(kExpandStep) * fabs(dm) * rh), double(a.lbr[q]));
       }
-      return v;
+      // what the damage solve may end on is what it delivers: d is a T
+      return qp ? double(T(v)) : v;
     };
 #pragma unroll
     for (int k = 0; k < RPT; ++k) {
