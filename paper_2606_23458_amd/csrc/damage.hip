@@ -320,7 +320,7 @@ __global__ __launch_bounds__(kBlock) void k_cg_setup(DmgArgs<T> a) {
   const int tile = tile_of_block(a.dr.n_tiles);
   const RowTile* const tp = a.dr.tiles + tile;
   const int n_own = tp->nl[0], nall = tp->nl[1], node0 = tp->node0, halo0 = tp->halo0, slice0 = tp->slice0;
-  const int el0 = tp->el0;
+  const int64_t el0 = tp->el0;
   const int inst = tp->inst;
   const Ctl* const c = a.ctl + inst;
   const InstP<T>* const P = a.ip + inst;

@@ -51,7 +51,8 @@ struct RowTile {
   int32_t slice0;                    // first 64-row slice
   int32_t nslice;
   int32_t inst;
-  int32_t el0;                       // offset into the element lists
+  int64_t el0;                       // offset into the element lists (10 elements per node with eight rings, so
+                                     // past 32 bits from 215 million nodes on)
   int32_t nel[kMaxRing];             // elements at a node up to ring k (those of each further ring at the end)
 };
 

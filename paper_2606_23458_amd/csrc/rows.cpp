@@ -295,7 +295,7 @@ bool row_plan_add(RowPlan& rp, const RowMesh& rm, int inst, size_t width, size_t
     r.slice0 = int32_t(slice);
     r.nslice = nslices(t);
     r.inst = inst;
-    r.el0 = int32_t(el);
+    r.el0 = int64_t(el);
     for (int k = 0; k < kMaxRing; ++k) r.nel[k] = t.nel[std::min(k, dmax - 1)];
     el += size_t(r.nel[dmax - 1]);
     rp.tiles.push_back(r);

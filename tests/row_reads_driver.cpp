@@ -19,6 +19,11 @@ using namespace pf;
     }                                                                         \
   } while (0)
 
+// A handle of 215 million nodes in plates of 128 owned nodes and degree 8 lists more than 2^31
+// elements, too many to build here; its other offsets stay below: at most 5 ring nodes and 5/64
+// slices per node, of 3.6e8 nodes.
+static_assert(sizeof(RowTile::el0) == 8, "offsets into the element lists need 64 bits");
+
 struct Plate {
   int nx, ny, fan;       // a grid, or `fan` triangles around one node
   bool diag;             // random diagonals
