@@ -61,10 +61,10 @@
 //   k_dmg_red  one workgroup per instance combines its tiles' partials in a
 //              fixed order (bitwise reproducible results) and advances the
 //              instance's state.
-// For instances of up to kFuseMaxTiles tiles the combination instead runs at
-// the end of the pass, in the instance's last workgroup to finish (arrivals
-// counted by integer atomics; same order, same bits), so a round is a single
-// launch.
+// For instances of few tiles (rows.cpp: combine_in_pass) the combination
+// instead runs at the end of the pass, in the instance's last workgroup to
+// finish (arrivals counted by integer atomics; same order, same bits), so a
+// round is a single launch.
 // (r, s), (w, z) and x are ping-pong pairs: a pass reads one half and writes
 // the other, so ring reads never race with the owners' writes.  No
 // floating-point atomics and no device-wide fences are used.  Linear mode
@@ -887,7 +887,6 @@ __global__ __launch_bounds__(kBlock, RPT <= 4 ? (RPT <= 2 ? 4 : 3) : 1) void k_c
 // tile's partials per thread at a time past this die's L2 (the partials of the
 // running kernel) and keeps the pass's register count.
 constexpr int kRedBatch = 8;
-constexpr int kFuseMaxTiles = 512;   // instances combined in the pass's last workgroup (see run_solve)
 __device__ __forceinline__ double combine_partials(double* part, size_t nt, int tile0, int ntiles, double* red) {
   const int tile_end = tile0 + ntiles;
   double v[8] = {0.0, INFINITY, 0.0, 0.0, -INFINITY, 0.0, 0.0, 0.0};
@@ -1219,11 +1218,7 @@ static DmgArgs<T> dmg_args(pf_mesh_s* m, int kind, const void* H, const void* d_
   a.tol = o->tol;
   a.max_iter = o->max_iter;
   a.deg = o->precond;
-  // Instances of up to kFuseMaxTiles tiles combine their partials in the pass's
-  // last workgroup (one launch per round: the last workgroup's combination
-  // takes one memory round trip per 256 tiles, which beats the separate
-  // reduction launch only while there are few)
-  a.fuse = m->max_inst_tiles <= kFuseMaxTiles ? 1 : 0;
+  a.fuse = m->fuse ? 1 : 0;
   a.arrive = m->dw.arrive;
   a.nch = 1;
   return a;
@@ -1245,7 +1240,7 @@ static CgKernel<T> cg_kernel_of(const pf_mesh_s* m, bool fuse, bool setup) {
 }
 template <typename T>
 static CgKernel<T> cg_kernel(const pf_mesh_s* m, int deg, bool setup) {
-  const bool fuse = m->max_inst_tiles <= kFuseMaxTiles;
+  const bool fuse = m->fuse;
   const bool one = m->cg.max_row_own <= kBlock;
   switch (cg_rows(m->cg, deg)) {
     case 1: return cg_kernel_of<T, 1, 1>(m, fuse, setup);

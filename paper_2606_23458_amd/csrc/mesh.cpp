@@ -756,11 +756,11 @@ extern "C" pf_status_t pf_mesh_create(const pf_mesh_desc_t* inst, int32_t n_inst
       c[k].dmax = rows.dmax[k];
       c[k].ddef = rows.ddef[k];
       chebyshev_steps(c[k], lmax[k]);
-      m->max_inst_tiles = std::max(m->max_inst_tiles, c[k].ntiles);
       c[k].cbase = ncnt;
       c[k].ctop = ncnt + (c[k].nrt + kArriveGroup - 1) / kArriveGroup;
       ncnt = c[k].ctop + 1;
     }
+    m->fuse = combine_in_pass(*std::max_element(rows.nrt.begin(), rows.nrt.end()), m->dr.n_tiles, tile_nodes);
     const size_t cbytes = size_t(ncnt) * kArriveStride * sizeof(uint32_t);
     if ((st = dev_alloc(m, cbytes, &tmpp)) != PF_OK) { free_all(m); delete m; return st; }
     m->dw.arrive = static_cast<uint32_t*>(tmpp);

@@ -247,7 +247,7 @@ struct pf_mesh_s {
   int32_t n_inst = 0, n_nodes = 0, n_elems = 0, n_tiles = 0, n_te = 0;
   int32_t max_tile_nodes = 0, max_tile_elems = 0, max_own = 0, max_lds_explicit = 0;
   int32_t max_corner = 0;
-  int32_t max_inst_tiles = 0;        // tiles of the largest instance
+  bool fuse = false;                 // a round's partials are combined in the pass's last workgroup (damage.hip)
   size_t adj_lds_damage = 0;         // LDS of the adjoint kernels (set by the first backward step)
   size_t adj_lds_explicit = 0;
   int32_t adj_chunks = 0;            // element chunks of the explicit step's adjoint (0: not yet chosen)
@@ -344,6 +344,9 @@ void rcb(std::vector<int32_t>& ids, size_t lo, size_t hi, const double* xy, size
          std::vector<std::pair<size_t, size_t>>& leaves);
 
 CgShape cg_shape(const RowPlan& rp, size_t width);
+// Whether the last workgroup of a pass combines its instance's partials (else a
+// launch of its own does), by the row tiles of the largest instance and of all.
+bool combine_in_pass(int32_t inst_tiles, int32_t all_tiles, int32_t tile_nodes);
 // Rows per thread of the CG pass: for the rows, and for the fixed distance
 // between the two halves of the vector in LDS.
 int cg_rows(const CgShape& c, int deg);

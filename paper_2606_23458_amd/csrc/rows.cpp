@@ -392,6 +392,20 @@ CgShape cg_shape(const RowPlan& rp, size_t width) {
   return c;
 }
 
+// The combination in a pass's last workgroup takes one memory round trip per 256
+// tiles of the instance, the separate launch about 5 us; in a large batch the
+// arrivals of all tiles cost more than one launch.  us per polled step, in the
+// pass / by a launch of its own, by row tiles:
+//   one plate  FP64  260  212 / 235    516  293 / 317    961  426 / 429   1134  480 / 469   2055  681 / 648
+//              FP32  329  145 / 155    516  152 / 161    961  179 / 185   1134  207 / 205   2055  277 / 269
+//   batches    FP32  8 x 130   186 / 196   16 x 130   251 / 262   3 x 516   228 / 230
+//                    16 uneven plates, 3600 in all   406 / 401   64 uneven plates, 13500   1280 / 1232
+// A caller's own tiles of under 128 nodes keep the limit, and the launches per
+// round, that they had before the row tiles (519 of 64 nodes: 407 / 443).
+bool combine_in_pass(int32_t inst_tiles, int32_t all_tiles, int32_t tile_nodes) {
+  return inst_tiles <= (tile_nodes < 128 ? 512 : 1024) && all_tiles <= 3072;
+}
+
 int cg_rows(const CgShape& c, int deg) {
   const int rpt = std::max((c.max_rows[deg] + kBlock - 1) / kBlock, (c.max_nodes[deg] + kBlock - 1) / kBlock - 1);
   if (rpt > 4) return 8;
