@@ -571,7 +571,6 @@ __global__ __launch_bounds__(kBlock, RPT <= 4 ? (RPT <= 2 ? 4 : 3) : 1) void k_c
 
   extern __shared__ __align__(16) unsigned char smem[];
   const int nall = tp->nl[xpass ? 1 : deg];   // nodes whose values the pass needs
-  const int nrow = cg_row_limit(*tp, deg, xpass);   // rows whose columns lie among them
   T* const ya = reinterpret_cast<T*>(smem);   // the vector the pass multiplies by A, two halves
   // the other half stands at a fixed distance, so that a column's address serves
   // both (degree 1 has one vector, of any length)
@@ -600,16 +599,14 @@ __global__ __launch_bounds__(kBlock, RPT <= 4 ? (RPT <= 2 ? 4 : 3) : 1) void k_c
       longest = max(longest, x.y);
 #pragma unroll
       for (int q = 0; q < kRowPairs; ++q) {
-        const uint32_t cc = a.dr.ac[at + q * 64];
-        ac[k][q] = tid + k * kBlock < nrow ? cc : 0u;
+        ac[k][q] = a.dr.ac[at + q * 64];
         av[k][q] = AV[at + q * 64];
       }
       if constexpr (PAIRS > kRowPairs) {
         // a slice without extra pairs gets entries of 0
         const size_t xo = size_t(xk[k] > 0 ? xb[k] : 0) * 64 + lane;
         const Two<T> v = XAV[xo];
-        const uint32_t cc = a.dr.xac[xo];
-        ac[k][kRowPairs] = xk[k] > 0 && tid + k * kBlock < nrow ? cc : 0u;
+        ac[k][kRowPairs] = xk[k] > 0 ? a.dr.xac[xo] : 0u;
         av[k][kRowPairs] = Two<T>{xk[k] > 0 ? v.x : T(0), xk[k] > 0 ? v.y : T(0)};
       }
       if (k < OWN) rsu[k] = a.rsum[node0 + min(tid + k * kBlock, n_own - 1)];
@@ -638,7 +635,7 @@ __global__ __launch_bounds__(kBlock, RPT <= 4 ? (RPT <= 2 ? 4 : 3) : 1) void k_c
       for (int e = PAIRS - kRowPairs; e < xk[k]; ++e) {
         const size_t xo = (size_t(xb[k]) + e) * 64 + lane;
         const Two<T> v = XAV[xo];
-        const uint32_t cx = a.dr.xac[xo], cc = tid + k * kBlock < nrow ? cx : 0u;
+        const uint32_t cc = a.dr.xac[xo];
         s[k] += f(k, v.x, y[cc & 0xffffu]);
         s[k] += f(k, v.y, y[cc >> 16]);
       }
@@ -819,7 +816,7 @@ __global__ __launch_bounds__(kBlock, RPT <= 4 ? (RPT <= 2 ? 4 : 3) : 1) void k_c
     // One step of the Chebyshev iteration from the values in ys to yd, over the
     // rows that the steps still to come read.  A wave takes those of its rows
     // whose slice holds any; what it computes past the last of them is not
-    // read (its columns lie in the pass's LDS, see cg_row_limit).
+    // read (its columns lie in the pass's LDS, see cg_shape).
     auto step = [&](int j, const T* ys, T* yd) {
       const int lim = __builtin_amdgcn_readlane(steps_nl, deg - j);
       const T c1 = lane_value(steps_c1, j - 1), c2 = lane_value(steps_c2, j - 1);
@@ -1241,7 +1238,7 @@ static CgKernel<T> cg_kernel_of(const pf_mesh_s* m, bool fuse, bool setup) {
 template <typename T>
 static CgKernel<T> cg_kernel(const pf_mesh_s* m, int deg, bool setup) {
   const bool fuse = m->fuse;
-  const bool one = m->cg.max_row_own <= kBlock;
+  const bool one = cg_own_rows(m->cg, deg) == 1;
   switch (cg_rows(m->cg, deg)) {
     case 1: return cg_kernel_of<T, 1, 1>(m, fuse, setup);
     case 2: return cg_kernel_of<T, 2, 1>(m, fuse, setup);

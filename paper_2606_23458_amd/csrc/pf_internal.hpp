@@ -156,20 +156,15 @@ struct DevMesh {
 struct CgShape {
   int32_t max_rows[kAskRing + 1];      // rows
   int32_t max_nodes[kAskRing + 1];     // nodes, of tiles with a polynomial
-  int32_t max_rlds[kAskRing + 1];      // values in LDS without a polynomial, or in a restart
-  int32_t max_slds[2][kAskRing + 1];   // and in the set-up pass with its elements in one and in two chunks
+  int32_t max_first[kAskRing + 1];     // values that any lane reads of the vector in a restart, or without a polynomial
+  int32_t max_cols[kAskRing + 1];      // and of either half of it with one
+  int32_t max_slds[2][kAskRing + 1];   // values in LDS in the set-up pass with its elements in one and in two chunks
   int32_t max_row_own;                 // owned nodes
   bool extra_pairs;                    // some rows are longer than the base pairs
 };
 // The degree that an instance runs at: the asked one as far as its tiles hold
 // rings for it, or its default.
 constexpr int cg_degree(const InstFix& f, int ask) { return ask ? (ask < f.dmax ? ask : f.dmax) : f.ddef; }
-// The rows of a tile whose sums a pass of degree `deg` uses: the owned ones in a
-// restart or check, else those up to ring deg - 1.  Their columns are what the
-// pass holds in LDS (nl[1], nl[deg] nodes); a lane past them multiplies by
-// column 0, since its row's columns may lie on any ring.
-constexpr int cg_row_limit(const RowTile& t, int deg, bool xpass) { return xpass ? t.nl[0] : t.nl[deg - 1]; }
-
 // Device view of the rows of the damage operator.  The nodes are numbered
 // once more for the damage solve ("row order", pos): row tiles own contiguous
 // runs of positions, chosen for the CG passes alone, so neither the caller's
@@ -325,6 +320,7 @@ struct RowPlan {
   std::vector<uint32_t> ac, xac, ete;
   std::vector<uint2> code, xcode;
   std::vector<int2> xs;
+  std::vector<uint16_t> cmax;                // [slice] the largest column of its rows (host only)
   std::vector<int32_t> rt0, nrt, dmax, ddef; // per instance
 };
 struct RowMesh {
@@ -350,6 +346,7 @@ bool combine_in_pass(int32_t inst_tiles, int32_t all_tiles, int32_t tile_nodes);
 // Rows per thread of the CG pass: for the rows, and for the fixed distance
 // between the two halves of the vector in LDS.
 int cg_rows(const CgShape& c, int deg);
+int cg_own_rows(const CgShape& c, int deg);   // of them owned ones
 // LDS bytes of a pass: the vector being multiplied, twice for a polynomial;
 // nch > 0: of the set-up pass, the start and the elements' values.
 size_t cg_lds(const CgShape& c, int deg, int nch, size_t width);

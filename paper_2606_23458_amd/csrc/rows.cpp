@@ -307,6 +307,7 @@ bool row_plan_add(RowPlan& rp, const RowMesh& rm, int inst, size_t width, size_t
     halo += size_t(r.nl[dmax] - r.nl[0]);
   }
   rp.halo.resize(halo);
+  rp.cmax.resize(slice, 0);
   rp.ac.resize(slice * kRowPairs * 64, 0);
   constexpr uint32_t no2 = kNoCode | (kNoCode << 16);
   rp.code.resize(slice * kRowPairs * 64, uint2{no2, no2});
@@ -351,6 +352,7 @@ bool row_plan_add(RowPlan& rp, const RowMesh& rm, int inst, size_t width, size_t
         uint2& code = base ? rp.code[at] : rp.xcode[at];
         const uint32_t cc = code16(g.c0[size_t(q)]) | (code16(g.c1[size_t(q)]) << 16);
         const uint32_t l = local(g.nbr[size_t(q)]);
+        rp.cmax[s] = std::max(rp.cmax[s], uint16_t(l));
         if (k % 2 == 0) {
           ac |= l;
           code.x = cc;
@@ -373,20 +375,36 @@ bool row_plan_add(RowPlan& rp, const RowMesh& rm, int inst, size_t width, size_t
   return true;
 }
 
+// Every lane multiplies the row that it loads, also one past those that its pass
+// uses (the sum is then discarded), and such a row's columns lie on any ring: the
+// LDS holds whatever they reach.  That costs a few KB at degrees 1 and 2;
+// masking the columns in the pass cost registers and 2 % of a gradient.
 CgShape cg_shape(const RowPlan& rp, size_t width) {
   CgShape c{};
   c.extra_pairs = !rp.xac.empty();
+  // an instance whose tiles hold fewer rings runs with its own largest degree
+  auto degree = [&](const RowTile& t, int dg) {
+    return dg == 0 ? rp.ddef[size_t(t.inst)] : std::min(dg, rp.dmax[size_t(t.inst)]);
+  };
   for (const RowTile& t : rp.tiles) {
     c.max_row_own = std::max(c.max_row_own, t.nl[0]);
     for (int dg = 0; dg <= kAskRing; ++dg) {
-      // an instance whose tiles hold fewer rings runs with its own largest degree
-      const int de = dg == 0 ? rp.ddef[size_t(t.inst)] : std::min(dg, rp.dmax[size_t(t.inst)]);
+      const int de = degree(t, dg);
       c.max_rows[dg] = std::max(c.max_rows[dg], t.nl[de - 1]);
       if (de > 1) c.max_nodes[dg] = std::max(c.max_nodes[dg], t.nl[de]);
-      // the vector of a pass without a polynomial, or the FP64 iterate of a restart
-      c.max_rlds[dg] = std::max(c.max_rlds[dg], t.nl[1] * int32_t(sizeof(double) / width));
       c.max_slds[0][dg] = std::max(c.max_slds[0][dg], t.nl[1] + 2 * (1 + t.nel[de - 1]));
       c.max_slds[1][dg] = std::max(c.max_slds[1][dg], t.nl[1] + 1 + t.nel[de - 1]);
+    }
+  }
+  for (int dg = 0; dg <= kAskRing; ++dg) {
+    const int own = cg_own_rows(c, dg) * kWaves, all = cg_rows(c, dg) * kWaves;   // slices
+    for (const RowTile& t : rp.tiles) {
+      c.max_first[dg] = std::max(c.max_first[dg], t.nl[1]);
+      for (int q = 0; q < std::min(t.nslice, all); ++q) {
+        const int32_t n = 1 + rp.cmax[size_t(t.slice0 + q)];
+        if (q < own) c.max_first[dg] = std::max(c.max_first[dg], n);
+        if (degree(t, dg) > 1) c.max_cols[dg] = std::max(c.max_cols[dg], n);
+      }
     }
   }
   return c;
@@ -412,10 +430,17 @@ int cg_rows(const CgShape& c, int deg) {
   return c.max_row_own <= kBlock ? std::max(rpt, 1) : std::max(rpt, 3);
 }
 
+int cg_own_rows(const CgShape& c, int deg) {
+  const int rpt = cg_rows(c, deg);
+  return rpt <= 3 && c.max_row_own <= kBlock ? 1 : rpt;
+}
+
 size_t cg_lds(const CgShape& c, int deg, int nch, size_t width) {
   if (nch > 0) return size_t(c.max_slds[nch - 1][deg]) * width;
-  const int halves = c.max_nodes[deg] > 0 ? 2 * (cg_rows(c, deg) + 1) * kBlock : 0;
-  return size_t(std::max(halves, c.max_rlds[deg])) * width;
+  const size_t half = size_t(cg_rows(c, deg) + 1) * kBlock;
+  // a restart's iterate is FP64
+  return std::max(size_t(c.max_first[deg]) * sizeof(double),
+                  c.max_nodes[deg] > 0 ? (half + std::max(half, size_t(c.max_cols[deg]))) * width : 0);
 }
 
 }  // namespace pf

@@ -67,28 +67,30 @@ static void add(RowPlan& rp, const Plate& c, int inst, size_t width) {
 static void check(const RowPlan& rp, size_t width) {
   const CgShape cg = cg_shape(rp, width);
   for (int ask = 0; ask <= kAskRing; ++ask) {
-    const int rpt = cg_rows(cg, ask);
-    const long lds = long(cg_lds(cg, ask, 0, width)), half = long((rpt + 1) * kBlock * int(width));
+    const int rpt = cg_rows(cg, ask), own = cg_own_rows(cg, ask);
+    const long w = long(width), lds = long(cg_lds(cg, ask, 0, width)), half = long((rpt + 1) * kBlock) * w;
+    CHECK(lds <= 163840 - 2048 && own * kBlock >= cg.max_row_own && own <= rpt);
     for (const RowTile& t : rp.tiles) {
       const int deg = ask ? std::min(ask, rp.dmax[size_t(t.inst)]) : rp.ddef[size_t(t.inst)];
       CHECK(rpt * kBlock >= t.nl[deg - 1]);
-      // the vectors' own nodes, and the other half's stores of a polynomial
-      CHECK(long(t.nl[1]) * 8 <= lds && long(t.nl[deg]) * long(width) <= (deg > 1 ? half : lds));
+      // the vectors' own nodes, and what a polynomial's steps store
+      CHECK(long(t.nl[1]) * 8 <= lds && long(t.nl[deg]) * w <= (deg > 1 ? half : lds));
       if (deg > 1) CHECK(2 * half <= lds && rpt <= kRowMax / kBlock);
       for (int i = 0; i < rpt * kBlock; ++i) {
         // the row that a lane loads (past the last slice: that slice's), and the columns it multiplies by
         const size_t s = size_t(t.slice0) + size_t(std::min(i / 64, t.nslice - 1)), lane = size_t(i % 64);
-        auto pair = [&](uint32_t cc, bool xpass) {
-          if (i >= cg_row_limit(t, deg, xpass)) cc = 0;
+        auto pair = [&](uint32_t cc) {
           for (uint32_t col : {cc & 0xffffu, cc >> 16}) {
-            CHECK(int(col) < t.nl[xpass ? 1 : deg]);
-            CHECK(xpass ? long(col + 1) * 8 <= lds : long(col + 1) * long(width) <= (deg > 1 ? half : lds));
+            // rows that a pass uses find their columns among the nodes it holds
+            if (i < t.nl[0]) CHECK(int(col) < t.nl[1]);
+            if (i < t.nl[deg - 1]) CHECK(int(col) < t.nl[deg]);
+            // every row's are read: in a restart and for A z (owned rows per thread), in a step (all)
+            if (i < own * kBlock) CHECK(long(col + 1) * 8 <= lds && long(col + 1) * w <= lds);
+            if (deg > 1) CHECK(half + long(col + 1) * w <= lds);
           }
         };
-        for (bool xpass : {true, false}) {
-          for (int q = 0; q < kRowPairs; ++q) pair(rp.ac[(s * kRowPairs + size_t(q)) * 64 + lane], xpass);
-          for (int q = 0; q < rp.xs[s].y; ++q) pair(rp.xac[(size_t(rp.xs[s].x) + size_t(q)) * 64 + lane], xpass);
-        }
+        for (int q = 0; q < kRowPairs; ++q) pair(rp.ac[(s * kRowPairs + size_t(q)) * 64 + lane]);
+        for (int q = 0; q < rp.xs[s].y; ++q) pair(rp.xac[(size_t(rp.xs[s].x) + size_t(q)) * 64 + lane]);
       }
       // the set-up pass: the start, then the elements' values behind a zero
       for (int nch : {1, 2})
