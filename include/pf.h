@@ -436,6 +436,9 @@ pf_status_t pf_subcycle_limit(pf_mesh_t m, const pf_params_t* p, int32_t* n_max_
  * chunks, keeping the fastest) and `reps` damage CG rounds (the launches of
  * one CG iteration, on a linear solve over all nodes), and scores the plan as
  *     explicit_us + cg_rounds_per_step * cg_round_us.
+ * The damage rounds depend on tile_nodes below 128 only: from there up they
+ * count with one time, and below with theirs times the ratio of the polynomial
+ * degrees (a lower degree takes more rounds).
  * The smallest score wins; pass out->best, out->best_explicit_block and
  * out->best_explicit_chunks as pf_tile_opts_t.tile_nodes, .explicit_block
  * and .explicit_chunks.
@@ -463,7 +466,7 @@ typedef struct {
     int32_t explicit_block[PF_TUNE_MAX];/* the faster explicit workgroup size (256, 512) */
     double explicit_us[PF_TUNE_MAX];    /* mean explicit-step time with that workgroup size
                                            and chunk count */
-    double cg_round_us[PF_TUNE_MAX];    /* mean damage CG round time */
+    double cg_round_us[PF_TUNE_MAX];    /* damage CG round time as scored */
     double score_us[PF_TUNE_MAX];
     int32_t best_explicit_chunks;       /* the chosen pf_tile_opts_t.explicit_chunks */
     int32_t explicit_chunks[PF_TUNE_MAX];/* the faster element chunk count (1, 2) */

@@ -34,15 +34,21 @@ struct Events {
 
 constexpr int kDefaultCandidates[] = {128, 192, 256, 384, 448, 512, 768, 1024};
 
-// Time `reps` explicit steps and `reps` damage CG rounds of one tile plan.
+// Time `reps` explicit steps and `reps` damage CG rounds of one tile plan;
+// degree: the polynomial degree of the largest instance's rounds.
 pf_status_t time_plan(const pf_mesh_desc_t* inst, int32_t n_inst, pf_dtype_t dtype, const pf_params_t* p,
                       int32_t tile_nodes, int32_t reps, hipStream_t s, double* explicit_us, int32_t* explicit_block,
-                      int32_t* explicit_chunks, double* round_us) {
+                      int32_t* explicit_chunks, double* round_us, int32_t* degree) {
   Handle h;
   pf_tile_opts_t to{tile_nodes, 0, 0, 0};
   pf_status_t st = pf_mesh_create(inst, n_inst, dtype, &to, s, &h.m);
   if (st != PF_OK) return st;
   pf_mesh_s* m = h.m;
+  std::vector<InstFix> fix(static_cast<size_t>(n_inst));
+  PF_HIP(hipMemcpy(fix.data(), m->dw.fix, sizeof(InstFix) * fix.size(), hipMemcpyDeviceToHost));
+  *degree = std::max_element(fix.begin(), fix.end(), [](const InstFix& x, const InstFix& y) {
+              return x.nnodes < y.nnodes;
+            })->ddef;
   const size_t w = (dtype == PF_F64) ? 8 : 4;
   const size_t N = size_t(m->n_nodes), Ne = size_t(m->n_elems);
   // two zero states for the ping-pong of the explicit step
@@ -136,13 +142,14 @@ extern "C" pf_status_t pf_tune_tiles(const pf_mesh_desc_t* inst, int32_t n_insta
   if (cand.empty()) cand.assign(std::begin(kDefaultCandidates), std::end(kDefaultCandidates));
   std::memset(out, 0, sizeof(*out));
   out->best = 0;
-  double best = 0.0;
   hipStream_t s = static_cast<hipStream_t>(stream);
+  int32_t degree[PF_TUNE_MAX] = {}, top = 1;
+  double common = 0.0;
   for (size_t k = 0; k < cand.size(); ++k) {
     out->tile_nodes[k] = cand[k];
     double te = 0.0, tr = 0.0;
     int32_t eb = 256, ec = 1;
-    const pf_status_t st = time_plan(inst, n_instances, dtype, p, cand[k], reps, s, &te, &eb, &ec, &tr);
+    const pf_status_t st = time_plan(inst, n_instances, dtype, p, cand[k], reps, s, &te, &eb, &ec, &tr, &degree[k]);
     out->status[k] = st;
     out->n_tried = int32_t(k + 1);
     if (st == PF_ERR_UNSUPPORTED) continue;   // the plan needs more LDS than a workgroup has
@@ -151,12 +158,24 @@ extern "C" pf_status_t pf_tune_tiles(const pf_mesh_desc_t* inst, int32_t n_insta
     out->explicit_block[k] = eb;
     out->explicit_chunks[k] = ec;
     out->cg_round_us[k] = tr;
-    out->score_us[k] = te + weight * tr;
+    top = std::max(top, degree[k]);
+    if (cand[k] >= 128 && (common == 0.0 || tr < common)) common = tr;
+  }
+  // From 128 nodes up the damage rounds run over tiles of their own, the same for
+  // every candidate: one time, the smallest measured (each candidate's own would
+  // add 16 times its noise to the score).  Smaller candidates get row tiles of
+  // their size and a lower degree, whose rounds are shorter but more: about in
+  // proportion to the degree (256x128 FP64: 12 at degree 8, 34 at degree 2).
+  double best = 0.0;
+  for (size_t k = 0; k < cand.size(); ++k) {
+    if (out->status[k] != PF_OK) continue;
+    out->cg_round_us[k] = cand[k] >= 128 ? common : out->cg_round_us[k] * top / degree[k];
+    out->score_us[k] = out->explicit_us[k] + weight * out->cg_round_us[k];
     if (out->best == 0 || out->score_us[k] < best) {
       best = out->score_us[k];
       out->best = cand[k];
-      out->best_explicit_block = eb;
-      out->best_explicit_chunks = ec;
+      out->best_explicit_block = out->explicit_block[k];
+      out->best_explicit_chunks = out->explicit_chunks[k];
     }
   }
   if (out->best == 0) return fail(PF_ERR_UNSUPPORTED, "no candidate tile size fits the device's LDS");
