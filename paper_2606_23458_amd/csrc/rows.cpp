@@ -185,7 +185,10 @@ bool row_plan_add(RowPlan& rp, const RowMesh& rm, int inst, size_t width, size_t
   Graph g;
   int dmax = 0;
   std::vector<std::vector<int32_t>> scratch(kThreads);   // per thread: the tile's local id of an element, or -1
-  // the second plan takes the handle's own tiles, whose first ring and elements are known to fit
+  // the second plan takes the handle's own tiles, for meshes on which a run of
+  // `own` nodes has too many neighbours for the LDS (hubs of thousands of them
+  // side by side) and a smaller one has not; what the explicit step's tiles may
+  // hold, which pf_mesh_create checks later, always fits here
   for (int plan = 0; plan < 2 && dmax < 1; ++plan) {
     std::vector<std::pair<size_t, size_t>> leaves;
     if (plan == 0) {

@@ -6,6 +6,7 @@
 #include <cstdlib>
 #include <numeric>
 #include <random>
+#include <set>
 
 #include "../paper_2606_23458_amd/csrc/pf_internal.hpp"
 
@@ -99,7 +100,63 @@ static void check(const RowPlan& rp, size_t width) {
   }
 }
 
+// Two hubs of 3600 triangles side by side, in one tile of the first plan and too much for it; the
+// handle's own tiles of 128 nodes keep them apart, and the second plan takes those.
+static void two_hubs() {
+  const int n = 3600;
+  std::vector<double> xy;
+  std::vector<int32_t> tri;
+  std::vector<std::set<int>> nbr;
+  for (int h = 0; h < 2; ++h) {
+    const int hub = int(xy.size() / 2);
+    xy.push_back(1e-3 * h), xy.push_back(0.0);
+    for (int i = 0; i < n; ++i) {
+      const double a = 6.283185307 * i / n;
+      xy.push_back((1.0 + h) * std::cos(a)), xy.push_back((1.0 + h) * std::sin(a));
+      tri.insert(tri.end(), {hub, hub + 1 + i, hub + 1 + (i + 1) % n});
+    }
+  }
+  const int nn = int(xy.size() / 2), ne = int(tri.size() / 3);
+  nbr.resize(size_t(nn));
+  for (int e = 0; e < ne; ++e)
+    for (int q = 0; q < 6; ++q) nbr[size_t(tri[size_t(3 * e + q / 2)])].insert(tri[size_t(3 * e + (q / 2 + 1 + q % 2) % 3)]);
+  std::vector<int32_t> ni(nn), eo(ne), te(ne);
+  std::iota(ni.begin(), ni.end(), 0);
+  std::iota(eo.begin(), eo.end(), 0);
+  std::iota(te.begin(), te.end(), 0);
+  std::vector<std::pair<size_t, size_t>> leaves;
+  for (size_t lo = 0; lo < size_t(nn); lo += 128) leaves.emplace_back(lo, std::min<size_t>(nn, lo + 128));
+  RowPlan rp;
+  rp.pos.resize(size_t(nn));
+  rp.node.resize(size_t(nn));
+  RowMesh rm{0, 0, nn, ne, xy.data(), tri.data(), ni.data(), eo.data(), te.data(), &leaves, 128};
+  CHECK(row_plan_add(rp, rm, 0, sizeof(float), 163840));
+  CHECK(rp.tiles.size() == leaves.size() && rp.dmax[0] == 1);
+  for (size_t k = 0; k < leaves.size(); ++k) {
+    const RowTile& t = rp.tiles[k];
+    CHECK(t.node0 == int(leaves[k].first) && t.nl[0] == int(leaves[k].second - leaves[k].first));
+    for (int i = 0; i < t.nl[0]; ++i) {   // every neighbour once
+      const size_t s = size_t(t.slice0 + i / 64), lane = size_t(i % 64);
+      std::set<int> got;
+      auto pair = [&](uint32_t cc, uint2 code) {
+        for (int h = 0; h < 2; ++h) {
+          const int col = int(h ? cc >> 16 : cc & 0xffffu);
+          if ((h ? code.y : code.x) == (kNoCode | kNoCode << 16)) continue;
+          CHECK(got.insert(col < t.nl[0] ? t.node0 + col : rp.halo[size_t(t.halo0 + col - t.nl[0])]).second);
+        }
+      };
+      for (size_t q = 0; q < kRowPairs; ++q) pair(rp.ac[(s * kRowPairs + q) * 64 + lane], rp.code[(s * kRowPairs + q) * 64 + lane]);
+      for (int q = 0; q < rp.xs[s].y; ++q)
+        pair(rp.xac[(size_t(rp.xs[s].x) + size_t(q)) * 64 + lane], rp.xcode[(size_t(rp.xs[s].x) + size_t(q)) * 64 + lane]);
+      CHECK(got == nbr[size_t(t.node0 + i)]);
+    }
+  }
+  check(rp, sizeof(float));
+  std::printf("two hubs ok\n");
+}
+
 int main() {
+  two_hubs();
   const Plate plates[] = {{64, 32, 0, false, 256}, {397, 211, 0, true, 256}, {120, 60, 0, true, 64},
                           {1, 1, 0, false, 256},   {3000, 1, 0, true, 256},  {0, 0, 12, false, 256},
                           {0, 0, 3000, false, 256}, {1448, 724, 0, true, 512}, {700, 300, 0, false, 256}};

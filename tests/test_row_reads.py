@@ -1,6 +1,6 @@
 """Every LDS read of the damage passes, checked on the CPU against the bytes their launch asks
 for: each degree a caller may ask for, both widths, lanes past a tile's rows, batches whose
-instances run different degrees."""
+instances run different degrees, and a mesh that only the row plan's second cut fits."""
 import os
 import subprocess
 
@@ -18,4 +18,4 @@ def test_damage_passes_read_inside_their_lds(tmp_path):
     assert res.returncode == 0, res.stderr[-2000:]
     run = subprocess.run([exe], capture_output=True, text=True, timeout=300)
     assert run.returncode == 0, run.stdout[-2000:] + run.stderr[-500:]
-    assert run.stdout.count(" ok") == 20
+    assert run.stdout.count(" ok") == 21
