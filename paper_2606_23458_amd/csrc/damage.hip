@@ -70,7 +70,6 @@
 // floating-point atomics and no device-wide fences are used.  Linear mode
 // (CG_LINEAR) solves A_FF x_F = b_F for a fixed held set and is used by the
 // adjoint step.
-#include <climits>
 #include <cstring>
 
 #include "device_common.hpp"
@@ -316,7 +315,7 @@ void rows_stiffness(pf_dtype_t dtype, const DevMesh& dm, const DevRows& dr, hipS
 // read, A written).
 template <typename T, int RPT, int OWN, bool FUSE>
 __global__ __launch_bounds__(kBlock) void k_cg_setup(DmgArgs<T> a) {
-  __shared__ double red[8 * 4 * kWaves];
+  __shared__ double red[8 * kWaves];
   const int tile = tile_of_block(a.dr.n_tiles);
   const RowTile* const tp = a.dr.tiles + tile;
   const int n_own = tp->nl[0], nall = tp->nl[1], node0 = tp->node0, halo0 = tp->halo0, slice0 = tp->slice0;
@@ -522,7 +521,7 @@ __global__ __launch_bounds__(kBlock) void k_cg_setup(DmgArgs<T> a) {
 // random diagonals 258 -> 238.
 template <typename T, int RPT, int OWN, int PAIRS, bool FUSE>
 __global__ __launch_bounds__(kBlock, RPT <= 4 ? (RPT <= 2 ? 4 : 3) : 1) void k_cg(DmgArgs<T> a) {
-  __shared__ double red[8 * 4 * kWaves];
+  __shared__ double red[8 * kWaves];
   const int tile = tile_of_block(a.dr.n_tiles);
   const RowTile* const tp = a.dr.tiles + tile;
   const int n_own = tp->nl[0];
@@ -875,7 +874,7 @@ __global__ __launch_bounds__(kBlock, RPT <= 4 ? (RPT <= 2 ? 4 : 3) : 1) void k_c
 
 // Combination of an instance's per-tile partials, in a fixed order: thread t
 // adds the partials of tiles tile0 + t, tile0 + t + block, ... in that order,
-// then the block's values are reduced (DPP rows, then a fixed-order combine);
+// then the block's values are reduced (by wave, then a fixed-order combine);
 // thread k < 8 returns value k.  k_dmg_red runs the same order with the loads
 // of kRedBatch tiles per thread in flight (it is latency-bound: one
 // workgroup, a few kilobytes; tiles past the end combine as the identity of
@@ -1023,7 +1022,7 @@ __device__ __forceinline__ void advance_solver(Ctl* c, int nnodes, const double 
 constexpr int kRedBlock = kBlock;
 __global__ __launch_bounds__(kRedBlock) void k_dmg_red(Ctl* ctl, const InstFix* fix, const double* part, int n_tiles, const int* bounds,
                                                        int kind, double tol, int max_iter) {
-  __shared__ double red[8 * 4 * (kRedBlock / 64)];
+  __shared__ double red[8 * (kRedBlock / 64)];
   __shared__ double tot[8];
   Ctl* const cp = ctl + blockIdx.x;
   Ctl cc;
@@ -1256,7 +1255,7 @@ static void launch_cg(const pf_mesh_s* m, DmgArgs<T> a, int nch, hipStream_t s) 
 
 // Element chunks of the set-up pass: two (the elements' mass coefficients and
 // their loads one after the other in LDS) when the halved space lets more
-// workgroups share a CU, or when only that fits a workgroup's LDS.
+// workgroups share a CU; the row plan takes care that one fits.
 template <typename T>
 static int damage_chunks(pf_mesh_s* m) {
   if (m->dmg_nch > 0) return m->dmg_nch;

@@ -155,33 +155,6 @@ __device__ __forceinline__ void row_reduce_all(double (&v)[K]) {
   }
 }
 
-// Several block-wide reductions at once, without LDS shuffles: each value is
-// reduced over every 16-lane row by DPP moves, lane 0 of each row stores the
-// row's results, and thread k < K combines value k's 4 NW row results in a
-// fixed order and returns it (other threads get 0).  OPS holds two bits per
-// value: 0 sum, 1 min, 2 max.  Every thread of the block must call it; `sh`
-// holds K * 4 * NW doubles and must not be in use by another reduction of the
-// block.
-template <int K, uint32_t OPS, int NW = kWaves>
-__device__ __forceinline__ double block_reduce_rows(double (&v)[K], double* sh) {
-  constexpr int R = 4 * NW;
-  row_reduce_all<K, OPS>(v);
-  const int lane = threadIdx.x & 63;
-  if ((lane & 15) == 0) {
-    const int r = (threadIdx.x >> 6) * 4 + (lane >> 4);
-#pragma unroll
-    for (int k = 0; k < K; ++k) sh[k * R + r] = v[k];
-  }
-  __syncthreads();
-  const int k = threadIdx.x;
-  if (k >= K) return 0.0;
-  const uint32_t op = (OPS >> (2 * k)) & 3u;
-  double s = sh[k * R];
-#pragma unroll
-  for (int j = 1; j < R; ++j) s = combine_op(op, s, sh[k * R + j]);
-  return s;
-}
-
 // Reduce x over the wave: the row results, then rows 0 and 2 onto rows 1 and 3
 // and row 1 onto row 3 by DPP broadcasts; lane 63 holds the result.
 constexpr int kDppBcast15 = 0x142;     // lane 15 of each row to the next row
@@ -206,9 +179,12 @@ __device__ __forceinline__ void wave_reduce_all(double (&v)[K]) {
   }
 }
 
-// Several block-wide reductions at once, as block_reduce_rows but with the
-// rows of a wave combined by DPP as well: thread k < K is left with NW values
-// to combine instead of 4 NW.  `sh` holds K * NW doubles.
+// Several block-wide reductions at once, without LDS shuffles: each value is
+// reduced over every wave by DPP moves, lane 63 stores the wave's results, and
+// thread k < K combines value k's NW wave results in a fixed order and returns
+// it (other threads get 0).  OPS holds two bits per value: 0 sum, 1 min, 2 max.
+// Every thread of the block must call it; `sh` holds K * NW doubles and must not
+// be in use by another reduction of the block.
 template <int K, uint32_t OPS, int NW = kWaves>
 __device__ __forceinline__ double block_reduce_waves(double (&v)[K], double* sh) {
   wave_reduce_all<K, OPS>(v);
@@ -242,8 +218,9 @@ __device__ __forceinline__ double block_sum(double v, double* sh) {
   return s;
 }
 
-// Several block-wide reductions at once; only thread 0's v holds the block
-// results afterwards.  Same scheme and arguments as block_reduce_rows.
+// Several block-wide reductions at once, as block_reduce_waves but over 16-lane
+// rows; only thread 0's v holds the block results afterwards, and `sh` holds
+// K * 4 * NW doubles.
 template <int K, uint32_t OPS, int NW = kWaves>
 __device__ __forceinline__ void block_reduce_to0(double (&v)[K], double* sh) {
   constexpr int R = 4 * NW;
