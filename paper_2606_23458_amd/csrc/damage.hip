@@ -305,6 +305,52 @@ void rows_stiffness(pf_dtype_t dtype, const DevMesh& dm, const DevRows& dr, hipS
     hipLaunchKernelGGL(k_rows_stiffness<float>, dim3(dr.n_tiles), dim3(kBlock), 0, s, dm, dr);
 }
 
+// The mass coefficient of an element, and a row's entry from its stiffness part
+// and the coefficients of the pair's elements.
+template <typename T>
+__device__ __forceinline__ T elem_mass(const InstP<T>& P, T area, T ph, T He) {
+  return (P.c0 * ph + P.cH * He) * area * T(1.0 / 12.0);
+}
+template <typename T>
+__device__ __forceinline__ T row_entry(double kap, T sv, double m0, double m1) {
+  return T(kap * double(sv) + (m0 + m1));
+}
+
+// DevRows::idle of a tile
+enum { TILE_IDLE = 1, TILE_NO_RINGS = 2 };
+
+// The ring rows that the set-up left out, up to row nrow: taken by a tile that
+// turns out to own free nodes after all.  A rare path and slow, one row per
+// thread and every value from memory; the entries have the set-up's bits.
+template <typename T>
+__device__ __forceinline__ void late_rings(const DmgArgs<T>& a, const RowTile* tp, const InstP<T>* P, int nrow) {
+  const T* const gcs = static_cast<const T*>(a.dm.gcs);
+  const T* const area = static_cast<const T*>(a.dr.earea) + tp->el0;
+  const double kap = double(P->kap);
+  auto mass = [&](uint32_t cd) {
+    const int e = int(cd & kCodeElem) - 1;
+    if (e < 0) return 0.0;
+    return double(elem_mass<T>(*P, area[e], gcs ? gcs[a.dr.ete[tp->el0 + e]] : T(1), a.H[a.dr.egid[tp->el0 + e]]));
+  };
+  auto entry = [&](Two<T> sv, uint2 cd) {
+    return Two<T>{row_entry<T>(kap, sv.x, mass(cd.x), mass(cd.x >> 16)), row_entry<T>(kap, sv.y, mass(cd.y), mass(cd.y >> 16))};
+  };
+#pragma unroll 1
+  for (int i = tp->nl[0] + threadIdx.x; i < nrow; i += kBlock) {
+    const int sl = tp->slice0 + i / 64;
+    const int2 x = a.dr.xs[sl];
+#pragma unroll 1
+    for (int q = 0; q < kRowPairs + x.y; ++q) {
+      const bool base = q < kRowPairs;
+      const size_t at = (base ? size_t(sl) * kRowPairs + q : size_t(x.x) + (q - kRowPairs)) * 64 + i % 64;
+      const Two<T>* const sv = static_cast<const Two<T>*>(base ? a.dr.sv : a.dr.xsv);
+      Two<T>* const av = static_cast<Two<T>*>(base ? a.dr.av : a.dr.xav);
+      av[at] = entry(sv[at], (base ? a.dr.code : a.dr.xcode)[at]);
+    }
+  }
+  __syncthreads();
+}
+
 // The first restart of a solve: the rows of this solve, A_ij = kap S_ij + the
 // mass coefficients of the pair's elements, the load and the diagonal, and the
 // true residual of the start,
@@ -312,7 +358,9 @@ void rows_stiffness(pf_dtype_t dtype, const DevMesh& dm, const DevRows& dr, hipS
 // The mass coefficients and loads of the tile's elements stand in LDS, together
 // or (nch = 2) one after the other in half the space; no value depends on that.
 // Sums in FP64, rounded once.  Bound by the bytes of the rows (S and the codes
-// read, A written).
+// read, A written), so on large handles (not FUSE) a tile of an AT1 plate whose
+// owned nodes all start held leaves its rings out: it will sit out the CG runs
+// (see late_rings).
 template <typename T, int RPT, int OWN, bool FUSE>
 __global__ __launch_bounds__(kBlock) void k_cg_setup(DmgArgs<T> a) {
   __shared__ double red[8 * kWaves];
@@ -329,11 +377,45 @@ __global__ __launch_bounds__(kBlock) void k_cg_setup(DmgArgs<T> a) {
   const bool monotone = projected && (c->flavor != 0);
   const double tol = a.tol;
   const int deg = cg_degree(a.fix[inst], a.deg);
-  const int nrow = tp->nl[deg - 1], nel = tp->nel[deg - 1];
+  int nrow = tp->nl[deg - 1], nel = tp->nel[deg - 1];
   const int tid = threadIdx.x;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   extern __shared__ __align__(16) unsigned char smem[];
   T* const ya = reinterpret_cast<T*>(smem);   // [nall] the start
+  // the start: d_prev (or its extrapolation in time), or 1 where the guess
+  // holds the node at the upper bound; linear solves at the caller's x
+  auto held_at = [&](int g, T xv) -> uint8_t {   // the held state that a node starts with
+    if (!qp) return a.win[g];
+    if (!projected) return HELD_NONE;
+    const T lbv = a.lb[g];
+    if (lbv >= T(1)) return HELD_FIXED;   // d_prev = 1: the node is fixed
+    const uint8_t gs = a.guess ? a.guess[g] : uint8_t(0);
+    return ((gs & PF_ACTIVE_LOWER) && xv <= lbv) ? HELD_LOWER
+                                                 : (((gs & PF_ACTIVE_UPPER) && xv >= T(1)) ? HELD_UPPER : HELD_NONE);
+  };
+  // AT1 alone: its threshold holds most nodes of a plate, AT2 holds hardly any,
+  // and asking first puts the elements' loads behind the nodes'
+  const bool ask = !FUSE && !monotone && P->model == PF_AT1;
+  bool rings = false;
+  for (int i = tid; i < nall; i += kBlock) {
+    const int g = i < n_own ? a.dr.node[node0 + i] : a.dr.hnode[halo0 + i - n_own];
+    T v;
+    if (!qp) {
+      v = a.dout[g];
+    } else {
+      v = a.lb[g];
+      if (a.start) v = clamp01<T>(T(2) * v - a.dout[g], v);
+      if (projected && a.guess && (a.guess[g] & PF_ACTIVE_UPPER)) v = T(1);
+    }
+    ya[i] = v;
+    if (ask && i < n_own) rings = rings || held_at(g, v) == HELD_NONE;
+  }
+  if constexpr (!FUSE) {
+    if (ask) rings = __syncthreads_or(rings);
+    const bool left_out = ask && !rings;
+    if (tid == 0) a.dr.idle[tile] = left_out ? TILE_NO_RINGS : 0;
+    if (left_out) nrow = n_own, nel = tp->nel[0];
+  }
   // [1 + nel] mass coefficients (nch = 2: then the loads) of the elements, 0
   // first for entries of fewer than two elements
   T* const sm = ya + nall;
@@ -365,23 +447,9 @@ __global__ __launch_bounds__(kBlock) void k_cg_setup(DmgArgs<T> a) {
     }
   };
 
-  // the start: d_prev (or its extrapolation in time), or 1 where the guess
-  // holds the node at the upper bound; linear solves at the caller's x
-  for (int i = tid; i < nall; i += kBlock) {
-    const int g = i < n_own ? a.dr.node[node0 + i] : a.dr.hnode[halo0 + i - n_own];
-    T v;
-    if (!qp) {
-      v = a.dout[g];
-    } else {
-      v = a.lb[g];
-      if (a.start) v = clamp01<T>(T(2) * v - a.dout[g], v);
-      if (projected && a.guess && (a.guess[g] & PF_ACTIVE_UPPER)) v = T(1);
-    }
-    ya[i] = v;
-  }
-  const T c0 = P->c0, cH = P->cH, b0 = P->b0, bH = P->bH;
+  const T b0 = P->b0, bH = P->bH;
   elements([&](int l, T A, T ph, T He) {
-    sm[1 + l] = (c0 * ph + cH * He) * A * T(1.0 / 12.0);
+    sm[1 + l] = elem_mass<T>(*P, A, ph, He);
     if (a.nch != 2) sb[1 + l] = (b0 * ph + bH * He) * A * T(1.0 / 3.0);
   });
   if (tid == 0) sm[0] = sb[0] = T(0);
@@ -406,8 +474,8 @@ __global__ __launch_bounds__(kBlock) void k_cg_setup(DmgArgs<T> a) {
     auto pair = [&](Two<T> sv, uint2 cd, uint32_t cc, Two<T>& out) {
       auto mass = [&](uint32_t e) { return double(sm[e & kCodeElem]); };
       const double m0 = mass(cd.x), m1 = mass(cd.y);
-      out.x = T(kap * double(sv.x) + (m0 + mass(cd.x >> 16)));
-      out.y = T(kap * double(sv.y) + (m1 + mass(cd.y >> 16)));
+      out.x = row_entry<T>(kap, sv.x, m0, mass(cd.x >> 16));
+      out.y = row_entry<T>(kap, sv.y, m1, mass(cd.y >> 16));
       if (!own) return;
       rs[k] += m0;
       rs[k] += m1;
@@ -472,23 +540,14 @@ __global__ __launch_bounds__(kBlock) void k_cg_setup(DmgArgs<T> a) {
     const T ri = T(double(bi) - (double(rsv) * double(xv) + qi[k]));
     const T di = T(1.0 / (double(rsv) - off[k]));   // the diagonal from the rows' sums
     const double sr = double(ri) * double(di);
-    uint8_t w = HELD_NONE;
+    const uint8_t w = held_at(g, xv);
     if (!qp) {
-      w = a.win[g];
       if (w == HELD_NONE) rb = fmax(rb, fabs(double(bi) * double(di)));
     } else {
       const T lbv = a.lb[g];
       a.lbr[q0] = lbv;
-      if (projected) {
-        if (lbv >= T(1)) {
-          w = HELD_FIXED;   // d_prev = 1: the node is fixed
-        } else {
-          const uint8_t gs = a.guess ? a.guess[g] : uint8_t(0);
-          w = ((gs & PF_ACTIVE_LOWER) && xv <= lbv) ? HELD_LOWER
-                                                    : (((gs & PF_ACTIVE_UPPER) && xv >= T(1)) ? HELD_UPPER : HELD_NONE);
-          if (!monotone) nc.restart_would_change(w, double(lbv), double(xv), sr, tol);
-        }
-      }
+      if (projected && !monotone && w != HELD_FIXED)
+        nc.restart_would_change(w, double(lbv), double(xv), sr, tol);
     }
     a.b[q0] = bi;
     a.rsum[q0] = rsv;
@@ -549,7 +608,7 @@ __global__ __launch_bounds__(kBlock, RPT <= 4 ? (RPT <= 2 ? 4 : 3) : 1) void k_c
   const bool monotone = projected && (flavor != 0);
   const bool xpass = (mode == MODE_RESTART || mode == MODE_CHECK);
   const bool iter = (mode == MODE_ITER);
-  if (iter && !monotone && idle_tile) {
+  if (iter && !monotone && (idle_tile & TILE_IDLE)) {
     // no free node here: z, p and the update of x are 0 (see the first pass)
     double v[8] = {0.0, INFINITY, 0.0, 0.0, -INFINITY, 0.0, 0.0, 0.0};
     finish_pass<T, FUSE>(a, inst, v, tile, bnd, red);
@@ -735,7 +794,10 @@ __global__ __launch_bounds__(kBlock, RPT <= 4 ? (RPT <= 2 ? 4 : 3) : 1) void k_c
 #pragma unroll
       for (int k = 0; k < RPT; ++k) free_node = free_node || (k < OWN && tid + k * kBlock < n_own && !(dmv[k] < T(0)));
       const bool idle = !__syncthreads_or(free_node);
-      if (tid == 0) a.dr.idle[tile] = idle;
+      const bool late = !FUSE && (idle_tile & TILE_NO_RINGS) != 0;
+      if (tid == 0) a.dr.idle[tile] = idle ? TILE_IDLE | (late ? TILE_NO_RINGS : 0) : 0;
+      if constexpr (!FUSE)
+        if (late && !idle) late_rings(a, tp, P, tp->nl[dset - 1]);
       if (idle) {
         for (int i = tid; i < n_own; i += kBlock) xn_[node0 + i] = xc[node0 + i];
         double v[8] = {0.0, INFINITY, 0.0, 0.0, -INFINITY, 0.0, 0.0, 0.0};

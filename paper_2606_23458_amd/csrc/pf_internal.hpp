@@ -198,7 +198,8 @@ struct DevRows {
   void* xsv;                    // [xpair][64][2]
   void* av;                     // [slice][kRowPairs][64][2] entries of the running solve (mesh dtype)
   void* xav;                    // [xpair][64][2]
-  int32_t* idle;                // [tile] 1 where the tile owns no free node of the running CG run
+  int32_t* idle;                // [tile] TILE_IDLE: it owns no free node of the running CG run; TILE_NO_RINGS:
+                                // its ring rows were not assembled in this solve (damage.hip)
   int32_t n_tiles;
 };
 

@@ -1,0 +1,103 @@
+"""On handles whose rounds take a reduction launch, a row tile whose owned nodes all start held
+leaves its ring rows out of the set-up and assembles them when its nodes are released.  Solves that
+begin with (nearly) everything held and end with much of it free, against the exact minimiser of
+the QP and against the bits of a repeat; polled, in fixed windows with resumed continuations, and
+by the monotone flavour.  Tolerances: the solver's stopping residual (1e-12 FP64, 1e-6 FP32) times
+the operator's condition number (about 30 at l0 = 2h), with a factor of three."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as w
+from oracle.damage import DamageQP
+from oracle.step import Sim as OSim
+
+pytestmark = pytest.mark.gpu
+
+TOL = {"f64": 1e-10, "f32": 1e-4}
+
+
+def _problem(model):
+    """709 row tiles of 64 nodes; a history well above AT1's threshold in one quarter."""
+    p = w.small_plate(300, 150, jitter=0.15, seed=6, model=model, random_diag=True).with_(d0=np.zeros(301 * 151))
+    cen = p.xy[p.tri].mean(1)
+    hc = 3 * p.Gc / (16 * p.l0)
+    H = 0.5 * hc + 40 * hc * np.exp(-((cen - cen.min(0)) ** 2).sum(1) / (40 * 2.5e-4) ** 2)
+    return p, H
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("model,precond,mode", [(1, 0, "polled"), (1, 2, "polled"), (1, 1, "polled"), (2, 0, "polled"),
+                                                (1, 0, "resumed"), (1, 0, "monotone"), (1, 0, "field")])
+def test_tiles_released_after_the_set_up(dtype, model, precond, mode):
+    from paper_2606_23458_amd import Mesh, Simulator, State
+    from paper_2606_23458_amd.sim import CgConfig, default_tol
+    p, H = _problem(model)
+    phi = None
+    mesh = Mesh([p], dtype, 64)
+    cg = dict(tol=default_tol(dtype), start=0, precond=precond, max_iter=4000)
+    sim = Simulator(p, dtype=dtype, mesh=mesh)
+    if mode == "field":
+        phi = np.random.default_rng(2).uniform(0.6, 1.5, p.n_elems)
+        sim.set_gc_field([phi])
+    z = np.zeros((p.n_nodes, 2))
+    s = State.from_user(mesh, [{"u": z, "v": z, "a": z, "d": z[:, 0], "H": H}])
+    other = State.from_user(mesh, [{"u": z, "v": z, "a": z, "d": z[:, 0], "H": 1e3 * H[::-1].copy()}])
+    held = torch.ones(mesh.n_nodes, dtype=torch.uint8, device="cuda")
+    got = []
+    for _ in range(2):
+        d, act = torch.zeros_like(s.d), torch.zeros_like(held)
+        # rows of another solve, with entries a thousand times larger, stand in the handle before
+        sim.damage(other.H, other.d, d, act, cg=CgConfig(**cg))
+        if mode == "resumed":
+            opt = dict(cg, check_every=0, rounds=3)
+            sim.damage(s.H, s.d, d, act, held, cg=CgConfig(**opt))
+            for _ in range(200):
+                sim.damage(s.H, s.d, d, act, held, cg=CgConfig(**opt, resume=1))
+        else:
+            sim.damage(s.H, s.d, d, act, held, cg=CgConfig(**cg, monotone=int(mode == "monotone")))
+        torch.cuda.synchronize()
+        st = sim.cg_stats()[0]
+        assert st["flags"] == 0, st
+        got.append(d.clone())
+    assert torch.equal(got[0], got[1])
+    ref = DamageQP(OSim(p).mesh, p.l0, model).solve(H, p.Gc, z[:, 0], phi)[0]
+    free = np.count_nonzero(ref)
+    assert (0.05 if model == 1 else 0.9) * p.n_nodes < free, free
+    assert np.max(np.abs(mesh.nodes_from_internal(got[0].double())[0] - ref)) < TOL[dtype], st
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+def test_adjoint_of_a_mostly_held_state(dtype):
+    """The adjoint solve on the released state: its tiles without free nodes have no ring rows."""
+    from paper_2606_23458_amd import Mesh, Simulator, State
+    from paper_2606_23458_amd.grad import backward_step
+    import scipy.sparse.linalg as spla
+    from oracle.damage import assemble_damage
+    p, H = _problem(1)
+    mesh = Mesh([p], dtype, 64)
+    sim = Simulator(p, dtype=dtype, mesh=mesh)
+    z = np.zeros((p.n_nodes, 2))
+    s0 = State.from_user(mesh, [{"u": z, "v": z, "a": z, "d": z[:, 0], "H": H}])
+    s1, act = State(mesh), torch.zeros(mesh.n_nodes, dtype=torch.uint8, device="cuda")
+    sim.step_into(s0, s1, act, torch.ones_like(act))
+    dbar = 1e-2 * (1.5 + np.cos(p.xy[:, 0] / (9 * 2.5e-4)))
+    adj1, adj0 = State(mesh), State(mesh)
+    adj1.nodes[6].copy_(torch.tensor(mesh.nodes_to_internal([dbar])).to(mesh.dtype))
+    dgc = torch.zeros(1, dtype=torch.float64, device="cuda")
+    backward_step(sim, s0, s1, act, adj1, adj0, dgc)
+    torch.cuda.synchronize()
+    st = sim.cg_stats()[0]
+    assert st["flags"] == 0, st
+    # the adjoint of H_n: 2 lambda'w^e - 2 lambda'M^e d on every element (the step's own H is unchanged)
+    got = s1.to_user()[0]
+    free = np.flatnonzero(mesh.nodes_from_internal(act)[0] == 0)
+    A, _ = assemble_damage(OSim(p).mesh, H, p.Gc, p.l0, 1)
+    lam = np.zeros(p.n_nodes)
+    lam[free] = spla.spsolve(A[free][:, free].tocsc(), dbar[free])
+    area = OSim(p).mesh.area.numpy()
+    le, de = lam[p.tri], got["d"][p.tri]
+    lmd = area / 12 * ((le * de).sum(1) + le.sum(1) * de.sum(1))
+    want = 2 * area / 3 * le.sum(1) - 2 * lmd
+    hbar = adj0.to_user()[0]["H"]
+    assert np.max(np.abs(hbar - want)) < TOL[dtype] * np.max(np.abs(want)) * 10, st
