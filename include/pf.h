@@ -164,7 +164,7 @@ typedef struct {
                                 unfinished by this handle's previous
                                 pf_damage_solve call with the same arguments
                                 (no set-up pass; iterate, held set and CG
-                                scalars are kept).  Every call ends with the
+                                scalars are kept; H as it was).  Every call ends with the
                                 final pass, so d, active_out and stats always
                                 hold the current iterate.  A precond above that
                                 of the call that began the solve runs as that
@@ -179,7 +179,8 @@ typedef struct {
                                 [lmax/30, lmax] where lmax bounds the spectrum
                                 of D^-1 A (from the mesh, so M is SPD).  0: the
                                 degree that is fastest for the instance's size
-                                (the library's choice).  A round makes `degree`
+                                (the library's choice; 0 used to mean Jacobi,
+                                which 1 has always meant).  A round makes `degree`
                                 matrix-vector products, in one pass over the
                                 tiles, and one reduction; max_iter and the
                                 iteration counts of pf_cg_stats_t count rounds.

@@ -33,12 +33,22 @@ namespace {
 //   FP32   256x128 8/128 164, 202   6/256 174, 223   4/256 199, 230
 //          512x256 8/128 317, 277   6/256 252, 238   4/256 264, 255   6/384 281, 270
 //         1024x512 8/128 445, 441   6/256 354, 342   4/256 390, 325   6/384 375, 363
-//         1448x724 6/256 545, 562   5/512 580, 553   3/685 614, 532
-// A batch of 16 plates of up to 512x256 in FP32 takes 599 at 6/256 and 660 with
-// 128 owned nodes on its smaller plates, so these take 256 as well.  On a
-// million nodes the set-up pass, which assembles every ring row once, is much
-// of a step with few free nodes, and larger tiles have the fewest (a
-// perforated plate of that size: 508 at 6/256, 458 at 3/685).
+// 8/128 suits a small FP32 plate by itself, but a batch of 16 plates of up to
+// 512x256 takes 599 at 6/256 and 660 with 128 owned nodes on its smaller ones,
+// and both have to get the same tiles: 6/256 costs the single plate 6 to 10 %.
+//
+// On a million nodes the set-up pass, which assembles a tile's ring rows too, is
+// much of a step with few free nodes, and larger tiles have the fewest.  FP32,
+// us per polled step at 6/256 and at 3/704, of an AT2 plate (regular, random
+// diagonals) and of AT1 plates whose damage hardly moves:
+//   534k nodes 275 / 277, 310 / 314   AT1 119 / 129, 135 / 112
+//   702k       333 / 370, 369 / 439       150 / 160, 165 / 148
+//   836k       379 / 399, 416 / 477       167 / 146, 155 / 177
+//   877k       382 / 410, 431 / 494       163 / 137, 217 / 174
+//   1.05M      441 / 453, 509 / 545       181 / 158, 235 / 177   perforated 226 / 187
+//   2.1M       865 / 773, 983 / 1034      337 / 302, 405 / 315
+// The line at 768k nodes is where the AT1 plates begin to gain (up to 25 %); AT2
+// plates up to a million nodes pay 3 to 15 % for it.
 //
 // Callers that ask for tiles of less than 128 nodes get them, and degree 2:
 // the rings of a higher one would outnumber their nodes.
