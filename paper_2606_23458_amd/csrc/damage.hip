@@ -411,7 +411,7 @@ __global__ __launch_bounds__(kBlock) void k_cg_setup(DmgArgs<T> a) {
         // back down (perforated plate, steps 21-80, windowed: 1 round each in place
         // of 1 to 5, FP32 217 -> 138 us per step, FP64 267 -> 215)
         const T e = clamp01<T>(T(2) * lbv - a.dout[g], lbv);
-        if (double(e) - double(lbv) > tol) v = e;
+        if (!(double(e) - double(lbv) <= tol)) v = e;   // a NaN goes on to be reported
       }
       if (projected && a.guess && (a.guess[g] & PF_ACTIVE_UPPER)) v = T(1);
     }

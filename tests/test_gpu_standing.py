@@ -35,3 +35,17 @@ def test_standing_damage_settles(dtype, model, nx, ny):
         prev, cur, act = cur, out, act2
     assert rounds[0] > 3
     assert rounds[12:] == [1] * 48 and all(same[12:]), rounds
+
+
+def test_non_finite_start_is_reported():
+    """A NaN in the output array, which holds the damage before d_prev on entry, is not hidden."""
+    from paper_2606_23458_amd import Simulator
+    from paper_2606_23458_amd._lib import PF_ERR_NONFINITE, PfError
+    p = w.small_plate(60, 30, seed=2, model=2)
+    sim = Simulator(p, dtype="f64")
+    H = torch.full((p.n_elems,), 500.0, dtype=torch.float64, device="cuda")
+    out = torch.zeros_like(sim.state.d)
+    out[7] = float("nan")
+    with pytest.raises(PfError) as e:
+        sim.damage(H, sim.state.d, out, torch.zeros_like(sim.active), sim.active)
+    assert e.value.status == PF_ERR_NONFINITE
