@@ -47,8 +47,9 @@
 //
 // One round of the solve is one or two launches:
 //   k_cg_setup the solve's first restart: b, the diagonal and the rows of A that
-//              a tile multiplies by (owned nodes and rings) from the element
-//              operator, the start and its true residual;
+//              a tile multiplies by (owned nodes and rings; large AT1 plates
+//              leave the rings of held tiles out) from the element operator,
+//              the start and its true residual;
 //   k_cg       one pass of the current phase for every row tile of every
 //              instance that is not done:
 //                restart / check: x-matvec in FP64, true residual, held-set
@@ -358,7 +359,7 @@ __device__ __forceinline__ void late_rings(const DmgArgs<T>& a, const RowTile* t
 // The mass coefficients and loads of the tile's elements stand in LDS, together
 // or (nch = 2) one after the other in half the space; no value depends on that.
 // Sums in FP64, rounded once.  Bound by the bytes of the rows (S and the codes
-// read, A written), so on large handles (not FUSE) a tile of an AT1 plate whose
+// read, A written: 331 MB in 62 us on the 1024x512 FP64 plate), so on large handles (not FUSE) a tile of an AT1 plate whose
 // owned nodes all start held leaves its rings out: it will sit out the CG runs
 // (see late_rings).
 template <typename T, int RPT, int OWN, bool FUSE>
@@ -576,8 +577,10 @@ __global__ __launch_bounds__(kBlock) void k_cg_setup(DmgArgs<T> a) {
 // pass (a row is multiplied deg times), the vector being multiplied in LDS;
 // PAIRS = 4: the first extra pair of a longer row as well (with random
 // diagonals nearly every slice has one, and each product would load it again).
-// A workgroup's time is latency: on the 256x128 plate (one workgroup per CU) it
-// was 22 thousand clocks, of which the control block and the vectors 5.5, nine
+// On large plates the rows' bytes bound it, ring rows included: 158 MB per pass of
+// the 1024x512 FP64 plate in 32 us, 0.95 of a copy's rate (FP32 94 MB in 22 us,
+// 0.82).  On small ones a workgroup's time is latency: on the 256x128 plate (one
+// workgroup per CU) it was 22 thousand clocks, of which the control block and the vectors 5.5, nine
 // products 10.6 and the reduction with the arrival 5.4.  So whatever the
 // start needs is asked for at once, a thread's rows are summed side by side
 // (row_sums), the two halves of the vector in LDS share their addresses, and
