@@ -12,7 +12,7 @@
  *                       history maximum (Sec. 2.1-2.3, eq. spectral_split,
  *                       eq. amor_split, eq. vv_u, eq. vv_a, eq. vv_v);
  *   - pf_damage_solve   the bound-constrained AT1/AT2 damage update by a
- *                       matrix-free projected preconditioned CG (Sec. 2.2,
+ *                       projected preconditioned CG (Sec. 2.2,
  *                       eq. damage_pde_at2, eq. damage_pde_at1; Sec. 2.4);
  *   - pf_step_backward  the reverse (adjoint) of one staggered step, with
  *                       the damage solve differentiated implicitly

@@ -101,3 +101,33 @@ def test_adjoint_of_a_mostly_held_state(dtype):
     want = 2 * area / 3 * le.sum(1) - 2 * lmd
     hbar = adj0.to_user()[0]["H"]
     assert np.max(np.abs(hbar - want)) < TOL[dtype] * np.max(np.abs(want)) * 10, st
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+def test_batch_with_late_rings_has_the_bits_of_single_plates(dtype):
+    """Eight plates of about 470 row tiles: their handle takes reduction launches and leaves rings
+    out, a handle of one of them combines in its passes and assembles every row in the set-up."""
+    from paper_2606_23458_amd import Simulator, State
+    from paper_2606_23458_amd.sim import CgConfig, default_tol
+    cg = CgConfig(tol=default_tol(dtype), start=0)
+    out = []
+    for plates in (8, 1):
+        p = w.small_plate(400, 299, jitter=0.15, seed=6, model=1, random_diag=True).with_(d0=np.zeros(401 * 300))
+        cen = p.xy[p.tri].mean(1)
+        hc = 3 * p.Gc / (16 * p.l0)
+        H = 0.5 * hc + 40 * hc * np.exp(-((cen - cen.min(0)) ** 2).sum(1) / (50 * 2.5e-4) ** 2)
+        sim = Simulator([p] * plates, dtype=dtype)
+        z = np.zeros((p.n_nodes, 2))
+        s = State.from_user(sim.mesh, [{"u": z, "v": z, "a": z, "d": z[:, 0], "H": H}] * plates)
+        d, act = torch.zeros_like(s.d), torch.zeros_like(sim.active)
+        sim.timer(True)
+        sim.damage(s.H, s.d, d, act, torch.ones_like(act), cg=cg)
+        _, reductions = sim.timer_read(4)
+        sim.timer(False)
+        assert (reductions > 0) == (plates == 8)
+        st = sim.cg_stats()
+        assert all(x["flags"] == 0 and x["restarts"] > 0 for x in st), st
+        out.append((sim.mesh.nodes_from_internal(d), sim.mesh.nodes_from_internal(act)))
+    for k in range(8):
+        assert np.array_equal(out[0][0][k], out[1][0][0]) and np.array_equal(out[0][1][k], out[1][1][0])
+    assert np.count_nonzero(out[1][0][0]) > 500
