@@ -272,9 +272,10 @@ __device__ __forceinline__ void finish_pass(const DmgArgs<T>& a, int inst, doubl
 }
 
 // Stiffness part of the rows, sum phi_e K^e_ij over an entry's elements: once
-// per handle with phi_e = 1, and in a copy of its own whenever a toughness
-// field is set, so that a graph captured with or without one keeps its rows.  The element operator's entries are kap phi_e K^e + mA (1 + delta_kl)
-// with K^e given by its off-diagonals K01, K02, K12 (its rows sum to zero).
+// per handle with phi_e = 1, and in a copy of its own whenever a toughness field
+// is set, so that a graph captured with or without one keeps its rows.  The
+// element operator's entries are kap phi_e K^e + mA (1 + delta_kl) with K^e given
+// by its off-diagonals K01, K02, K12 (its rows sum to zero).
 template <typename T>
 __global__ __launch_bounds__(kBlock) void k_rows_stiffness(DevMesh dm, DevRows dr) {
   const RowTile* const tp = dr.tiles + blockIdx.x;
@@ -359,9 +360,10 @@ __device__ __forceinline__ void late_rings(const DmgArgs<T>& a, const RowTile* t
 // The mass coefficients and loads of the tile's elements stand in LDS, together
 // or (nch = 2) one after the other in half the space; no value depends on that.
 // Sums in FP64, rounded once.  Bound by the bytes of the rows (S and the codes
-// read, A written: 331 MB in 62 us on the 1024x512 FP64 plate), so on large handles (not FUSE) a tile of an AT1 plate whose
-// owned nodes all start held leaves its rings out: it will sit out the CG runs
-// (see late_rings).
+// read, A written: 331 MB in 62 us on the 1024x512 FP64 plate), so on large
+// handles (not FUSE) a tile of an AT1 plate whose owned nodes all start held
+// leaves its rings out: it will sit out the CG runs (see late_rings).  Standing
+// perforated plate, us per windowed step: FP64 331 -> 267, FP32 polled 194 -> 187.
 template <typename T, int RPT, int OWN, bool FUSE>
 __global__ __launch_bounds__(kBlock) void k_cg_setup(DmgArgs<T> a) {
   __shared__ double red[8 * kWaves];
@@ -579,16 +581,16 @@ __global__ __launch_bounds__(kBlock) void k_cg_setup(DmgArgs<T> a) {
 // diagonals nearly every slice has one, and each product would load it again).
 // On large plates the rows' bytes bound it, ring rows included: 158 MB per pass of
 // the 1024x512 FP64 plate in 32 us, 0.95 of a copy's rate (FP32 94 MB in 22 us,
-// 0.82).  On small ones a workgroup's time is latency: on the 256x128 plate (one
-// workgroup per CU) it was 22 thousand clocks, of which the control block and the vectors 5.5, nine
-// products 10.6 and the reduction with the arrival 5.4.  So whatever the
-// start needs is asked for at once, a thread's rows are summed side by side
-// (row_sums), the two halves of the vector in LDS share their addresses, and
-// the reduction ends in DPP (block_reduce_waves) on four values where only four
-// are new: 18.5 thousand clocks.  Measured, us per step: FP64 64x32 227 -> 191,
-// 256x128 246 -> 219, 1024x512 775 -> 733; FP32 397x211 238 -> 209, 16 plates
-// 584 -> 512.  OWN = 1: FP64 1024x512 764 -> 742; PAIRS = 4: FP32 397x211 with
-// random diagonals 258 -> 238.
+// 0.83).  On small ones a workgroup's time is latency: on the 256x128 plate (one
+// workgroup per CU) it was 22 thousand clocks, of which the control block and the
+// vectors 5.5, nine products 10.6 and the reduction with the arrival 5.4.  So
+// whatever the start needs is asked for at once, a thread's rows are summed side
+// by side (row_sums), the two halves of the vector in LDS share their addresses,
+// and the reduction ends in DPP (block_reduce_waves) on four values where only
+// four are new: 18.5 thousand clocks.  Measured, us per step: FP64 64x32 227 ->
+// 191, 256x128 246 -> 219, 1024x512 775 -> 733; FP32 397x211 238 -> 209, 16
+// plates 584 -> 512.  OWN = 1: FP64 1024x512 764 -> 742; PAIRS = 4: FP32 397x211
+// with random diagonals 258 -> 238.
 template <typename T, int RPT, int OWN, int PAIRS, bool FUSE>
 __global__ __launch_bounds__(kBlock, RPT <= 4 ? (RPT <= 2 ? 4 : 3) : 1) void k_cg(DmgArgs<T> a) {
   __shared__ double red[8 * kWaves];
