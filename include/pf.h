@@ -147,8 +147,9 @@ typedef struct {
                                 1: start from clamp(2 d_prev - d, d_prev, 1),
                                 where the output array d holds, on entry, the
                                 damage of the step before d_prev (a linear
-                                extrapolation in time), where that is more than
-                                tol above d_prev, and from d_prev elsewhere.  pf_step_backward:
+                                extrapolation in time); in FP32 from d_prev
+                                where that is no more than tol above it.
+                                pf_step_backward:
                                 1: warm start from the multipliers of the
                                 handle's previous calls; 0: start from zero and
                                 forget them (the first call of a reverse sweep,

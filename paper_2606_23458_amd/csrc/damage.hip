@@ -409,12 +409,15 @@ __global__ __launch_bounds__(kBlock) void k_cg_setup(DmgArgs<T> a) {
       const T lbv = a.lb[g];
       v = lbv;
       if (a.start) {
-        // no movement within tol is carried on: a start that creeps upward by it
-        // step after step leaves the tolerance again and again, and d cannot come
-        // back down (perforated plate, steps 21-80, windowed: 1 round each in place
-        // of 1 to 5, FP32 217 -> 138 us per step, FP64 267 -> 215)
         const T e = clamp01<T>(T(2) * lbv - a.dout[g], lbv);
-        if (!(double(e) - double(lbv) <= tol)) v = e;   // a NaN goes on to be reported
+        // FP32: no movement within tol is carried on, as a start that creeps upward
+        // by it step after step leaves the tolerance again and again, and d cannot
+        // come back down (perforated plate, steps 21-80, windowed: 1 round each in
+        // place of 1 to 5, 217 -> 138 us per step).  FP64, the type of gradients,
+        // carries every movement on (267 us there, 215 without): where the terms of
+        // dL/dGc cancel, the sum is the residual of this start, and another start
+        // changes all its digits.
+        if (sizeof(T) == 8 || !(double(e) - double(lbv) <= tol)) v = e;   // a NaN goes on to be reported
       }
       if (projected && a.guess && (a.guess[g] & PF_ACTIVE_UPPER)) v = T(1);
     }
